@@ -2,12 +2,9 @@
 // matrix cores (GEMMs with fused bias / GELU epilogues, GELU backward, column sums,
 // loss, Adam) and fused BF16 inference.
 //
-// GEMM tiles: a workgroup of four wavefronts computes a 64 x 64 block of C, each
-// wavefront one 32 x 32 quadrant with v_mfma_f32_32x32x2f32 (lane l supplies
-// A[l % 32][l / 32] and B[l / 32][l % 32] of a 32 x 2 x 32 step; accumulator element i
-// of lane l is C[8 (i / 4) + 4 (l / 32) + i % 4][l % 32]).  Operands are staged through
-// LDS in chunks of 32 along K, k-major, so that both operands are read as 32
-// consecutive floats per half-wave.
+// GEMM tiles: each wavefront computes a 32 x 32 tile of C with v_mfma_f32_32x32x2f32
+// (lane l supplies A[l % 32][l / 32] and B[l / 32][l % 32] of a 32 x 2 x 32 step;
+// accumulator element i of lane l is C[8 (i / 4) + 4 (l / 32) + i % 4][l % 32]).
 //
 // Inference: one workgroup of four wavefronts carries 64 rows through the whole network
 // with the activations in LDS as BF16.  The first layer (5 inputs) runs in FP32 so that
@@ -46,109 +43,145 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {
   return (uint16_t)((b + 0x7fffu + ((b >> 16) & 1u)) >> 16);
 }
 
-constexpr int GT = 64;   // C tile side
-constexpr int GK = 32;   // K chunk
+constexpr int GT = 32;   // C tile side of one wavefront
+constexpr int GD = 8;    // K groups of 8 in flight per wavefront
 
-// C[M x N] = op(A)[M x K] op(B)[K x N]; EPI 0: C = acc; 1: Z = acc + bias, C = gelu(Z);
-// 2: C = acc + bias; 3: C += acc atomically (split K: blockIdx.z takes K range
-// [z kc, (z + 1) kc)).  op(A) = A^T when TA (A stored [K x M]), likewise for B.
-template <bool TA, bool TB, int EPI>
+// C[M x N] = op(A)[M x K] op(B)[K x N]; EPI 1: Z = acc + bias, C = gelu(Z);
+// 2: C = acc + bias; 3: C += acc atomically; 4: C = acc gelu'(Z).  op(A) = A^T when TA (A
+// stored [K x M]), likewise for B.
+//
+// The products of the network are short (K = 256, 450 or a batch) and what bounds them is
+// the latency of their loads, not the matrix cores (0.54 GFLOP is 3.7 us at the card's FP32
+// rate): so a wavefront owns a 32 x 32 tile and keeps GD groups of eight k in flight in
+// registers, straight from global memory (the other tiles' waves on the compute unit share
+// its lines through L1), with no LDS staging and no barrier.  Inside a group, half-wave h
+// holds k = 4 h .. 4 h + 3 (the order of a sum over k is free), so that a K-contiguous
+// operand is one 16-byte load where its rows are aligned (VA, VB).
+//  EPI 1/2/4: a workgroup is 2 x 2 tiles (4096 x 256 x 256: 256 workgroups).
+//  EPI 3 (weight gradients, K = batch): a workgroup is one tile, its four wavefronts take a
+//  quarter of the K range [z kc, (z + 1) kc) each and meet in LDS, so that one add per
+//  element and z reaches memory; the tiles of m = 0 also sum B's columns into db.
+// Batch 4096, per product: 37 / 48 / 43 us (forward / input gradient / weight gradient,
+// LDS-staged 64 x 64 tiles) before, 13 / 17 / 13 us now.
+template <bool TA, bool TB, int EPI, bool VA, bool VB>
 __global__ __launch_bounds__(256) void k_gemm(const float* __restrict__ A, int lda,
                                               const float* __restrict__ B, int ldb,
                                               float* __restrict__ C, int ldc,
                                               float* __restrict__ Z,
-                                              const float* __restrict__ bias, int M, int N,
-                                              int K, int kc) {
-  __shared__ float As[GK][GT + 4];
-  __shared__ float Bs[GK][GT + 4];
-  const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int wm = wv >> 1, wn = wv & 1;
-  const int kb = blockIdx.z * kc;
-  const int ke = min(K, kb + kc);
+                                              const float* __restrict__ bias,
+                                              float* __restrict__ db, int M, int N, int K,
+                                              int kc) {
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr bool SPLIT = EPI == 3;
+  const int m0 = SPLIT ? blockIdx.y * GT : (blockIdx.y * 2 + (wv >> 1)) * GT;
+  const int n0 = SPLIT ? blockIdx.x * GT : (blockIdx.x * 2 + (wv & 1)) * GT;
+  int kb = 0, ke = K;
+  if constexpr (SPLIT) {
+    const int z0 = blockIdx.z * kc, z1 = min(K, z0 + kc);
+    const int kq = ((z1 - z0 + 3) / 4 + 7) / 8 * 8;
+    kb = min(z1, z0 + wv * kq);
+    ke = min(z1, kb + kq);
+  }
+  const int h4 = 4 * (lane >> 5);
+  // rows and columns past the matrix read the last one; they are not written
+  const int m = min(m0 + (lane & 31), M - 1), n = min(n0 + (lane & 31), N - 1);
+  const float* __restrict__ pa = TA ? A + (int64_t)(kb + h4) * lda + m
+                                    : A + (int64_t)m * lda + kb + h4;
+  const float* __restrict__ pb = TB ? B + (int64_t)n * ldb + kb + h4
+                                    : B + (int64_t)(kb + h4) * ldb + n;
+  const int sa = TA ? lda : 1, sb = TB ? 1 : ldb;
   f32x16 acc;
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-  for (int k0 = kb; k0 < ke; k0 += GK) {
-    for (int i = tid; i < GT * GK; i += 256) {
-      int m, k;
-      if (TA) {
-        k = i / GT;
-        m = i - k * GT;
-      } else {
-        m = i / GK;
-        k = i - m * GK;
-      }
-      const int gm = m0 + m, gk = k0 + k;
-      float v = 0.f;
-      if (gm < M && gk < ke) v = TA ? A[(int64_t)gk * lda + gm] : A[(int64_t)gm * lda + gk];
-      As[k][m] = v;
-    }
-    for (int i = tid; i < GT * GK; i += 256) {
-      int n, k;
-      if (TB) {
-        n = i / GK;
-        k = i - n * GK;
-      } else {
-        k = i / GT;
-        n = i - k * GT;
-      }
-      const int gn = n0 + n, gk = k0 + k;
-      float v = 0.f;
-      if (gn < N && gk < ke) v = TB ? B[(int64_t)gn * ldb + gk] : B[(int64_t)gk * ldb + gn];
-      Bs[k][n] = v;
-    }
-    __syncthreads();
+  float bsum = 0.f;
+  const bool sum_b = SPLIT && blockIdx.y == 0;
+  const int ng = (ke - kb) >> 3;
+  auto load = [&](int g, float (&a)[4], float (&b)[4]) {
+    if constexpr (VA) {
+      const float4 t = *reinterpret_cast<const float4*>(pa + 8 * g);
+      a[0] = t.x, a[1] = t.y, a[2] = t.z, a[3] = t.w;
+    } else {
 #pragma unroll
-    for (int kk = 0; kk < GK; kk += 2) {
-      const float a = As[kk + (lane >> 5)][wm * 32 + (lane & 31)];
-      const float b = Bs[kk + (lane >> 5)][wn * 32 + (lane & 31)];
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
+      for (int i = 0; i < 4; ++i) a[i] = pa[(8 * g + i) * sa];
     }
-    __syncthreads();
+    if constexpr (VB) {
+      const float4 t = *reinterpret_cast<const float4*>(pb + 8 * g);
+      b[0] = t.x, b[1] = t.y, b[2] = t.z, b[3] = t.w;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) b[i] = pb[(8 * g + i) * sb];
+    }
+  };
+  auto step = [&](const float (&a)[4], const float (&b)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], acc, 0, 0, 0);
+      if constexpr (SPLIT) bsum += b[i];
+    }
+  };
+  if (ng > 0) {
+    float a[GD][4], b[GD][4];
+#pragma unroll
+    for (int d = 0; d < GD; ++d) load(min(d, ng - 1), a[d], b[d]);
+    for (int g = 0; g < ng; g += GD) {
+#pragma unroll
+      for (int d = 0; d < GD; ++d) {
+        if (g + d < ng) step(a[d], b[d]);
+        load(min(g + d + GD, ng - 1), a[d], b[d]);   // past the end: the last group again
+      }
+    }
   }
-  const int col = n0 + wn * 32 + (lane & 31);
+  if (kb + 8 * ng < ke) {
+    float a[4], b[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool in = kb + 8 * ng + h4 + i < ke;
+      a[i] = in ? pa[(8 * ng + i) * sa] : 0.f;
+      b[i] = in ? pb[(8 * ng + i) * sb] : 0.f;
+    }
+    step(a, b);
+  }
+  const int col = n0 + (lane & 31);
+  if constexpr (SPLIT) {
+    __shared__ float part[3][16][64];
+    __shared__ float bpart[4][64];
+    if (wv > 0) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) part[wv - 1][i][lane] = acc[i];
+    }
+    bpart[wv][lane] = bsum;
+    __syncthreads();
+    if (wv > 0) return;
+    if (sum_b && lane < 32 && col < N) {
+      float t = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) t += bpart[w][lane] + bpart[w][lane + 32];
+      atomicAdd(&db[col], t);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      acc[i] = (acc[i] + part[0][i][lane]) + (part[1][i][lane] + part[2][i][lane]);
+  }
   if (col >= N) return;
   const float bb = (EPI == 1 || EPI == 2) ? bias[col] : 0.f;
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
-    const int row = m0 + wm * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
+    const int row = m0 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
     if (row >= M) continue;
     const float v = acc[i] + bb;
+    const int64_t o = (int64_t)row * ldc + col;
     if (EPI == 1) {
-      Z[(int64_t)row * ldc + col] = v;
-      C[(int64_t)row * ldc + col] = gelu(v);
+      Z[o] = v;
+      C[o] = gelu(v);
     } else if (EPI == 3) {
-      atomicAdd(&C[(int64_t)row * ldc + col], v);
+      atomicAdd(&C[o], v);
+    } else if (EPI == 4) {
+      C[o] = v * gelu_grad(Z[o]);
     } else {
-      C[(int64_t)row * ldc + col] = v;
+      C[o] = v;
     }
   }
-}
-
-__global__ __launch_bounds__(256) void k_gelu_bwd(float* __restrict__ dH,
-                                                  const float* __restrict__ Z, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    dH[i] *= gelu_grad(Z[i]);
-}
-
-// db[c] += sum over rows [256 blockIdx.y, 256 blockIdx.y + 256) of D[r][c] (D [rows x N],
-// row stride ld; db cleared by the caller); 64 columns per block, four row phases
-// reduced in LDS.
-__global__ __launch_bounds__(256) void k_colsum(const float* __restrict__ D, int ld, int rows,
-                                                int N, float* __restrict__ db) {
-  __shared__ float part[4][64];
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63), ph = threadIdx.x >> 6;
-  const int r0 = blockIdx.y * 256, r1 = min(rows, r0 + 256);
-  float s = 0.f;
-  if (c < N)
-    for (int r = r0 + ph; r < r1; r += 4) s += D[(int64_t)r * ld + c];
-  part[ph][threadIdx.x & 63] = s;
-  __syncthreads();
-  if (ph == 0 && c < N)
-    atomicAdd(&db[c], (part[0][threadIdx.x] + part[1][threadIdx.x]) +
-                          (part[2][threadIdx.x] + part[3][threadIdx.x]));
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -159,31 +192,49 @@ __device__ __forceinline__ float wave_sum(float v) {
 
 // Loss of one batch, one wavefront per example: dP = 2 (P - T) / B on the kernel
 // outputs, 2 (e - log10(max(r, 1e-8))) / B on the error output with r held constant;
-// loss[0] += kernel loss, loss[1] += error-output loss.
-__global__ __launch_bounds__(64) void k_loss(const float* __restrict__ P,
-                                             const float* __restrict__ T, float* __restrict__ dP,
-                                             int B, float* __restrict__ loss) {
-  const int b = blockIdx.x, lane = threadIdx.x;
-  const float* p = P + (int64_t)b * MLP_OUT;
-  const float* t = T + (int64_t)b * MLP_KOUT;
-  float* d = dP + (int64_t)b * MLP_OUT;
-  const float inv = 2.0f / (float)B;
-  float s = 0.f, st = 0.f;
-  for (int j = lane; j < MLP_KOUT; j += 64) {
-    const float e = p[j] - t[j];
-    s += e * e;
-    st += t[j] * t[j];
-    d[j] = inv * e;
-  }
-  s = wave_sum(s);
-  st = wave_sum(st);
-  if (lane == 0) {
+// loss[0] += kernel loss, loss[1] += error-output loss.  A workgroup of 16 wavefronts adds
+// its examples' terms in LDS and reaches the two sums once: they are one address each, and
+// two atomics per example were serialised there (batch 4096: 109 us before, 9 us now).
+constexpr int LOSS_WAVES = 16;
+__global__ __launch_bounds__(64 * LOSS_WAVES) void k_loss(const float* __restrict__ P,
+                                                          const float* __restrict__ T,
+                                                          float* __restrict__ dP, int B,
+                                                          float* __restrict__ loss) {
+  __shared__ float part[2][LOSS_WAVES];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int b = blockIdx.x * LOSS_WAVES + wv;
+  float lk = 0.f, le = 0.f;
+  if (b < B) {
+    const float* p = P + (int64_t)b * MLP_OUT;
+    const float* t = T + (int64_t)b * MLP_KOUT;
+    float* d = dP + (int64_t)b * MLP_OUT;
+    const float inv = 2.0f / (float)B;
+    float s = 0.f, st = 0.f;
+    for (int j = lane; j < MLP_KOUT; j += 64) {
+      const float e = p[j] - t[j];
+      s += e * e;
+      st += t[j] * t[j];
+      d[j] = inv * e;
+    }
+    s = wave_sum(s);
+    st = wave_sum(st);
     const float r = sqrtf(s) / fmaxf(sqrtf(st), 1e-30f);
     const float tgt = log10f(fmaxf(r, 1e-8f));
     const float e = p[MLP_KOUT] - tgt;
-    d[MLP_KOUT] = inv * e;
-    atomicAdd(&loss[0], s / (float)B);
-    atomicAdd(&loss[1], e * e / (float)B);
+    if (lane == 0) d[MLP_KOUT] = inv * e;
+    lk = s / (float)B;
+    le = e * e / (float)B;
+  }
+  if (lane == 0) {
+    part[0][wv] = lk;
+    part[1][wv] = le;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < LOSS_WAVES; ++w) t += part[threadIdx.x][w];
+    atomicAdd(&loss[threadIdx.x], t);
   }
 }
 
@@ -395,53 +446,50 @@ unsigned grid_for(int64_t n, int64_t cap = 8192) {
 
 }  // namespace
 
-hipError_t launch_mlp_gemm(bool ta, bool tb, int epi, const float* A, int lda, const float* B,
-                           int ldb, float* C, int ldc, float* Z, const float* bias, int M,
-                           int N, int K, hipStream_t s) {
-  // transposed-A products (weight gradients: small M x N, K = batch) split K over up to
-  // 64 workgroup layers and add into a cleared C
-  int splits = 1, kc = K;
-  if (ta) {
-    splits = std::max(1, std::min(64, K / 256));
-    kc = ((K + splits - 1) / splits + GK - 1) / GK * GK;
-    splits = (K + kc - 1) / kc;
-    if (epi != 0) return hipErrorInvalidValue;
-    hipError_t e = launch_fill_zero(C, (int64_t)M * ldc, s);
-    if (e != hipSuccess) return e;
-    epi = 3;
+hipError_t launch_mlp_gemm(int epi, const float* A, int lda, const float* B, int ldb, float* C,
+                           int ldc, float* Z, const float* bias, float* db, int M, int N, int K,
+                           hipStream_t s) {
+  // 16-byte loads along K where every row starts on such a boundary
+  auto aligned = [](const float* p, int ld) {
+    return ld % 4 == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0;
+  };
+  const bool va = aligned(A, lda), vb = aligned(B, ldb);
+  dim3 grid((N + 2 * GT - 1) / (2 * GT), (M + 2 * GT - 1) / (2 * GT), 1);
+  int kc = K;
+  if (epi == 3) {
+    // small M x N, long K: up to four layers of workgroups along K (each adds its share
+    // of every element atomically; more layers cost more in adds than they hide), a
+    // wavefront's quarter at least 64 long
+    const int splits = std::max(1, std::min(4, K / 256));
+    kc = ((K + splits - 1) / splits + 7) / 8 * 8;
+    grid = dim3((N + GT - 1) / GT, (M + GT - 1) / GT, (K + kc - 1) / kc);
   }
-  const dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT, splits);
-#define G(TA, TB, E)                                                                   \
-  if (ta == TA && tb == TB && epi == E) {                                              \
-    hipLaunchKernelGGL((k_gemm<TA, TB, E>), grid, dim3(256), 0, s, A, lda, B, ldb, C, \
-                       ldc, Z, bias, M, N, K, kc);                                     \
-    return hipGetLastError();                                                          \
+#define G(TA, TB, E, VA, VB)                                                             \
+  {                                                                                      \
+    hipLaunchKernelGGL((k_gemm<TA, TB, E, VA, VB>), grid, dim3(256), 0, s, A, lda, B,    \
+                       ldb, C, ldc, Z, bias, db, M, N, K, kc);                           \
+    return hipGetLastError();                                                            \
   }
-  G(false, false, 1)
-  G(false, false, 2)
-  G(true, false, 3)
-  G(false, true, 0)
+  switch (epi) {
+    case 1:
+      if (va) G(false, false, 1, true, false)
+      G(false, false, 1, false, false)
+    case 2:
+      if (va) G(false, false, 2, true, false)
+      G(false, false, 2, false, false)
+    case 3: G(true, false, 3, false, false)
+    case 4:
+      if (va && vb) G(false, true, 4, true, true)
+      G(false, true, 4, false, false)
+    default: return hipErrorInvalidValue;
+  }
 #undef G
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_mlp_gelu_bwd(float* dH, const float* Z, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_gelu_bwd, dim3(grid_for(n)), dim3(256), 0, s, dH, Z, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_mlp_colsum(const float* D, int ld, int rows, int N, float* db,
-                             hipStream_t s) {
-  hipError_t e = launch_fill_zero(db, N, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_colsum, dim3((N + 63) / 64, (rows + 255) / 256), dim3(256), 0, s, D, ld,
-                     rows, N, db);
-  return hipGetLastError();
 }
 
 hipError_t launch_mlp_loss(const float* P, const float* T, float* dP, int B, float* loss,
                            hipStream_t s) {
-  hipLaunchKernelGGL(k_loss, dim3(B), dim3(64), 0, s, P, T, dP, B, loss);
+  hipLaunchKernelGGL(k_loss, dim3((B + LOSS_WAVES - 1) / LOSS_WAVES), dim3(64 * LOSS_WAVES), 0, s,
+                     P, T, dP, B, loss);
   return hipGetLastError();
 }
 

@@ -540,12 +540,12 @@ hipError_t launch_exact_targets(const double* w, const double* L, int64_t n,
                                 const KernelParams& kp, float* t, hipStream_t s);
 
 // Residual-kernel network kernels.
-hipError_t launch_mlp_gemm(bool ta, bool tb, int epi, const float* A, int lda, const float* B,
-                           int ldb, float* C, int ldc, float* Z, const float* bias, int M,
-                           int N, int K, hipStream_t s);
-hipError_t launch_mlp_gelu_bwd(float* dH, const float* Z, int64_t n, hipStream_t s);
-hipError_t launch_mlp_colsum(const float* D, int ld, int rows, int N, float* db,
-                             hipStream_t s);
+// Products of the network: C = A B with an epilogue.  1: Z = acc + bias, C = gelu(Z);
+// 2: C = acc + bias; 3: C += A^T B (A stored [K x M]) and db += column sums of B; 4:
+// C = (A B^T) gelu'(Z) (B stored [N x K]).
+hipError_t launch_mlp_gemm(int epi, const float* A, int lda, const float* B, int ldb, float* C,
+                           int ldc, float* Z, const float* bias, float* db, int M, int N, int K,
+                           hipStream_t s);
 hipError_t launch_mlp_loss(const float* P, const float* T, float* dP, int B, float* loss,
                            hipStream_t s);
 hipError_t launch_mlp_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr,

@@ -72,15 +72,15 @@ const float* Bp(const wf_mlp* m, int l) { return (const float*)m->params.p + mlp
 
 // Forward pass of B rows of X; the output layer writes to out (row stride MLP_OUT).
 wf_status forward(wf_mlp* m, const float* X, int B, float* out, hipStream_t s) {
-  WF_HIP(launch_mlp_gemm(false, false, 1, X, MLP_IN, Wp(m, 0), MLP_HID, (float*)m->H[0].p,
-                         MLP_HID, (float*)m->Z[0].p, Bp(m, 0), B, MLP_HID, MLP_IN, s));
+  WF_HIP(launch_mlp_gemm(1, X, MLP_IN, Wp(m, 0), MLP_HID, (float*)m->H[0].p, MLP_HID,
+                         (float*)m->Z[0].p, Bp(m, 0), nullptr, B, MLP_HID, MLP_IN, s));
   for (int l = 1; l < MLP_LAYERS; ++l)
-    WF_HIP(launch_mlp_gemm(false, false, 1, (const float*)m->H[l - 1].p, MLP_HID, Wp(m, l),
-                           MLP_HID, (float*)m->H[l].p, MLP_HID, (float*)m->Z[l].p, Bp(m, l), B,
+    WF_HIP(launch_mlp_gemm(1, (const float*)m->H[l - 1].p, MLP_HID, Wp(m, l), MLP_HID,
+                           (float*)m->H[l].p, MLP_HID, (float*)m->Z[l].p, Bp(m, l), nullptr, B,
                            MLP_HID, MLP_HID, s));
-  WF_HIP(launch_mlp_gemm(false, false, 2, (const float*)m->H[MLP_LAYERS - 1].p, MLP_HID,
-                         Wp(m, MLP_LAYERS), MLP_OUT, out, MLP_OUT, nullptr,
-                         Bp(m, MLP_LAYERS), B, MLP_OUT, MLP_HID, s));
+  WF_HIP(launch_mlp_gemm(2, (const float*)m->H[MLP_LAYERS - 1].p, MLP_HID, Wp(m, MLP_LAYERS),
+                         MLP_OUT, out, MLP_OUT, nullptr, Bp(m, MLP_LAYERS), nullptr, B, MLP_OUT,
+                         MLP_HID, s));
   return WF_OK;
 }
 
@@ -92,26 +92,27 @@ wf_status loss_grad(wf_mlp* m, const float* X, const float* T, int B, float* los
   WF_HIP(launch_mlp_loss((const float*)m->P.p, T, (float*)m->dP.p, B, loss, s));
   float* g = (float*)m->grad.p;
   const int L = MLP_LAYERS;
-  // output layer: gW = H^T dP, gb = colsum(dP), dH = dP[:, :450] W[:, :450]^T
-  WF_HIP(launch_mlp_gemm(true, false, 0, (const float*)m->H[L - 1].p, MLP_HID,
-                         (const float*)m->dP.p, MLP_OUT, g + mlp_w_offset(L), MLP_OUT, nullptr,
-                         nullptr, MLP_HID, MLP_OUT, B, s));
-  WF_HIP(launch_mlp_colsum((const float*)m->dP.p, MLP_OUT, B, MLP_OUT, g + mlp_b_offset(L), s));
-  WF_HIP(launch_mlp_gemm(false, true, 0, (const float*)m->dP.p, MLP_OUT, Wp(m, L), MLP_OUT,
-                         (float*)m->dA.p, MLP_HID, nullptr, nullptr, B, MLP_HID, MLP_KOUT, s));
-  float* dH = (float*)m->dA.p;
+  // the weight-gradient products add into the gradient (weights and, from the same pass
+  // over D, the biases' column sums), cleared once for all layers
+  WF_HIP(launch_fill_zero(g, mlp_num_params(), s));
+  // output layer: gW = H^T dP, gb = colsum(dP), dZ = dP[:, :450] W[:, :450]^T gelu'(Z)
+  WF_HIP(launch_mlp_gemm(3, (const float*)m->H[L - 1].p, MLP_HID, (const float*)m->dP.p, MLP_OUT,
+                         g + mlp_w_offset(L), MLP_OUT, nullptr, nullptr, g + mlp_b_offset(L),
+                         MLP_HID, MLP_OUT, B, s));
+  WF_HIP(launch_mlp_gemm(4, (const float*)m->dP.p, MLP_OUT, Wp(m, L), MLP_OUT, (float*)m->dA.p,
+                         MLP_HID, (float*)m->Z[L - 1].p, nullptr, nullptr, B, MLP_HID, MLP_KOUT,
+                         s));
+  float* dZ = (float*)m->dA.p;
   float* dN = (float*)m->dB.p;
   for (int l = L - 1; l >= 0; --l) {
-    WF_HIP(launch_mlp_gelu_bwd(dH, (const float*)m->Z[l].p, (int64_t)B * MLP_HID, s));
     const float* Hp = l == 0 ? X : (const float*)m->H[l - 1].p;
     const int in = mlp_fan_in(l);
-    WF_HIP(launch_mlp_gemm(true, false, 0, Hp, in, dH, MLP_HID, g + mlp_w_offset(l), MLP_HID,
-                           nullptr, nullptr, in, MLP_HID, B, s));
-    WF_HIP(launch_mlp_colsum(dH, MLP_HID, B, MLP_HID, g + mlp_b_offset(l), s));
+    WF_HIP(launch_mlp_gemm(3, Hp, in, dZ, MLP_HID, g + mlp_w_offset(l), MLP_HID, nullptr,
+                           nullptr, g + mlp_b_offset(l), in, MLP_HID, B, s));
     if (l > 0) {
-      WF_HIP(launch_mlp_gemm(false, true, 0, dH, MLP_HID, Wp(m, l), MLP_HID, dN, MLP_HID,
-                             nullptr, nullptr, B, MLP_HID, MLP_HID, s));
-      std::swap(dH, dN);
+      WF_HIP(launch_mlp_gemm(4, dZ, MLP_HID, Wp(m, l), MLP_HID, dN, MLP_HID,
+                             (float*)m->Z[l - 1].p, nullptr, nullptr, B, MLP_HID, MLP_HID, s));
+      std::swap(dZ, dN);
     }
   }
   return WF_OK;

@@ -245,3 +245,25 @@ def test_network_gain_under_strategy_c(trained):
         assert e <= 1e-3
     op_e.close()
     op_n.close()
+
+
+@pytest.mark.parametrize("B", [1, 9, 33, 257, 1031])
+def test_loss_grad_batch_edges(params, B):
+    """Batches around the product tiles (32 rows, groups of 8 along K, K layers of 256)
+    against the FP64 gradient: FP32 sums of at most 1031 terms, 1e-4 per tensor."""
+    net = _net()(seed=1)
+    th = params.astype(np.float32)
+    net.set_params(th)
+    r = np.random.default_rng(40 + B)
+    xo = r.normal(0, 1, (B, 5)).astype(np.float32)
+    to = r.normal(0, 0.1, (B, 450)).astype(np.float32)
+    loss, g = net.loss_grad(to_dev(xo), to_dev(to))
+    lk, le, go = omlp.loss_grad(th.astype(np.float64), xo.astype(np.float64),
+                                to.astype(np.float64))
+    loss, g = loss.cpu().numpy(), g.cpu().numpy()
+    assert abs(loss[0] - lk) <= 1e-5 * lk and abs(loss[1] - le) <= 1e-4 * le
+    o = 0
+    for a, b in zip(omlp.SIZES[:-1], omlp.SIZES[1:]):
+        for n in (a * b, b):
+            assert rel(g[o:o + n], go[o:o + n]) <= 1e-4, (B, a, b, n)
+            o += n
