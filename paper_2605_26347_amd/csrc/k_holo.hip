@@ -14,7 +14,9 @@
 // global atomics, into the stencil of each output cell.
 #include <hip/hip_fp16.h>
 
+#include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "wf_internal.h"
@@ -118,10 +120,19 @@ __device__ __forceinline__ void hval4(const void* __restrict__ v, int64_t i, flo
   }
 }
 
-// Y += H X over the active tiles of one bin; one workgroup per tile, the X window
-// (tile + 2R cells per side, wrapped on the periodic grid) staged in LDS as two planes.
-// Thread t owns the four consecutive cells 4t .. 4t + 3 of the tile (one vector load of
-// stencil values per offset).  tile * tile == 4 * 256.
+// Y += H X over the active tiles of one bin.  Workgroup (tile, part) streams the stencil
+// rows [part D / parts, (part + 1) D / parts) of its tile, the X cells they reach (tile +
+// rows - 1 rows of tile + 2R cells, wrapped on the periodic grid) staged in LDS as two
+// planes.  Thread t owns the four consecutive cells 4t .. 4t + 3 of the tile (one vector load
+// of stencil values per offset); tile * tile == 4 * 256.  The stream from HBM is what bounds
+// it: HU vector loads are in flight per thread, and along a stencil row the four cells' X
+// values slide by one cell per offset, so an offset reads two floats of LDS.
+// A bin of a small field has a few hundred tiles, fewer than the chip holds workgroups: its
+// tiles are cut into parts (launch_happly) that add their sums atomically; a single part
+// adds plainly.  512^2 field, 8M rows, 2 bins of 455 tiles: 415 us per bin in one part with
+// one load in flight, 214 us (3.9 TB/s of stencil values, what a plain sum over them reads at) now.
+constexpr int HU = 4;
+
 template <int STORE>
 __global__ __launch_bounds__(256) void k_happly(const HTile* __restrict__ ht,
                                                 const void* __restrict__ hv,
@@ -130,13 +141,16 @@ __global__ __launch_bounds__(256) void k_happly(const HTile* __restrict__ ht,
                                                 int Kx, int Ky) {
   extern __shared__ float xw[];
   const HTile t = ht[blockIdx.x];
+  const int parts = gridDim.y;
+  const int dv0 = t.D * (int)blockIdx.y / parts, dv1 = t.D * ((int)blockIdx.y + 1) / parts;
+  if (dv0 == dv1) return;
   const int tile = 1 << tsh, ncell = tile * tile;
   const int tu = t.tile % tiles_x, tv = t.tile / tiles_x;
-  const int R = (t.D - 1) / 2, W = tile + 2 * R;
+  const int R = (t.D - 1) / 2, W = tile + 2 * R, H = tile + (dv1 - dv0) - 1;
   float* xr = xw;
-  float* xi = xw + W * W;
-  const int u0 = tu * tile - R, v0 = tv * tile - R;
-  for (int i = threadIdx.x; i < W * W; i += blockDim.x) {
+  float* xi = xw + W * H;
+  const int u0 = tu * tile - R, v0 = tv * tile - R + dv0;
+  for (int i = threadIdx.x; i < W * H; i += blockDim.x) {
     const int wv = i / W, wu = i - wv * W;
     const float2 x = X[strip_index((v0 + wv) & (Ky - 1), (u0 + wu) & (Kx - 1), Ky)];
     xr[i] = x.x;
@@ -146,26 +160,55 @@ __global__ __launch_bounds__(256) void k_happly(const HTile* __restrict__ ht,
   const int c0 = 4 * threadIdx.x;
   const int cv = c0 >> tsh, cu = c0 & (tile - 1);
   float ar[4] = {0.f, 0.f, 0.f, 0.f}, ai[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int dv = 0; dv < t.D; ++dv) {
-    const float* rr = xr + (cv + dv) * W + cu;
-    const float* ri = xi + (cv + dv) * W + cu;
+  for (int dv = dv0; dv < dv1; ++dv) {
+    const float* rr = xr + (cv + dv - dv0) * W + cu;
+    const float* ri = xi + (cv + dv - dv0) * W + cu;
     const int64_t rowbase = t.voff + (int64_t)dv * t.D * ncell + c0;
-    for (int du = 0; du < t.D; ++du) {
-      float2 h[4];
-      hval4<STORE>(hv, rowbase + (int64_t)du * ncell, h);
+    float wr[3 + HU], wi[3 + HU];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float x0 = rr[du + j], x1 = ri[du + j];
-        ar[j] += h[j].x * x0 - h[j].y * x1;
-        ai[j] += h[j].x * x1 + h[j].y * x0;
-      }
+    for (int j = 0; j < 3; ++j) {
+      wr[j] = rr[j];
+      wi[j] = ri[j];
     }
+    // HU offsets at a time, then the rest one by one
+    auto offsets = [&](int du, auto nn) {
+      constexpr int n = decltype(nn)::value;
+      float2 h[n][4];
+#pragma unroll
+      for (int k = 0; k < n; ++k) hval4<STORE>(hv, rowbase + (int64_t)(du + k) * ncell, h[k]);
+#pragma unroll
+      for (int k = 0; k < n; ++k) {
+        wr[3 + k] = rr[du + 3 + k];
+        wi[3 + k] = ri[du + 3 + k];
+      }
+#pragma unroll
+      for (int k = 0; k < n; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float x0 = wr[k + j], x1 = wi[k + j];
+          ar[j] += h[k][j].x * x0 - h[k][j].y * x1;
+          ai[j] += h[k][j].x * x1 + h[k][j].y * x0;
+        }
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        wr[j] = wr[n + j];
+        wi[j] = wi[n + j];
+      }
+    };
+    int du = 0;
+    for (; du + HU <= t.D; du += HU) offsets(du, std::integral_constant<int, HU>{});
+    for (; du < t.D; ++du) offsets(du, std::integral_constant<int, 1>{});
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     float2* p = Y + strip_index(tv * tile + cv, tu * tile + cu + j, Ky);
-    const float2 y = *p;
-    *p = make_float2(y.x + ar[j], y.y + ai[j]);
+    if (parts > 1) {
+      unsafeAtomicAdd(&p->x, ar[j]);
+      unsafeAtomicAdd(&p->y, ai[j]);
+    } else {
+      const float2 y = *p;
+      *p = make_float2(y.x + ar[j], y.y + ai[j]);
+    }
   }
 }
 
@@ -208,26 +251,23 @@ hipError_t launch_happly(const HTile* ht, int ntiles, int Dmax, const void* hv, 
                          const float2* X, float2* Y, int tiles_x, int tsh, int Kx, int Ky,
                          hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
+  // parts: enough workgroups for eight per compute unit (2048), none below four stencil
+  // rows on the widest tile (each part stages the tile's own X rows again)
+  const int parts = std::max(1, std::min((2048 + ntiles - 1) / ntiles, Dmax / 4));
   const int W = (1 << tsh) + (Dmax - 1);
-  const size_t lds = 2 * sizeof(float) * (size_t)W * W;
+  const int H = (1 << tsh) + (Dmax + parts - 1) / parts - 1;
+  const size_t lds = 2 * sizeof(float) * (size_t)W * H;
   hipError_t e;
+#define WF_H(ST)                                                                             \
+  if ((e = lds_limit(k_happly<ST>, lds)) != hipSuccess) return e;                            \
+  hipLaunchKernelGGL(k_happly<ST>, dim3(ntiles, parts), dim3(256), lds, s, ht, hv, X, Y,     \
+                     tiles_x, tsh, Kx, Ky);
   switch (store) {
-    case WF_STORE_F32:
-      if ((e = lds_limit(k_happly<WF_STORE_F32>, lds)) != hipSuccess) return e;
-      hipLaunchKernelGGL(k_happly<WF_STORE_F32>, dim3(ntiles), dim3(256), lds, s, ht, hv, X, Y,
-                         tiles_x, tsh, Kx, Ky);
-      break;
-    case WF_STORE_F16:
-      if ((e = lds_limit(k_happly<WF_STORE_F16>, lds)) != hipSuccess) return e;
-      hipLaunchKernelGGL(k_happly<WF_STORE_F16>, dim3(ntiles), dim3(256), lds, s, ht, hv, X, Y,
-                         tiles_x, tsh, Kx, Ky);
-      break;
-    default:
-      if ((e = lds_limit(k_happly<WF_STORE_BF16>, lds)) != hipSuccess) return e;
-      hipLaunchKernelGGL(k_happly<WF_STORE_BF16>, dim3(ntiles), dim3(256), lds, s, ht, hv, X, Y,
-                         tiles_x, tsh, Kx, Ky);
-      break;
+    case WF_STORE_F32: WF_H(WF_STORE_F32) break;
+    case WF_STORE_F16: WF_H(WF_STORE_F16) break;
+    default: WF_H(WF_STORE_BF16) break;
   }
+#undef WF_H
   return hipGetLastError();
 }
 
