@@ -5,7 +5,8 @@ load the library it builds), or __graft_entry__.build().
 Each translation unit is compiled by hipcc in parallel, then linked as one shared
 library next to this file.  FP32 packed-math instructions are disabled for all device
 code; the FP64 build kernels are compiled without floating-point contraction so that
-their integer decisions (bins, cells, kernel sides, thresholds) are reproducible.
+their integer decisions (bins, cells, kernel sides, thresholds) are reproducible.  The FFT
+passes may ignore the sign of zeros, so that the butterflies drop the terms of the padding.
 """
 from __future__ import annotations
 
@@ -24,7 +25,7 @@ BUILD = os.path.join(HERE, "_build")
 ARCH = os.environ.get("WF_OFFLOAD_ARCH", "gfx950")
 
 SOURCES = {
-    "k_fft.hip": [],
+    "k_fft.hip": ["-fno-signed-zeros"],
     "k_grid.hip": [],
     "k_build.hip": ["-ffp-contract=off"],
     "k_util.hip": [],

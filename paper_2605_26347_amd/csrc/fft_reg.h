@@ -1,5 +1,5 @@
-// Register-resident radix-16/32 FFT passes for CDNA (wave64), used by the row passes of
-// the oversampled 2-D DFT F (Sect. 3.2, eq. 6) at the long row lengths.
+// Register-resident FFT passes for CDNA (wave64) of the oversampled 2-D DFT F (Sect. 3.2,
+// eq. 6), for lines of 64 to 16384 points.
 //
 // A length-N transform runs as three Stockham passes of radices R1, R2, R3
 // (N = R1 R2 R3, each at most 32).  A thread holds E = N / NT elements and performs
@@ -10,6 +10,9 @@
 // length Ns: butterfly j in [0, N/R) reads x[j + r N/R], multiplies input r by
 // W_{Ns R}^{r (j mod Ns)}, does an R-point DFT and writes output r to
 // ((j / Ns) Ns R + j mod Ns) + r Ns.
+// The twiddles are laid out per pass, [r][j mod Ns] for the second pass and then for the
+// third, so that neighbouring lanes read neighbouring values: by the index r (j mod Ns) N /
+// (Ns R) of one table of N roots, a wavefront's load touched up to 60 lines.
 // R-point DFTs of 16 and 32 points are Cooley-Tukey products of the 2/4/8-point ones
 // with their inner twiddles as compile-time constants (cos and sin of k pi / 16 from
 // their Taylor series, evaluated in double precision by the compiler).
@@ -18,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include "fft_lds.h"
+#include "wf_internal.h"
 
 namespace wf {
 
@@ -118,109 +122,74 @@ __device__ __forceinline__ void dft_reg(float2* v) {
   else CT<8, 4, INV>::run(v);
 }
 
-// The three radices of a length-N row transform and its thread count.
+// The three radices of a length-N transform, its threads per line, and the lines that a
+// workgroup of the row passes carries (one from 512 points on; shorter lines share a
+// wavefront).
 template <int N>
 struct RowPlan {
-  static constexpr int R1 = N >= 8192 ? 32 : 16;
-  static constexpr int R2 = N >= 16384 ? 32 : 16;
+  static constexpr int R1 = fft_r1(N), R2 = fft_r2(N);
   static constexpr int R3 = N / (R1 * R2);
   static constexpr int E = R1 > R2 ? (R1 > R3 ? R1 : R3) : (R2 > R3 ? R2 : R3);
   static constexpr int NT = N / E;
+  static constexpr int LW = NT >= 64 ? 1 : 64 / NT;
+  static constexpr int WG = NT * LW;
 };
 
-// Whether element q = j + r S (j < S) of a pass lies in a needed column strip of mask m
-// (strip q / 16).  When a step of S covers at most 32 strips, all lanes' strips of one r
-// share one mask word, so that word is one uniform load per r instead of a load per
-// element.
-template <int S>
-__device__ __forceinline__ bool strip_on(const uint32_t* __restrict__ m, int j, int r) {
-  constexpr int SS = S / 16;
-  if constexpr (SS <= 32) {
-    static_assert(32 % SS == 0, "strips per step must divide a mask word");
-    const uint32_t w = m[(r * SS) >> 5];
-    return (w >> (((r * SS) & 31) + (j >> 4))) & 1u;
-  } else {
-    const int st = (j >> 4) + r * SS;
-    return (m[st >> 5] >> (st & 31)) & 1u;
-  }
+// 32-bit byte offset of a lane from a wave-uniform base: the constant part of an address
+// then rides in the scalar base and the lanes share one offset register.
+template <typename T>
+__device__ __forceinline__ T ld_off(const void* base, uint32_t off) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + off);
+}
+template <typename T>
+__device__ __forceinline__ void st_off(void* base, uint32_t off, T v) {
+  *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + off) = v;
 }
 
-// LDS slot of element idx: one float2 of padding after every 32, so that the strided
-// writes of the first pass (stride R1 elements) spread over the banks.
-__device__ __forceinline__ int lds_slot(int idx) { return idx + (idx >> 5); }
+// LDS slot of element idx: one element of padding after every 32, so that the strided
+// writes of the first pass (stride R1 elements) spread over the banks.  The padding of a sum
+// is the sum of the paddings when the low five bits do not carry, which holds for every
+// (thread, element) pair of the exchanges below: slots are one register per access pattern
+// plus a compile-time constant (an LDS instruction's immediate offset).
+__host__ __device__ constexpr int lds_slot(int idx) { return idx + (idx >> 5); }
 template <int N>
 constexpr int lds_elems() {
   return N + N / 32;
 }
 
-// One middle pass over the line in buf: inputs from LDS, outputs to LDS (all inputs are
-// read before the barrier, outputs written after it).  The butterflies of a thread are
-// j = tid + b NT; several lines may share the block, each with its own NT threads.
-template <int N, int R, int NS, int NT, bool INV>
-__device__ __forceinline__ void reg_pass_lds(float2* buf, const float2* __restrict__ tw,
-                                             int tid) {
-  constexpr int B = (N / R) / NT;
-  float2 v[B][R];
-#pragma unroll
-  for (int b = 0; b < B; ++b) {
-    const int j = tid + b * NT;
-#pragma unroll
-    for (int r = 0; r < R; ++r) v[b][r] = buf[lds_slot(j + r * (N / R))];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int b = 0; b < B; ++b) {
-    const int j = tid + b * NT;
-    const int kk = j & (NS - 1);
-    const int step = kk * (N / (NS * R));
-#pragma unroll
-    for (int r = 1; r < R; ++r) {
-      const float2 t = tw[r * step];
-      v[b][r] = INV ? cmulc(v[b][r], t) : cmul(v[b][r], t);
-    }
-    dft_reg<R, INV>(v[b]);
-    const int d = (j - kk) * R + kk;
-#pragma unroll
-    for (int r = 0; r < R; ++r) buf[lds_slot(d + r * NS)] = v[b][r];
-  }
-  __syncthreads();
-}
-
 // Cross-lane exchange through LDS in two halves, the real parts and then the imaginary
 // parts, so that a line occupies N floats of LDS instead of N complex values.  out[k]
-// goes to slot oslot(k) and in[k] comes from slot islot(k); the block's threads pass the
-// four barriers together (the last one lets the next exchange reuse the buffer).
-// The slots are functions of (k, tid); they are computed afresh for the second half
-// (the empty asm hides that tid is unchanged) instead of being held in registers across
-// it.
+// goes to slot ob + oslot(k) and in[k] comes from slot ib + islot(k), oslot and islot being
+// compile-time constants of k; the block's threads pass the four barriers together (the last
+// one lets the next exchange reuse the buffer).
 template <int KO, int KI, typename OS, typename IS>
-__device__ __forceinline__ void xchg_split(float* buf, int tid, const float2 (&out)[KO],
+__device__ __forceinline__ void xchg_split(float* buf, int ob, int ib, const float2 (&out)[KO],
                                            OS&& oslot, float2 (&in)[KI], IS&& islot) {
-  int t = tid;
+  float* wo = buf + ob;
+  const float* ri = buf + ib;
 #pragma unroll
-  for (int k = 0; k < KO; ++k) buf[oslot(k, t)] = out[k].x;
+  for (int k = 0; k < KO; ++k) wo[oslot(k)] = out[k].x;
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < KI; ++k) in[k].x = buf[islot(k, t)];
-  __syncthreads();
-  asm volatile("" : "+v"(t));
-#pragma unroll
-  for (int k = 0; k < KO; ++k) buf[oslot(k, t)] = out[k].y;
+  for (int k = 0; k < KI; ++k) in[k].x = ri[islot(k)];
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < KI; ++k) in[k].y = buf[islot(k, t)];
+  for (int k = 0; k < KO; ++k) wo[oslot(k)] = out[k].y;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < KI; ++k) in[k].y = ri[islot(k)];
   __syncthreads();
 }
 
 // The same exchange with complex values in one go (N complex values of LDS per line).
 template <int KO, int KI, typename OS, typename IS>
-__device__ __forceinline__ void xchg_full(float2* buf, int tid, const float2 (&out)[KO],
+__device__ __forceinline__ void xchg_full(float2* buf, int ob, int ib, const float2 (&out)[KO],
                                           OS&& oslot, float2 (&in)[KI], IS&& islot) {
 #pragma unroll
-  for (int k = 0; k < KO; ++k) buf[oslot(k, tid)] = out[k];
+  for (int k = 0; k < KO; ++k) buf[ob + oslot(k)] = out[k];
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < KI; ++k) in[k] = buf[islot(k, tid)];
+  for (int k = 0; k < KI; ++k) in[k] = buf[ib + islot(k)];
   __syncthreads();
 }
 
@@ -237,63 +206,66 @@ constexpr size_t line_lds_bytes() {
   return (size_t)lds_elems<N>() * (line_split<N>() ? sizeof(float) : sizeof(float2));
 }
 
-// The middle of a row transform, the line crossing LDS twice (xchg_split or xchg_full as
+// The middle of a transform, the line crossing LDS twice (xchg_split or xchg_full as
 // line_split says; buf is the line, in floats or complex values accordingly).  v1 holds
-// the first pass's outputs of the thread's butterflies j = tid + b NT (output r of
+// the first pass's outputs of the thread's butterflies j = t + b NT (output r of
 // butterfly j belongs at position j R1 + r); the second pass (radix R2, sub-transform
 // length R1, twiddles from tw) runs in registers between the two exchanges; v3 receives
 // the third pass's inputs x[j + r R1 R2].
 template <int N, bool INV>
 __device__ __forceinline__ void row_middle(void* buf, const float2 (&v1)[N / RowPlan<N>::NT],
                                            float2 (&v3)[N / RowPlan<N>::NT],
-                                           const float2* __restrict__ tw, int tid) {
+                                           const float2* __restrict__ tw, int t) {
   using RP = RowPlan<N>;
   constexpr int R1 = RP::R1, R2 = RP::R2, R3 = RP::R3, NT = RP::NT, E = N / NT;
   constexpr int B2 = (N / R2) / NT;
   static_assert(((N / R1) / NT) * R1 == E && B2 * R2 == E && ((N / R3) / NT) * R3 == E,
                 "every pass holds E elements per thread");
+  // no carry out of the low five bits: see lds_slot
+  static_assert((NT * R1) % 32 == 0 && NT % R1 == 0 && 32 % R1 == 0, "write slots");
+  static_assert(NT % 32 == 0 || (NT == 16 && (N / R2) % 16 == 0 && B2 <= 2), "read slots");
   float2 v2[E];
-  auto xchg = [&](const float2(&o)[E], auto&& os, float2(&in)[E], auto&& is) {
+  const int kk = t & (R1 - 1);
+  const int w1 = lds_slot(t * R1);             // writes of the first exchange: t R1 + ...
+  const int w2 = lds_slot((t - kk) * R2) + kk;  // of the second: (t / R1) R1 R2 + kk + ...
+  const int rd = lds_slot(t);                   // reads of both: t + ...
+  auto xchg = [&](int ob, const float2(&o)[E], auto&& os, float2(&in)[E], auto&& is) {
     if constexpr (line_split<N>())
-      xchg_split(reinterpret_cast<float*>(buf), tid, o, os, in, is);
+      xchg_split(reinterpret_cast<float*>(buf), ob, rd, o, os, in, is);
     else
-      xchg_full(reinterpret_cast<float2*>(buf), tid, o, os, in, is);
+      xchg_full(reinterpret_cast<float2*>(buf), ob, rd, o, os, in, is);
   };
   xchg(
-      v1,
-      [](int k, int t) {
-        const int b = k / R1, r = k - b * R1;
-        return lds_slot((t + b * NT) * R1 + r);
-      },
-      v2,
-      [](int k, int t) {
-        const int b = k / R2, r = k - b * R2;
-        return lds_slot(t + b * NT + r * (N / R2));
-      });
+      w1, v1, [](int k) { return lds_slot((k / R1) * NT * R1) + k % R1; }, v2,
+      [](int k) { return lds_slot((k / R2) * NT + (k % R2) * (N / R2)); });
 #pragma unroll
-  for (int b = 0; b < B2; ++b) {
-    const int j = tid + b * NT;
-    const int kk = j & (R1 - 1);
-    const int step = kk * (N / (R1 * R2));
+  for (int r = 1; r < R2; ++r) {
+    // exp(-2 pi i r kk R3 / N): the same for all of the thread's butterflies (NT is a
+    // multiple of R1)
+    const float2 f = ld_off<float2>(tw + r * R1, (uint32_t)kk * 8);
 #pragma unroll
-    for (int r = 1; r < R2; ++r) {
-      const float2 t = tw[r * step];
-      v2[b * R2 + r] = INV ? cmulc(v2[b * R2 + r], t) : cmul(v2[b * R2 + r], t);
-    }
-    dft_reg<R2, INV>(v2 + b * R2);
+    for (int b = 0; b < B2; ++b)
+      v2[b * R2 + r] = INV ? cmulc(v2[b * R2 + r], f) : cmul(v2[b * R2 + r], f);
   }
+#pragma unroll
+  for (int b = 0; b < B2; ++b) dft_reg<R2, INV>(v2 + b * R2);
   xchg(
-      v2,
-      [](int k, int t) {
-        const int b = k / R2, r = k - b * R2;
-        const int j = t + b * NT, kk = j & (R1 - 1);
-        return lds_slot((j - kk) * R2 + kk + r * R1);
-      },
-      v3,
-      [](int k, int t) {
-        const int b = k / R3, r = k - b * R3;
-        return lds_slot(t + b * NT + r * (R1 * R2));
-      });
+      w2, v2,
+      [](int k) { return lds_slot((k / R2) * NT * R2) + lds_slot((k % R2) * R1); }, v3,
+      [](int k) { return lds_slot((k / R3) * NT + (k % R3) * (R1 * R2)); });
+}
+
+// The last pass: butterflies j = t + b NT of radix R3 with twiddles exp(-2 pi i r j / N).
+template <int N, bool INV>
+__device__ __forceinline__ void last_twiddle(float2* v, const float2* __restrict__ tw, int b,
+                                             int t) {
+  constexpr int R1 = RowPlan<N>::R1, R2 = RowPlan<N>::R2, R3 = RowPlan<N>::R3;
+  constexpr int NT = RowPlan<N>::NT;
+#pragma unroll
+  for (int r = 1; r < R3; ++r) {
+    const float2 f = ld_off<float2>(tw + R1 * R2 + r * (R1 * R2) + b * NT, (uint32_t)t * 8);
+    v[r] = INV ? cmulc(v[r], f) : cmul(v[r], f);
+  }
 }
 
 }  // namespace wf

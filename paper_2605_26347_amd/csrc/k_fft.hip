@@ -132,7 +132,7 @@ __device__ __forceinline__ bool bit_set(const uint32_t* __restrict__ m, int i) {
 }
 
 // Geometry of the pruning masks: tile bitmap [Ky/tile][Kx/tile] and strip bitmap
-// [Kx/16], both as packed 32-bit words.
+// [Kx/MSTRIP], both as packed 32-bit words.
 struct Masks {
   const uint32_t* strip;  // null: all strips needed
   const uint32_t* tile;   // null: all tiles needed
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(NT) void k_fwd_rows(const float* __restrict__ img,
   __syncthreads();
   fft_lines<N, NT, 1, false>(buf, N, tw);
   for (int q = threadIdx.x; q < N; q += NT)
-    if (!smask || bit_set(smask, q >> 4)) A[strip_index(j, q, ny)] = buf[q];
+    if (!smask || bit_set(smask, q >> 4)) A[half_index(j, q, ny)] = buf[q];
 }
 
 template <int N, int NT>
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(NT) void k_inv_rows(const float2* __restrict__ A,
   extern __shared__ float2 buf[];
   const int j = blockIdx.x;
   for (int q = threadIdx.x; q < N; q += NT)
-    buf[q] = (!smask || bit_set(smask, q >> 4)) ? A[strip_index(j, q, ny)]
+    buf[q] = (!smask || bit_set(smask, q >> 4)) ? A[half_index(j, q, ny)]
                                                 : make_float2(0.f, 0.f);
   __syncthreads();
   fft_lines<N, NT, 1, true>(buf, N, tw);
@@ -215,62 +215,111 @@ __global__ __launch_bounds__(NT) void k_inv_rows(const float2* __restrict__ A,
   }
 }
 
-// Row passes at the long lengths (N = 2048 .. 16384): three register-resident passes
-// (fft_reg.h).  Since N = 2 nx, input r of a first-pass butterfly holds an image pixel
-// exactly when r < R1/4 (pixel q + nx/2) or r >= 3 R1/4 (pixel q - 3 nx/2), and output r
-// of a last-pass butterfly lands inside the crop under the same rule with R3: the zero
-// half of the padded row and the discarded half of the inverse are skipped at compile
-// time.
+// Row passes of lines of 64 points and more: three register-resident passes (fft_reg.h).
+// They are bound by instruction issue and L1 accesses rather than by HBM (205 and 272 MB per
+// pass at 8192 points, half of the columns needed: 45 and 60 us at the copy rate), so that
+// what counts is instructions and lines per element: constant parts of addresses in scalar
+// registers and immediate offsets, twiddles in reading order, padding terms dropped by the
+// compiler, masks settled by scalar branches.  Forward / inverse pass at 8192 points 109 / 121
+// us before, 90 / 96 us now; 16384 points forward 524 / 362; 4096 points 38 / 37 -> 29 / 27;
+// 1024 points (LDS-resident stages before) 10.5 / 13.5 -> 7.5 / 7.1.
+// Since N = 2 nx, input r of a first-pass butterfly holds an image pixel exactly when r <
+// R1/4 (pixel q + nx/2) or r >= 3 R1/4 (pixel q - 3 nx/2), and output r of a last-pass
+// butterfly lands inside the crop under the same rule with R3: the zero half of the padded
+// row and the discarded half of the inverse are skipped at compile time.
 // With a sweep's layer table sl, workgroup (row, layer) takes the layer's grid, mask and
 // centroid from sl[blockIdx.y] and its channel's image from img (all channels' images).
+//
+// Pixel (or grid column) of element (b, r) relative to the thread: a compile-time constant.
+template <int N, int R>
+__device__ __forceinline__ constexpr int kept_pixel(int b, int r) {
+  return b * RowPlan<N>::NT + r * (N / R) + (r < R / 4 ? N / 4 : -3 * (N / 4));
+}
+template <int R>
+__device__ __forceinline__ constexpr bool kept(int r) {
+  return r < R / 4 || r >= 3 * R / 4;
+}
+
+// Calls on(k) for each of the thread's elements k whose column t + col(k) lies in a needed
+// strip.  A wavefront's 64 columns are four whole mask strips (lines of 512 points and more:
+// col(k) is a multiple of 64), one nibble of one mask word, which a scalar load and a scalar
+// branch settle for all lanes unless the support's edge lies inside.
+template <int N, int K, typename COL, typename ON>
+__device__ __forceinline__ void needed_columns(const uint32_t* __restrict__ smask, int t,
+                                               COL&& col, ON&& on) {
+  if (!smask) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) on(k);
+  } else if constexpr (RowPlan<N>::NT % 64 == 0) {
+    const int s0 = __builtin_amdgcn_readfirstlane(t >> 4);
+    const int sl = (t >> 4) & 3;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int s = s0 + col(k) / MSTRIP;
+      const uint32_t f = (smask[s >> 5] >> (s & 31)) & 15u;
+      if (f == 15u) {
+        on(k);
+      } else if (f != 0u) {
+        if ((f >> sl) & 1u) on(k);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int s = (t + col(k)) / MSTRIP;
+      if ((smask[s >> 5] >> (s & 31)) & 1u) on(k);
+    }
+  }
+}
+
 template <int N>
-__global__ __launch_bounds__(RowPlan<N>::NT) __attribute__((amdgpu_waves_per_eu(4))) void k_fwd_rows_reg(
+__global__ __launch_bounds__(RowPlan<N>::WG) __attribute__((amdgpu_waves_per_eu(4))) void k_fwd_rows_reg(
     const float* __restrict__ img, float2* __restrict__ A, const float2* __restrict__ tw,
-    const float* __restrict__ sx, const float* __restrict__ sy, int nx, int ny, double cell,
-    double wp, const uint32_t* __restrict__ smask, const SweepLayer* __restrict__ sl,
+    const float* __restrict__ sx, const float* __restrict__ sy, int ny, double cell, double wp,
+    const uint32_t* __restrict__ smask, const SweepLayer* __restrict__ sl,
     const float2* __restrict__ ctab) {
   using RP = RowPlan<N>;
-  constexpr int R1 = RP::R1, R2 = RP::R2, R3 = RP::R3, NT = RP::NT;
+  constexpr int R1 = RP::R1, R2 = RP::R2, R3 = RP::R3, NT = RP::NT, LW = RP::LW;
+  constexpr int NX = N / 2, E = N / NT;
   extern __shared__ float2 buf[];
-  const int jr = blockIdx.x;
+  const int l = LW == 1 ? 0 : threadIdx.x / NT, t = LW == 1 ? threadIdx.x : threadIdx.x % NT;
+  const int j0 = blockIdx.x * LW, jr = j0 + l;
   if (sl) {
     const SweepLayer& L = sl[blockIdx.y];
-    img += (int64_t)L.chan * nx * ny;
+    img += (int64_t)L.chan * NX * ny;
     A = L.A;
     wp = L.wp;
     smask = L.smask;
     ctab = L.ctab;
   }
   const float syj = sy[jr];
-  const float* __restrict__ row = img + (int64_t)jr * nx;
-  float2 v1[N / NT];
+  const float* __restrict__ row = img + (int64_t)j0 * NX;
+  const uint32_t toff = (uint32_t)(l * NX + t) * 4;
+  float2 v1[E];
   {
-    constexpr int B = (N / R1) / NT;
     // the modulation of the lane's pixels, one uniform branch for the whole row (a
     // branch per pixel would keep the loads of different pixels from overlapping)
-    auto pix = [&](int b, int r) {
-      const int q = threadIdx.x + b * NT + r * (N / R1);
-      return r < R1 / 4 ? q + nx / 2 : q - 3 * (nx / 2);
-    };
+    constexpr int B = E / R1;
     float2 zr[B][R1 / 2];
     if (ctab) {
-      const ChirpRow cr = chirp_row(jr, nx, ny, cell, wp, syj);
+      const ChirpRow cr = chirp_row(jr, NX, ny, cell, wp, syj);
 #pragma unroll
       for (int b = 0; b < B; ++b)
 #pragma unroll
         for (int r = 0; r < R1; ++r)
-          if (r < R1 / 4 || r >= 3 * R1 / 4) {
-            const int i = pix(b, r);
-            zr[b][r < R1 / 4 ? r : r - R1 / 2] = zvalue_tab(cr, i, ctab[i]);
+          if (kept<R1>(r)) {
+            const int c = kept_pixel<N, R1>(b, r);
+            zr[b][r < R1 / 4 ? r : r - R1 / 2] =
+                zvalue_tab(cr, t + c, ld_off<float2>(ctab + c, (uint32_t)t * 8));
           }
     } else {
 #pragma unroll
       for (int b = 0; b < B; ++b)
 #pragma unroll
         for (int r = 0; r < R1; ++r)
-          if (r < R1 / 4 || r >= 3 * R1 / 4) {
-            const int i = pix(b, r);
-            zr[b][r < R1 / 4 ? r : r - R1 / 2] = zvalue(i, jr, nx, ny, cell, wp, sx[i], syj);
+          if (kept<R1>(r)) {
+            const int i = t + kept_pixel<N, R1>(b, r);
+            zr[b][r < R1 / 4 ? r : r - R1 / 2] = zvalue(i, jr, NX, ny, cell, wp, sx[i], syj);
           }
     }
 #pragma unroll
@@ -278,8 +327,8 @@ __global__ __launch_bounds__(RowPlan<N>::NT) __attribute__((amdgpu_waves_per_eu(
       float2* v = v1 + b * R1;
 #pragma unroll
       for (int r = 0; r < R1; ++r) {
-        if (r < R1 / 4 || r >= 3 * R1 / 4) {
-          const float x = row[pix(b, r)];
+        if (kept<R1>(r)) {
+          const float x = ld_off<float>(row + kept_pixel<N, R1>(b, r), toff);
           const float2 z = zr[b][r < R1 / 4 ? r : r - R1 / 2];
           v[r] = make_float2(x * z.x, x * z.y);
         } else {
@@ -289,128 +338,113 @@ __global__ __launch_bounds__(RowPlan<N>::NT) __attribute__((amdgpu_waves_per_eu(
       dft_reg<R1, false>(v);
     }
   }
-  float2 v3[N / NT];
-  row_middle<N, false>(buf, v1, v3, tw, threadIdx.x);
+  float2 v3[E];
+  void* line = line_split<N>() ? (void*)(reinterpret_cast<float*>(buf) + l * lds_elems<N>())
+                               : (void*)(buf + l * lds_elems<N>());
+  row_middle<N, false>(line, v1, v3, tw, t);
   {
-    // the thread index taken afresh (the empty asm hides that it is unchanged) rather
-    // than held through the exchanges; a wave-uniform row base and 32-bit strip offsets
-    // (a grid holds at most 2^27 elements)
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    float2* __restrict__ arow = A + (int64_t)jr * SW;
     constexpr int NS = R1 * R2;
-    constexpr int B = (N / R3) / NT;
+    const uint32_t off = (uint32_t)half_index(l, t, ny) * 8;
+    float2* __restrict__ arow = A + ((int64_t)j0 << HALF_L);
+    auto col = [](int k) { return (k / R3) * NT + (k % R3) * NS; };
 #pragma unroll
-    for (int b = 0; b < B; ++b) {
-      const int j = tid + b * NT;
-      float2* v = v3 + b * R3;
-#pragma unroll
-      for (int r = 1; r < R3; ++r) v[r] = cmul(v[r], tw[r * j]);
-      dft_reg<R3, false>(v);
-#pragma unroll
-      for (int r = 0; r < R3; ++r) {
-        const int q = j + r * NS;
-        if (!smask || strip_on<NS>(smask, j, r)) arow[(q >> 4) * ny * SW + (q & (SW - 1))] = v[r];
-      }
+    for (int b = 0; b < E / R3; ++b) {
+      last_twiddle<N, false>(v3 + b * R3, tw, b, t);
+      dft_reg<R3, false>(v3 + b * R3);
     }
+    needed_columns<N, E>(smask, t, col, [&](int k) {
+      st_off(arow + (((int64_t)(col(k) >> HALF_L) * ny) << HALF_L), off, v3[k]);
+    });
   }
 }
 
+// First pass of the inverse row transform: the needed columns of row j0 + l of A.
 template <int N>
-__global__ __launch_bounds__(RowPlan<N>::NT) __attribute__((amdgpu_waves_per_eu(3))) void k_inv_rows_reg(
+__device__ __forceinline__ void inv_rows_first(const float2* __restrict__ A,
+                                               const uint32_t* __restrict__ smask, int ny,
+                                               int j0, int l, int t,
+                                               float2 (&v1)[N / RowPlan<N>::NT]) {
+  constexpr int R1 = RowPlan<N>::R1, NT = RowPlan<N>::NT, E = N / NT;
+  const uint32_t off = (uint32_t)half_index(l, t, ny) * 8;
+  const float2* __restrict__ arow = A + ((int64_t)j0 << HALF_L);
+  auto col = [](int k) { return (k / R1) * NT + (k % R1) * (N / R1); };
+#pragma unroll
+  for (int k = 0; k < E; ++k) v1[k] = make_float2(0.f, 0.f);
+  needed_columns<N, E>(smask, t, col, [&](int k) {
+    v1[k] = ld_off<float2>(arow + (((int64_t)(col(k) >> HALF_L) * ny) << HALF_L), off);
+  });
+#pragma unroll
+  for (int b = 0; b < E / R1; ++b) dft_reg<R1, true>(v1 + b * R1);
+}
+
+template <int N>
+__global__ __launch_bounds__(RowPlan<N>::WG) __attribute__((amdgpu_waves_per_eu(N >= 8192 ? 3 : 4))) void k_inv_rows_reg(
     const float2* __restrict__ A, void* __restrict__ out, const float2* __restrict__ tw,
-    const float* __restrict__ sx, const float* __restrict__ sy, int nx, int ny, double cell,
-    double wp, int mode, const uint32_t* __restrict__ smask, const float2* __restrict__ ctab) {
+    const float* __restrict__ sx, const float* __restrict__ sy, int ny, double cell, double wp,
+    int mode, const uint32_t* __restrict__ smask, const float2* __restrict__ ctab) {
   using RP = RowPlan<N>;
-  constexpr int R1 = RP::R1, R2 = RP::R2, R3 = RP::R3, NT = RP::NT;
+  constexpr int R3 = RP::R3, NT = RP::NT, LW = RP::LW, NX = N / 2, E = N / NT;
   extern __shared__ float2 buf[];
-  const int jr = blockIdx.x;
-  constexpr int NS3 = R1 * R2;
-  constexpr int B3 = (N / R3) / NT;
-  float2 v1[N / NT];
-  {
-    constexpr int B = (N / R1) / NT;
-#pragma unroll
-    for (int b = 0; b < B; ++b) {
-      const int j = threadIdx.x + b * NT;
-      float2* v = v1 + b * R1;
-#pragma unroll
-      for (int r = 0; r < R1; ++r) {
-        const int q = j + r * (N / R1);
-        v[r] = (!smask || strip_on<N / R1>(smask, j, r)) ? A[strip_index(jr, q, ny)]
-                                                         : make_float2(0.f, 0.f);
-      }
-      dft_reg<R1, true>(v);
-    }
-  }
-  float2 v3[N / NT];
-  row_middle<N, true>(buf, v1, v3, tw, threadIdx.x);
+  const int l = LW == 1 ? 0 : threadIdx.x / NT, t = LW == 1 ? threadIdx.x : threadIdx.x % NT;
+  const int j0 = blockIdx.x * LW, jr = j0 + l;
+  float2 v1[E], v3[E];
+  inv_rows_first<N>(A, smask, ny, j0, l, t, v1);
+  void* line = line_split<N>() ? (void*)(reinterpret_cast<float*>(buf) + l * lds_elems<N>())
+                               : (void*)(buf + l * lds_elems<N>());
+  row_middle<N, true>(line, v1, v3, tw, t);
   const float syj = sy[jr];
-  {
-    constexpr int NS = R1 * R2;
-    constexpr int B = (N / R3) / NT;
-    // the modulation of the lane's output pixels, one uniform branch for the row
-    auto pix = [&](int b, int r) {
-      const int q = threadIdx.x + b * NT + r * NS;
-      return r < R3 / 4 ? q + nx / 2 : q - 3 * (nx / 2);
-    };
-    const ChirpRow cr = chirp_row(jr, nx, ny, cell, wp, syj);
+  const ChirpRow cr = chirp_row(jr, NX, ny, cell, wp, syj);
+  const uint32_t pix = (uint32_t)(l * NX + t);   // the lane's pixel 0 from row j0 on
 #pragma unroll
-    for (int b = 0; b < B; ++b) {
-      // one group's modulations at a time (registers), one uniform branch per group
-      float2 zr[R3 / 2];
-      if (ctab) {
+  for (int b = 0; b < E / R3; ++b) {
+    // one group's modulations at a time (registers), one uniform branch per group
+    float2 zr[R3 / 2];
+    if (ctab) {
 #pragma unroll
-        for (int r = 0; r < R3; ++r)
-          if (r < R3 / 4 || r >= 3 * R3 / 4) {
-            const int i = pix(b, r);
-            zr[r < R3 / 4 ? r : r - R3 / 2] = zvalue_tab(cr, i, ctab[i]);
-          }
-      } else {
+      for (int r = 0; r < R3; ++r)
+        if (kept<R3>(r)) {
+          const int c = kept_pixel<N, R3>(b, r);
+          zr[r < R3 / 4 ? r : r - R3 / 2] =
+              zvalue_tab(cr, t + c, ld_off<float2>(ctab + c, (uint32_t)t * 8));
+        }
+    } else {
 #pragma unroll
-        for (int r = 0; r < R3; ++r)
-          if (r < R3 / 4 || r >= 3 * R3 / 4) {
-            const int i = pix(b, r);
-            zr[r < R3 / 4 ? r : r - R3 / 2] = zvalue(i, jr, nx, ny, cell, wp, sx[i], syj);
-          }
-      }
-      const int j = threadIdx.x + b * NT;
-      // the previous image sum of the real-part accumulate mode, requested before this
-      // group's transform so that its latency hides behind it (per group: registers)
-      float prev[R3 / 2];
-      if (mode == 3) {
+      for (int r = 0; r < R3; ++r)
+        if (kept<R3>(r)) {
+          const int i = t + kept_pixel<N, R3>(b, r);
+          zr[r < R3 / 4 ? r : r - R3 / 2] = zvalue(i, jr, NX, ny, cell, wp, sx[i], syj);
+        }
+    }
+    // the previous image sum of the real-part accumulate mode, requested before this
+    // group's transform so that its latency hides behind it (per group: registers)
+    float prev[R3 / 2];
+    if (mode == 3) {
+      const float* row = reinterpret_cast<const float*>(out) + (int64_t)j0 * NX;
 #pragma unroll
-        for (int r = 0; r < R3; ++r)
-          if (r < R3 / 4 || r >= 3 * R3 / 4) {
-            const int q = j + r * NS3;
-            const int i = r < R3 / 4 ? q + nx / 2 : q - 3 * (nx / 2);
-            prev[r < R3 / 4 ? r : r - R3 / 2] =
-                reinterpret_cast<const float*>(out)[(int64_t)jr * nx + i];
-          }
-      }
-      float2* v = v3 + b * R3;
+      for (int r = 0; r < R3; ++r)
+        if (kept<R3>(r))
+          prev[r < R3 / 4 ? r : r - R3 / 2] =
+              ld_off<float>(row + kept_pixel<N, R3>(b, r), pix * 4);
+    }
+    float2* v = v3 + b * R3;
+    last_twiddle<N, true>(v, tw, b, t);
+    dft_reg<R3, true>(v);
 #pragma unroll
-      for (int r = 1; r < R3; ++r) v[r] = cmulc(v[r], tw[r * j]);
-      dft_reg<R3, true>(v);
-#pragma unroll
-      for (int r = 0; r < R3; ++r) {
-        if (r < R3 / 4 || r >= 3 * R3 / 4) {
-          const int q = j + r * NS;
-          const int i = r < R3 / 4 ? q + nx / 2 : q - 3 * (nx / 2);
-          const float2 c = cmulc(v[r], zr[r < R3 / 4 ? r : r - R3 / 2]);
-          const int64_t o = (int64_t)jr * nx + i;
-          if (mode < 2) {
-            float2* po = reinterpret_cast<float2*>(out) + o;
-            if (mode == 1) {
-              const float2 p = *po;
-              *po = make_float2(p.x + c.x, p.y + c.y);
-            } else {
-              *po = c;
-            }
+    for (int r = 0; r < R3; ++r) {
+      if (kept<R3>(r)) {
+        const float2 c = cmulc(v[r], zr[r < R3 / 4 ? r : r - R3 / 2]);
+        const int64_t o = (int64_t)j0 * NX + kept_pixel<N, R3>(b, r);
+        if (mode < 2) {
+          float2* row = reinterpret_cast<float2*>(out) + o;
+          if (mode == 1) {
+            const float2 p = ld_off<float2>(row, pix * 8);
+            st_off(row, pix * 8, make_float2(p.x + c.x, p.y + c.y));
           } else {
-            float* po = reinterpret_cast<float*>(out) + o;
-            *po = (mode == 3) ? (prev[r < R3 / 4 ? r : r - R3 / 2] + c.x) : c.x;
+            st_off(row, pix * 8, c);
           }
+        } else {
+          float* row = reinterpret_cast<float*>(out) + o;
+          st_off(row, pix * 4, mode == 3 ? prev[r < R3 / 4 ? r : r - R3 / 2] + c.x : c.x);
         }
       }
     }
@@ -426,13 +460,14 @@ template <int N>
 __global__ __launch_bounds__(RowPlan<N>::NT) void k_inv_rows_sweep(
     const SweepLayer* __restrict__ sl, const int2* __restrict__ chan_layers, int c0,
     void* __restrict__ out, const float2* __restrict__ tw, const float* __restrict__ sx,
-    const float* __restrict__ sy, int nx, int ny, double cell, int real_out,
+    const float* __restrict__ sy, int ny, double cell, int real_out,
     unsigned long long* __restrict__ stamps, int* __restrict__ done) {
   using RP = RowPlan<N>;
-  constexpr int R1 = RP::R1, R2 = RP::R2, R3 = RP::R3, NT = RP::NT;
-  constexpr int NS3 = R1 * R2;
-  constexpr int B3 = (N / R3) / NT;
+  constexpr int R3 = RP::R3, NT = RP::NT, NX = N / 2, E = N / NT;
+  static_assert(RP::LW == 1, "one row per workgroup");
+  constexpr int B3 = E / R3;
   extern __shared__ float2 buf[];
+  const int t = threadIdx.x;
   const int jr = blockIdx.x, c = c0 + (int)blockIdx.y;
   const int2 cl = chan_layers[c];
   const float syj = sy[jr];
@@ -443,55 +478,33 @@ __global__ __launch_bounds__(RowPlan<N>::NT) void k_inv_rows_sweep(
     for (int r = 0; r < R3 / 2; ++r) acc[b][r] = make_float2(0.f, 0.f);
   for (int li = cl.x; li < cl.x + cl.y; ++li) {
     const SweepLayer& L = sl[li];
-    const float2* __restrict__ A = L.A;
-    const uint32_t* __restrict__ smask = L.smask;
-    float2 v1[N / NT];
-    {
-      constexpr int B = (N / R1) / NT;
-#pragma unroll
-      for (int b = 0; b < B; ++b) {
-        const int j = threadIdx.x + b * NT;
-        float2* v = v1 + b * R1;
-#pragma unroll
-        for (int r = 0; r < R1; ++r) {
-          const int q = j + r * (N / R1);
-          v[r] = (!smask || strip_on<N / R1>(smask, j, r)) ? A[strip_index(jr, q, ny)]
-                                                           : make_float2(0.f, 0.f);
-        }
-        dft_reg<R1, true>(v);
-      }
-    }
-    float2 v3[N / NT];
-    row_middle<N, true>(buf, v1, v3, tw, threadIdx.x);
+    float2 v1[E], v3[E];
+    inv_rows_first<N>(L.A, L.smask, ny, jr, 0, t, v1);
+    row_middle<N, true>(buf, v1, v3, tw, t);
 #pragma unroll
     for (int b = 0; b < B3; ++b) {
-      const int j = threadIdx.x + b * NT;
       float2* v = v3 + b * R3;
-#pragma unroll
-      for (int r = 1; r < R3; ++r) v[r] = cmulc(v[r], tw[r * j]);
+      last_twiddle<N, true>(v, tw, b, t);
       dft_reg<R3, true>(v);
 #pragma unroll
       for (int r = 0; r < R3; ++r) {
-        if (r < R3 / 4 || r >= 3 * R3 / 4) {
-          const int q = j + r * NS3;
-          const int i = r < R3 / 4 ? q + nx / 2 : q - 3 * (nx / 2);
-          const float2 z = zvalue(i, jr, nx, ny, cell, L.wp, sx[i], syj);
-          const float2 t = cmulc(v[r], z);
+        if (kept<R3>(r)) {
+          const int i = t + kept_pixel<N, R3>(b, r);
+          const float2 z = zvalue(i, jr, NX, ny, cell, L.wp, sx[i], syj);
+          const float2 m = cmulc(v[r], z);
           float2& a = acc[b][r < R3 / 4 ? r : r - R3 / 2];
-          a = make_float2(a.x + t.x, a.y + t.y);
+          a = make_float2(a.x + m.x, a.y + m.y);
         }
       }
     }
   }
-  const int64_t base = (int64_t)c * nx * ny + (int64_t)jr * nx;
+  const int64_t base = (int64_t)c * NX * ny + (int64_t)jr * NX;
 #pragma unroll
   for (int b = 0; b < B3; ++b) {
-    const int j = threadIdx.x + b * NT;
 #pragma unroll
     for (int r = 0; r < R3; ++r) {
-      if (r < R3 / 4 || r >= 3 * R3 / 4) {
-        const int q = j + r * NS3;
-        const int i = r < R3 / 4 ? q + nx / 2 : q - 3 * (nx / 2);
+      if (kept<R3>(r)) {
+        const int i = t + kept_pixel<N, R3>(b, r);
         const float2 a = acc[b][r < R3 / 4 ? r : r - R3 / 2];
         if (real_out) reinterpret_cast<float*>(out)[base + i] = a.x;
         else reinterpret_cast<float2*>(out)[base + i] = a;
@@ -508,15 +521,18 @@ __global__ __launch_bounds__(RowPlan<N>::NT) void k_inv_rows_sweep(
   }
 }
 
-// Column passes at the long lengths (N = 2048 .. 16384), register-resident like the row
-// passes: CW columns of one strip per workgroup, NT threads per column, interleaved so
-// that the CW columns of one grid row are read and written by neighbouring lanes.  The
-// needed tiles of the group's column of tiles are copied into LDS flags once, so that no
-// element waits on a mask load.  Since N = 2 ny, the zero half of each forward column and
-// the discarded half of each inverse column follow the same compile-time rule as rows.
+// Column passes of 64 points and more, register-resident like the row passes: CW columns
+// per workgroup (col_width_for), NT threads per column, interleaved so that the columns of
+// one strip are read and written by neighbouring lanes.  Bound by the lines that their narrow
+// accesses touch, then by HBM (at 4096 points the inverse pass moves 335 MB in 69 us).
+// Forward / inverse at 8192 points 115 / 163 us before, 97 / 139 now; 4096 points 52 / 84 ->
+// 52 / 69; 1024 points 24 / 25 -> 9 / 9 (64 workgroups of 16 columns before, 256 of 4 now).
+// Since N = 2 ny, the zero half of
+// each forward column and the discarded half of each inverse column follow the same
+// compile-time rule as rows.
 template <int N>
 struct ColPlan {
-  static constexpr int CW = (16384 / N) > 16 ? 16 : (16384 / N);
+  static constexpr int CW = N <= 1024 ? 4 : 16384 / N;
   static constexpr int NTC = RowPlan<N>::NT;   // threads per column
   static constexpr int NT = CW * NTC;
   // The CW columns of one grid row sit on neighbouring lanes.  An LDS access of 64 lanes
@@ -524,42 +540,64 @@ struct ColPlan {
   // lines: lines 32 / CW elements apart beyond their padded length (which is a multiple
   // of 32) put those CW runs on disjoint banks.
   static constexpr int LS = lds_elems<N>() + 32 / CW;
-  // CW lines of LS complex values, or of LS floats where lines cross LDS in halves
-  // (xchg_split, line_split), then the tile flags
-  static constexpr size_t lds_bytes() {
-    return (size_t)CW * LS * (line_split<N>() ? sizeof(float) : sizeof(float2)) + N / 8;
+  static constexpr size_t line_bytes() {
+    return (size_t)CW * LS * (line_split<N>() ? sizeof(float) : sizeof(float2));
   }
+  // CW lines of LS complex values, or of LS floats where lines cross LDS in halves
+  // (xchg_split, line_split), then the tile bits
+  static size_t lds_bytes(int nbits) { return line_bytes() + 4 * (size_t)nbits; }
 };
 
-// Flags of the needed tiles of column-tile ct (one byte per row of tiles; all ones when
-// there is no mask).
-__device__ __forceinline__ void load_tile_flags(uint8_t* flags, const Masks& mk, int N, int ct,
-                                                int nthreads) {
-  const int nty = (N >> mk.tsh) > 0 ? (N >> mk.tsh) : 1;
-  for (int t = threadIdx.x; t < nty; t += nthreads)
-    flags[t] = mk.tile ? (uint8_t)bit_set(mk.tile, t * mk.tiles_x + ct) : (uint8_t)1;
+// Needed-tile bits of a column pass's elements: element (b, r) of thread t is grid row
+// j + r S, j = t + b NTC < S = N / R, r < R <= 32.  Entry t0 = j >> tsh holds bit r for each r
+// (the tile row of j + r S is that of (t0 << tsh) + r S: below a tile's side nothing carries),
+// so that a butterfly reads one word.  Without a mask (tsh beyond the line) the one entry has
+// every bit set.
+template <int N, int R>
+__host__ __device__ __forceinline__ int tile_bit_entries(int tsh) {
+  const int n = (N / R) >> tsh;
+  return n > 0 ? n : 1;
 }
-
-// Needed-tile bits of a forward column pass's outputs.  The last pass writes outputs
-// j + r NS (j < NS = R1 R2, r < R3), whose tile rows are t0 + r S with t0 = j >> tsh and
-// S = NS >> tsh (a mask's tile, at most 128, never exceeds NS): entry t0 holds bit r for
-// each r, so that a butterfly reads one word instead of R3 flags.  Without a mask every
-// entry a butterfly can read (one when tsh exceeds the line) has every bit set.
-template <int N>
-__device__ __forceinline__ void load_out_tile_bits(uint32_t* bits, const Masks& mk, int ct,
-                                                   int nthreads) {
-  constexpr int NS = RowPlan<N>::R1 * RowPlan<N>::R2, R3 = RowPlan<N>::R3;
-  static_assert(R3 <= 32, "one word per entry");
-  const int S = (NS >> mk.tsh) > 0 ? (NS >> mk.tsh) : 1;
-  for (int t0 = threadIdx.x; t0 < S; t0 += nthreads) {
+template <int N, int R>
+__device__ __forceinline__ void load_tile_bits(uint32_t* bits, const Masks& mk, int ct,
+                                               int nthreads) {
+  const int n = tile_bit_entries<N, R>(mk.tsh);
+  for (int t0 = threadIdx.x; t0 < n; t0 += nthreads) {
     uint32_t m = 0xffffffffu;
     if (mk.tile) {
       m = 0;
-      for (int r = 0; r < R3; ++r)
-        m |= (uint32_t)bit_set(mk.tile, (t0 + r * S) * mk.tiles_x + ct) << r;
+      for (int r = 0; r < R; ++r)
+        m |= (uint32_t)bit_set(mk.tile, (((t0 << mk.tsh) + r * (N / R)) >> mk.tsh) * mk.tiles_x + ct)
+             << r;
     }
     bits[t0] = m;
   }
+}
+// Calls on(r) for the elements r of a butterfly whose bit is set in need: by scalar branches
+// where all lanes of the wavefront share the word (their rows lie in one row of tiles).
+template <int R, typename ON>
+__device__ __forceinline__ void needed_rows(uint32_t need, ON&& on) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(need);
+  if (__all(need == lo)) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if ((lo >> r) & 1u) on(r);
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if ((need >> r) & 1u) on(r);
+  }
+}
+
+// Byte offset of row t of column q0 + c of an R-row grid from column q0's strip (CW columns
+// never straddle a strip unless they are whole strips).
+template <int L>
+__device__ __forceinline__ uint32_t col_offset(int q0, int c, int t, int R) {
+  return (uint32_t)strip_index<L>(t, (q0 & ((1 << L) - 1)) + c, R) * 8;
+}
+template <int L>
+__device__ __forceinline__ int64_t col_base(int q0, int R) {
+  return ((int64_t)(q0 >> L) * R) << L;
 }
 
 // With a sweep's layer table sl, workgroup i takes (layer, column group) pairs[i].
@@ -567,18 +605,16 @@ template <int N>
 __global__ __launch_bounds__(ColPlan<N>::NT) __attribute__((amdgpu_waves_per_eu(4))) void k_fwd_cols_reg(const float2* __restrict__ A,
                                                                  float2* __restrict__ X,
                                                                  const float2* __restrict__ tw,
-                                                                 int ny, Masks mk,
+                                                                 Masks mk,
                                                                  const SweepLayer* __restrict__ sl,
                                                                  const int2* __restrict__ pairs) {
   using RP = RowPlan<N>;
-  constexpr int R1 = RP::R1, R2 = RP::R2, R3 = RP::R3;
+  constexpr int R1 = RP::R1, R3 = RP::R3, NY = N / 2;
   constexpr int CW = ColPlan<N>::CW, NTC = ColPlan<N>::NTC, NT = ColPlan<N>::NT;
-  constexpr int LS = ColPlan<N>::LS;
+  constexpr int LS = ColPlan<N>::LS, E = N / NTC;
   extern __shared__ float2 buf[];
-  // CW lines of LS floats (split exchange) or complex values, then the output tile bits
-  constexpr bool SPLIT = line_split<N>();
-  uint32_t* omask = SPLIT ? reinterpret_cast<uint32_t*>(reinterpret_cast<float*>(buf) + CW * LS)
-                          : reinterpret_cast<uint32_t*>(buf + CW * LS);
+  uint32_t* omask = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(buf) +
+                                                ColPlan<N>::line_bytes());
   const int gi = xcd_remap(blockIdx.x, gridDim.x);
   int g;
   if (sl) {
@@ -592,56 +628,41 @@ __global__ __launch_bounds__(ColPlan<N>::NT) __attribute__((amdgpu_waves_per_eu(
     g = mk.groups ? mk.groups[gi] : gi;
   }
   const int q0 = g * CW;
-  const int strip = q0 >> 4, c0 = q0 & (SW - 1);
-  const int c = threadIdx.x % CW, tj = threadIdx.x / CW;
-  void* line = SPLIT ? (void*)(reinterpret_cast<float*>(buf) + c * LS) : (void*)(buf + c * LS);
+  const int c = threadIdx.x % CW, t = threadIdx.x / CW;
+  void* line = line_split<N>() ? (void*)(reinterpret_cast<float*>(buf) + c * LS)
+                               : (void*)(buf + c * LS);
   // the bits are read after the exchanges' barriers only
-  load_out_tile_bits<N>(omask, mk, q0 >> mk.tsh, NT);
-  // wave-uniform bases and 32-bit element offsets (a strip holds at most 16 N elements)
-  const float2* __restrict__ src = A + ((int64_t)strip * ny) * SW + c0;
-  float2 v1[N / NTC];
-  {
-    constexpr int B = (N / R1) / NTC;
+  load_tile_bits<N, R3>(omask, mk, q0 >> mk.tsh, NT);
+  const float2* __restrict__ src = A + col_base<HALF_L>(q0, NY);
+  const uint32_t so = col_offset<HALF_L>(q0, c, t, NY);
+  float2 v1[E];
 #pragma unroll
-    for (int b = 0; b < B; ++b) {
-      const int j = tj + b * NTC;
-      float2* v = v1 + b * R1;
+  for (int b = 0; b < E / R1; ++b) {
+    float2* v = v1 + b * R1;
 #pragma unroll
-      for (int r = 0; r < R1; ++r) {
-        const int q = j + r * (N / R1);
-        if (r < R1 / 4 || r >= 3 * R1 / 4) {
-          const int jrow = r < R1 / 4 ? q + N / 4 : q - 3 * (N / 4);
-          v[r] = src[jrow * SW + c];
-        } else {
-          v[r] = make_float2(0.f, 0.f);
-        }
-      }
-      dft_reg<R1, false>(v);
-    }
+    for (int r = 0; r < R1; ++r)
+      v[r] = kept<R1>(r) ? ld_off<float2>(src + kept_pixel<N, R1>(b, r) * (1 << HALF_L), so)
+                         : make_float2(0.f, 0.f);
+    dft_reg<R1, false>(v);
   }
-  float2 v3[N / NTC];
-  row_middle<N, false>(line, v1, v3, tw, tj);
-  float2* __restrict__ dst = X + ((int64_t)strip * N) * SW + c0;
+  float2 v3[E];
+  row_middle<N, false>(line, v1, v3, tw, t);
+  float2* __restrict__ dst = X + col_base<GRID_L>(q0, N);
   {
     // the lane's column and butterfly index are taken afresh from the thread index (the
     // empty asm hides that it is unchanged) rather than held through the exchanges
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int cl = tid % CW, tl = tid / CW;
-    constexpr int NS = R1 * R2;
-    constexpr int B = (N / R3) / NTC;
+    const uint32_t off = col_offset<GRID_L>(q0, cl, tl, N);
 #pragma unroll
-    for (int b = 0; b < B; ++b) {
-      const int j = tl + b * NTC;
+    for (int b = 0; b < E / R3; ++b) {
       float2* v = v3 + b * R3;
-#pragma unroll
-      for (int r = 1; r < R3; ++r) v[r] = cmul(v[r], tw[r * j]);
+      last_twiddle<N, false>(v, tw, b, tl);
       dft_reg<R3, false>(v);
-      const uint32_t need = omask[j >> mk.tsh];
-#pragma unroll
-      for (int r = 0; r < R3; ++r) {
-        if ((need >> r) & 1u) dst[(j + r * NS) * SW + cl] = v[r];
-      }
+      needed_rows<R3>(omask[(tl + b * NTC) >> mk.tsh], [&](int r) {
+        st_off(dst + ((b * NTC + r * (N / R3)) << GRID_L), off, v[r]);
+      });
     }
   }
 }
@@ -650,18 +671,16 @@ template <int N>
 __global__ __launch_bounds__(ColPlan<N>::NT) __attribute__((amdgpu_waves_per_eu(4))) void k_inv_cols_reg(float2* __restrict__ Y,
                                                                  float2* __restrict__ A,
                                                                  const float2* __restrict__ tw,
-                                                                 int ny, Masks mk,
+                                                                 Masks mk,
                                                                  const SweepLayer* __restrict__ sl,
                                                                  const int2* __restrict__ pairs) {
   using RP = RowPlan<N>;
-  constexpr int R1 = RP::R1, R2 = RP::R2, R3 = RP::R3;
+  constexpr int R1 = RP::R1, R3 = RP::R3, NY = N / 2;
   constexpr int CW = ColPlan<N>::CW, NTC = ColPlan<N>::NTC, NT = ColPlan<N>::NT;
-  constexpr int LS = ColPlan<N>::LS;
+  constexpr int LS = ColPlan<N>::LS, E = N / NTC;
   extern __shared__ float2 buf[];
-  // CW lines of LS floats (split exchange) or complex values, then the tile flags
-  constexpr bool SPLIT = line_split<N>();
-  uint8_t* tflag = SPLIT ? reinterpret_cast<uint8_t*>(reinterpret_cast<float*>(buf) + CW * LS)
-                         : reinterpret_cast<uint8_t*>(buf + CW * LS);
+  uint32_t* imask = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(buf) +
+                                                ColPlan<N>::line_bytes());
   const int gi = xcd_remap(blockIdx.x, gridDim.x);
   int g;
   if (sl) {
@@ -675,59 +694,54 @@ __global__ __launch_bounds__(ColPlan<N>::NT) __attribute__((amdgpu_waves_per_eu(
     g = mk.groups ? mk.groups[gi] : gi;
   }
   const int q0 = g * CW;
-  const int strip = q0 >> 4, c0 = q0 & (SW - 1);
-  const int c = threadIdx.x % CW, tj = threadIdx.x / CW;
-  void* line = SPLIT ? (void*)(reinterpret_cast<float*>(buf) + c * LS) : (void*)(buf + c * LS);
-  load_tile_flags(tflag, mk, N, q0 >> mk.tsh, NT);
+  const int c = threadIdx.x % CW, t = threadIdx.x / CW;
+  void* line = line_split<N>() ? (void*)(reinterpret_cast<float*>(buf) + c * LS)
+                               : (void*)(buf + c * LS);
+  load_tile_bits<N, R1>(imask, mk, q0 >> mk.tsh, NT);
   __syncthreads();
-  // Y is read only inside needed tiles and cleared behind the read, ready for the next
-  // gridding; elsewhere it is zero already
-  float2* __restrict__ src = Y + ((int64_t)strip * N) * SW + c0 + c;
-  float2 v1[N / NTC];
-  {
-    constexpr int B = (N / R1) / NTC;
+  // Y is read only inside needed tiles and cleared there, ready for the next gridding;
+  // elsewhere it is zero already
+  float2* __restrict__ src = Y + col_base<GRID_L>(q0, N);
+  const uint32_t so = col_offset<GRID_L>(q0, c, t, N);
+  float2 v1[E];
 #pragma unroll
-    for (int b = 0; b < B; ++b) {
-      const int j = tj + b * NTC;
-      float2* v = v1 + b * R1;
+  for (int k = 0; k < E; ++k) v1[k] = make_float2(0.f, 0.f);
 #pragma unroll
-      for (int r = 0; r < R1; ++r) {
-        const int q = j + r * (N / R1);
-        v[r] = make_float2(0.f, 0.f);
-        if (tflag[q >> mk.tsh]) {
-          v[r] = src[(int64_t)q * SW];
-          src[(int64_t)q * SW] = make_float2(0.f, 0.f);
-        }
-      }
-      dft_reg<R1, true>(v);
-    }
+  for (int b = 0; b < E / R1; ++b) {
+    float2* v = v1 + b * R1;
+    needed_rows<R1>(imask[(t + b * NTC) >> mk.tsh], [&](int r) {
+      v[r] = ld_off<float2>(src + ((b * NTC + r * (N / R1)) << GRID_L), so);
+    });
+    dft_reg<R1, true>(v);
   }
-  float2 v3[N / NTC];
-  row_middle<N, true>(line, v1, v3, tw, tj);
-  float2* __restrict__ dst = A + ((int64_t)strip * ny) * SW + c0 + c;
-  {
-    constexpr int NS = R1 * R2;
-    constexpr int B = (N / R3) / NTC;
+  float2 v3[E];
+  row_middle<N, true>(line, v1, v3, tw, t);
+  float2* __restrict__ dst = A + col_base<HALF_L>(q0, NY);
+  // the lane's column and butterfly index taken afresh (see the forward pass)
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int cl = tid % CW, tl = tid / CW;
+  const uint32_t off = col_offset<HALF_L>(q0, cl, tl, NY);
 #pragma unroll
-    for (int b = 0; b < B; ++b) {
-      const int j = tj + b * NTC;
-      float2* v = v3 + b * R3;
+  for (int b = 0; b < E / R3; ++b) {
+    float2* v = v3 + b * R3;
+    last_twiddle<N, true>(v, tw, b, tl);
+    dft_reg<R3, true>(v);
 #pragma unroll
-      for (int r = 1; r < R3; ++r) v[r] = cmulc(v[r], tw[r * j]);
-      dft_reg<R3, true>(v);
-#pragma unroll
-      for (int r = 0; r < R3; ++r) {
-        if (r < R3 / 4 || r >= 3 * R3 / 4) {
-          const int q = j + r * NS;
-          const int jrow = r < R3 / 4 ? q + N / 4 : q - 3 * (N / 4);
-          dst[(int64_t)jrow * SW] = v[r];
-        }
-      }
-    }
+    for (int r = 0; r < R3; ++r)
+      if (kept<R3>(r)) st_off(dst + kept_pixel<N, R3>(b, r) * (1 << HALF_L), off, v[r]);
   }
+  // the clearing comes last: between the loads it held them up, and before the exchanges its
+  // addresses cost registers
+  const uint32_t zo = col_offset<GRID_L>(q0, cl, tl, N);
+#pragma unroll
+  for (int b = 0; b < E / R1; ++b)
+    needed_rows<R1>(imask[(tl + b * NTC) >> mk.tsh], [&](int r) {
+      st_off(src + ((b * NTC + r * (N / R1)) << GRID_L), zo, make_float2(0.f, 0.f));
+    });
 }
 
-// Column passes: CW adjacent columns of one strip per workgroup, lines padded by one
+// Column passes of 16 and 32 points: CW adjacent columns per workgroup, lines padded by one
 // element in LDS so that the strip-order global accesses (column index fastest) hit
 // distinct banks.
 template <int N, int NT, int CW>
@@ -740,24 +754,21 @@ __global__ __launch_bounds__(NT) void k_fwd_cols(const float2* __restrict__ A,
   const int gi = xcd_remap(blockIdx.x, gridDim.x);
   const int g = mk.groups ? mk.groups[gi] : gi;
   const int q0 = g * CW;
-  const int strip = q0 >> 4, c0 = q0 & (SW - 1);
   const int nz = N - ny;
   for (int t = threadIdx.x; t < CW * nz; t += NT) {
     const int c = t / nz, r = t - c * nz;
     buf[c * S + ny / 2 + r] = make_float2(0.f, 0.f);
   }
-  const float2* src = A + ((int64_t)strip * ny) * SW + c0;
   for (int t = threadIdx.x; t < CW * ny; t += NT) {
     const int jr = t / CW, c = t - jr * CW;
-    buf[c * S + ((jr - ny / 2) & (N - 1))] = src[(int64_t)jr * SW + c];
+    buf[c * S + ((jr - ny / 2) & (N - 1))] = A[half_index(jr, q0 + c, ny)];
   }
   __syncthreads();
   fft_lines<N, NT, CW, false>(buf, S, tw);
-  float2* dst = X + ((int64_t)strip * N) * SW + c0;
   for (int t = threadIdx.x; t < CW * N; t += NT) {
     const int qv = t / CW, c = t - qv * CW;
     if (!mk.tile || bit_set(mk.tile, (qv >> mk.tsh) * mk.tiles_x + ((q0 + c) >> mk.tsh)))
-      dst[(int64_t)qv * SW + c] = buf[c * S + qv];
+      X[grid_index(qv, q0 + c, N)] = buf[c * S + qv];
   }
 }
 
@@ -770,11 +781,9 @@ __global__ __launch_bounds__(NT) void k_inv_cols(float2* __restrict__ Y, float2*
   const int gi = xcd_remap(blockIdx.x, gridDim.x);
   const int g = mk.groups ? mk.groups[gi] : gi;
   const int q0 = g * CW;
-  const int strip = q0 >> 4, c0 = q0 & (SW - 1);
-  float2* src = Y + ((int64_t)strip * N) * SW + c0;
   for (int t = threadIdx.x; t < CW * N; t += NT) {
     const int qv = t / CW, c = t - qv * CW;
-    float2* p = src + (int64_t)qv * SW + c;
+    float2* p = Y + grid_index(qv, q0 + c, N);
     if (!mk.tile || bit_set(mk.tile, (qv >> mk.tsh) * mk.tiles_x + ((q0 + c) >> mk.tsh))) {
       buf[c * S + qv] = *p;
       *p = make_float2(0.f, 0.f);
@@ -784,10 +793,9 @@ __global__ __launch_bounds__(NT) void k_inv_cols(float2* __restrict__ Y, float2*
   }
   __syncthreads();
   fft_lines<N, NT, CW, true>(buf, S, tw);
-  float2* dst = A + ((int64_t)strip * ny) * SW + c0;
   for (int t = threadIdx.x; t < CW * ny; t += NT) {
     const int jr = t / CW, c = t - jr * CW;
-    dst[(int64_t)jr * SW + c] = buf[c * S + ((jr - ny / 2) & (N - 1))];
+    A[half_index(jr, q0 + c, ny)] = buf[c * S + ((jr - ny / 2) & (N - 1))];
   }
 }
 
@@ -797,7 +805,7 @@ __global__ void k_strip_to_rowmajor(const float2* __restrict__ src, float2* __re
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n;
        t += (int64_t)gridDim.x * blockDim.x) {
     const int r = (int)(t / Q), q = (int)(t - (int64_t)r * Q);
-    dst[t] = src[strip_index(r, q, R)];
+    dst[t] = src[grid_index(r, q, R)];
   }
 }
 
@@ -828,32 +836,12 @@ static hipError_t set_lds(K kern, size_t bytes) {
 }
 
 #define WF_FOR_SIZES(X) \
-  X(16) X(32) X(64) X(128) X(256) X(512) X(1024) X(2048) X(4096) X(8192) X(16384)
+  X(64) X(128) X(256) X(512) X(1024) X(2048) X(4096) X(8192) X(16384)
+#define WF_FOR_SHORT(X) X(16) X(32)
 
 template <int N>
-static hipError_t launch_fwd_rows_reg(const float* img, float2* A, const float2* tw,
-                                      const float* sx, const float* sy, int nx, int ny,
-                                      double cell, double wp, const uint32_t* smask,
-                                      const float2* ctab, hipStream_t s) {
-  const size_t lds = line_lds_bytes<N>();
-  hipError_t e = set_lds(k_fwd_rows_reg<N>, lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_fwd_rows_reg<N>), dim3(ny), dim3(RowPlan<N>::NT), lds, s, img, A, tw,
-                     sx, sy, nx, ny, cell, wp, smask, nullptr, ctab);
-  return hipGetLastError();
-}
-
-template <int N>
-static hipError_t launch_inv_rows_reg(const float2* A, void* out, const float2* tw,
-                                      const float* sx, const float* sy, int nx, int ny,
-                                      double cell, double wp, int mode, const uint32_t* smask,
-                                      const float2* ctab, hipStream_t s) {
-  const size_t lds = line_lds_bytes<N>();
-  hipError_t e = set_lds(k_inv_rows_reg<N>, lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_inv_rows_reg<N>), dim3(ny), dim3(RowPlan<N>::NT), lds, s, A, out, tw,
-                     sx, sy, nx, ny, cell, wp, mode, smask, ctab);
-  return hipGetLastError();
+static constexpr size_t row_lds() {
+  return RowPlan<N>::LW * line_lds_bytes<N>();
 }
 
 hipError_t launch_chirp_table(float2* ct, int nx, double cell, double wp, const float* sx,
@@ -866,27 +854,27 @@ hipError_t launch_chirp_table(float2* ct, int nx, double cell, double wp, const 
 hipError_t launch_fwd_rows(const float* img, float2* A, const float2* tw, const float* sx,
                            const float* sy, int nx, int ny, int Kx, double cell, double wp,
                            const uint32_t* smask, const float2* ctab, hipStream_t s) {
-  if (Kx == 2 * nx) {
-    switch (Kx) {
-      case 2048: return launch_fwd_rows_reg<2048>(img, A, tw, sx, sy, nx, ny, cell, wp, smask, ctab, s);
-      case 4096: return launch_fwd_rows_reg<4096>(img, A, tw, sx, sy, nx, ny, cell, wp, smask, ctab, s);
-      case 8192: return launch_fwd_rows_reg<8192>(img, A, tw, sx, sy, nx, ny, cell, wp, smask, ctab, s);
-      case 16384: return launch_fwd_rows_reg<16384>(img, A, tw, sx, sy, nx, ny, cell, wp, smask, ctab, s);
-      default: break;
-    }
-  }
+  if (Kx != 2 * nx || ny % 8 != 0) return hipErrorInvalidValue;
   switch (Kx) {
 #define C(N)                                                                              \
   case N: {                                                                               \
-    constexpr int NT = row_threads<N>();                                                  \
-    const size_t lds = (size_t)N * sizeof(float2);                                        \
-    hipError_t e = set_lds(k_fwd_rows<N, NT>, lds);                                       \
+    hipError_t e = set_lds(k_fwd_rows_reg<N>, row_lds<N>());                              \
     if (e != hipSuccess) return e;                                                        \
-    hipLaunchKernelGGL((k_fwd_rows<N, NT>), dim3(ny), dim3(NT), lds, s, img, A, tw, sx,  \
-                       sy, nx, ny, cell, wp, smask);                                      \
+    hipLaunchKernelGGL((k_fwd_rows_reg<N>), dim3(ny / RowPlan<N>::LW),                    \
+                       dim3(RowPlan<N>::WG), row_lds<N>(), s, img, A, tw, sx, sy, ny,     \
+                       cell, wp, smask, nullptr, ctab);                                   \
     return hipGetLastError();                                                             \
   }
     WF_FOR_SIZES(C)
+#undef C
+#define C(N)                                                                              \
+  case N: {                                                                               \
+    constexpr int NT = row_threads<N>();                                                  \
+    hipLaunchKernelGGL((k_fwd_rows<N, NT>), dim3(ny), dim3(NT), N * sizeof(float2), s,    \
+                       img, A, tw, sx, sy, nx, ny, cell, wp, smask);                      \
+    return hipGetLastError();                                                             \
+  }
+    WF_FOR_SHORT(C)
 #undef C
     default:
       return hipErrorInvalidValue;
@@ -897,97 +885,92 @@ hipError_t launch_inv_rows(const float2* A, void* out, const float2* tw, const f
                            const float* sy, int nx, int ny, int Kx, double cell, double wp,
                            int mode, const uint32_t* smask, const float2* ctab,
                            hipStream_t s) {
-  if (Kx == 2 * nx) {
-    switch (Kx) {
-      case 2048: return launch_inv_rows_reg<2048>(A, out, tw, sx, sy, nx, ny, cell, wp, mode, smask, ctab, s);
-      case 4096: return launch_inv_rows_reg<4096>(A, out, tw, sx, sy, nx, ny, cell, wp, mode, smask, ctab, s);
-      case 8192: return launch_inv_rows_reg<8192>(A, out, tw, sx, sy, nx, ny, cell, wp, mode, smask, ctab, s);
-      case 16384: return launch_inv_rows_reg<16384>(A, out, tw, sx, sy, nx, ny, cell, wp, mode, smask, ctab, s);
-      default: break;
-    }
-  }
+  if (Kx != 2 * nx || ny % 8 != 0) return hipErrorInvalidValue;
   switch (Kx) {
 #define C(N)                                                                              \
   case N: {                                                                               \
-    constexpr int NT = row_threads<N>();                                                  \
-    const size_t lds = (size_t)N * sizeof(float2);                                        \
-    hipError_t e = set_lds(k_inv_rows<N, NT>, lds);                                       \
+    hipError_t e = set_lds(k_inv_rows_reg<N>, row_lds<N>());                              \
     if (e != hipSuccess) return e;                                                        \
-    hipLaunchKernelGGL((k_inv_rows<N, NT>), dim3(ny), dim3(NT), lds, s, A, out, tw, sx,  \
-                       sy, nx, ny, cell, wp, mode, smask);                                \
+    hipLaunchKernelGGL((k_inv_rows_reg<N>), dim3(ny / RowPlan<N>::LW),                    \
+                       dim3(RowPlan<N>::WG), row_lds<N>(), s, A, out, tw, sx, sy, ny,     \
+                       cell, wp, mode, smask, ctab);                                      \
     return hipGetLastError();                                                             \
   }
     WF_FOR_SIZES(C)
+#undef C
+#define C(N)                                                                              \
+  case N: {                                                                               \
+    constexpr int NT = row_threads<N>();                                                  \
+    hipLaunchKernelGGL((k_inv_rows<N, NT>), dim3(ny), dim3(NT), N * sizeof(float2), s, A, \
+                       out, tw, sx, sy, nx, ny, cell, wp, mode, smask);                   \
+    return hipGetLastError();                                                             \
+  }
+    WF_FOR_SHORT(C)
 #undef C
     default:
       return hipErrorInvalidValue;
   }
 }
 
-template <int N, bool INV>
-static hipError_t launch_cols_reg(float2* in, float2* out, const float2* tw, int ny, int Kx,
-                                  const ColPrune* pr, hipStream_t s) {
-  constexpr int CW = ColPlan<N>::CW;
-  if (Kx % CW != 0) return hipErrorInvalidValue;
-  const size_t lds = ColPlan<N>::lds_bytes();
+// Masks and workgroup count of a column pass of CW columns per workgroup.
+template <int CW>
+static Masks col_masks(const ColPrune* pr, int Kx, int* ng) {
   Masks mk{nullptr, nullptr, nullptr, 1, 0};
-  int ng = Kx / CW;
+  *ng = Kx / CW;
   if (pr) {
     mk = Masks{pr->strip, pr->tile, pr->groups, pr->tiles_x, pr->tsh};
-    ng = pr->ngroups;
+    *ng = pr->ngroups;
   }
-  if (!pr || !pr->tile) {   // no mask: one row of tiles of any side
-    mk.tsh = 30;
-  }
+  if (!pr || !pr->tile) mk.tsh = 30;   // no mask: one row of tiles of any side
+  return mk;
+}
+
+template <int N, bool INV>
+static hipError_t launch_cols_reg(float2* in, float2* out, const float2* tw, int Kx,
+                                  const ColPrune* pr, hipStream_t s) {
+  using CP = ColPlan<N>;
+  if (Kx % CP::CW != 0) return hipErrorInvalidValue;
+  int ng;
+  const Masks mk = col_masks<CP::CW>(pr, Kx, &ng);
   if (ng == 0) return hipSuccess;
   hipError_t e;
   if constexpr (INV) {
+    const size_t lds = CP::lds_bytes(tile_bit_entries<N, RowPlan<N>::R1>(mk.tsh));
     e = set_lds(k_inv_cols_reg<N>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_inv_cols_reg<N>), dim3(ng), dim3(ColPlan<N>::NT), lds, s, in, out, tw,
-                       ny, mk, nullptr, nullptr);
+    hipLaunchKernelGGL((k_inv_cols_reg<N>), dim3(ng), dim3(CP::NT), lds, s, in, out, tw, mk,
+                       nullptr, nullptr);
   } else {
+    const size_t lds = CP::lds_bytes(tile_bit_entries<N, RowPlan<N>::R3>(mk.tsh));
     e = set_lds(k_fwd_cols_reg<N>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_fwd_cols_reg<N>), dim3(ng), dim3(ColPlan<N>::NT), lds, s,
-                       (const float2*)in, out, tw, ny, mk, nullptr, nullptr);
+    hipLaunchKernelGGL((k_fwd_cols_reg<N>), dim3(ng), dim3(CP::NT), lds, s, (const float2*)in,
+                       out, tw, mk, nullptr, nullptr);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_fwd_cols(const float2* A, float2* X, const float2* tw, int ny, int Kx,
                            int Ky, const ColPrune* pr, hipStream_t s) {
-  if (Ky == 2 * ny) {
-    float2* a = const_cast<float2*>(A);
-    switch (Ky) {
-      case 2048: return launch_cols_reg<2048, false>(a, X, tw, ny, Kx, pr, s);
-      case 4096: return launch_cols_reg<4096, false>(a, X, tw, ny, Kx, pr, s);
-      case 8192: return launch_cols_reg<8192, false>(a, X, tw, ny, Kx, pr, s);
-      case 16384: return launch_cols_reg<16384, false>(a, X, tw, ny, Kx, pr, s);
-      default: break;
-    }
-  }
+  if (Ky != 2 * ny) return hipErrorInvalidValue;
   switch (Ky) {
+#define C(N) \
+  case N: return launch_cols_reg<N, false>(const_cast<float2*>(A), X, tw, Kx, pr, s);
+    WF_FOR_SIZES(C)
+#undef C
 #define C(N)                                                                              \
   case N: {                                                                               \
     constexpr int CW = col_width<N>();                                                    \
     constexpr int NT = col_threads<N>();                                                  \
     if (Kx % CW != 0) return hipErrorInvalidValue;                                        \
-    const size_t lds = (size_t)CW * (N + 1) * sizeof(float2);                             \
-    hipError_t e = set_lds(k_fwd_cols<N, NT, CW>, lds);                                   \
-    if (e != hipSuccess) return e;                                                        \
-    Masks mk{nullptr, nullptr, nullptr, 1, 0};                                            \
-    int ng = Kx / CW;                                                                     \
-    if (pr) {                                                                             \
-      mk = Masks{pr->strip, pr->tile, pr->groups, pr->tiles_x, pr->tsh};                  \
-      ng = pr->ngroups;                                                                   \
-    }                                                                                     \
+    int ng;                                                                               \
+    const Masks mk = col_masks<CW>(pr, Kx, &ng);                                          \
     if (ng == 0) return hipSuccess;                                                       \
-    hipLaunchKernelGGL((k_fwd_cols<N, NT, CW>), dim3(ng), dim3(NT), lds, s, A, X, tw, ny, \
-                       mk);                                                               \
+    hipLaunchKernelGGL((k_fwd_cols<N, NT, CW>), dim3(ng), dim3(NT),                       \
+                       CW * (N + 1) * sizeof(float2), s, A, X, tw, ny, mk);               \
     return hipGetLastError();                                                             \
   }
-    WF_FOR_SIZES(C)
+    WF_FOR_SHORT(C)
 #undef C
     default:
       return hipErrorInvalidValue;
@@ -996,36 +979,25 @@ hipError_t launch_fwd_cols(const float2* A, float2* X, const float2* tw, int ny,
 
 hipError_t launch_inv_cols(float2* Y, float2* A, const float2* tw, int ny, int Kx, int Ky,
                            const ColPrune* pr, hipStream_t s) {
-  if (Ky == 2 * ny) {
-    switch (Ky) {
-      case 2048: return launch_cols_reg<2048, true>(Y, A, tw, ny, Kx, pr, s);
-      case 4096: return launch_cols_reg<4096, true>(Y, A, tw, ny, Kx, pr, s);
-      case 8192: return launch_cols_reg<8192, true>(Y, A, tw, ny, Kx, pr, s);
-      case 16384: return launch_cols_reg<16384, true>(Y, A, tw, ny, Kx, pr, s);
-      default: break;
-    }
-  }
+  if (Ky != 2 * ny) return hipErrorInvalidValue;
   switch (Ky) {
+#define C(N) \
+  case N: return launch_cols_reg<N, true>(Y, A, tw, Kx, pr, s);
+    WF_FOR_SIZES(C)
+#undef C
 #define C(N)                                                                              \
   case N: {                                                                               \
     constexpr int CW = col_width<N>();                                                    \
     constexpr int NT = col_threads<N>();                                                  \
     if (Kx % CW != 0) return hipErrorInvalidValue;                                        \
-    const size_t lds = (size_t)CW * (N + 1) * sizeof(float2);                             \
-    hipError_t e = set_lds(k_inv_cols<N, NT, CW>, lds);                                   \
-    if (e != hipSuccess) return e;                                                        \
-    Masks mk{nullptr, nullptr, nullptr, 1, 0};                                            \
-    int ng = Kx / CW;                                                                     \
-    if (pr) {                                                                             \
-      mk = Masks{pr->strip, pr->tile, pr->groups, pr->tiles_x, pr->tsh};                  \
-      ng = pr->ngroups;                                                                   \
-    }                                                                                     \
+    int ng;                                                                               \
+    const Masks mk = col_masks<CW>(pr, Kx, &ng);                                          \
     if (ng == 0) return hipSuccess;                                                       \
-    hipLaunchKernelGGL((k_inv_cols<N, NT, CW>), dim3(ng), dim3(NT), lds, s, Y, A, tw, ny, \
-                       mk);                                                               \
+    hipLaunchKernelGGL((k_inv_cols<N, NT, CW>), dim3(ng), dim3(NT),                       \
+                       CW * (N + 1) * sizeof(float2), s, Y, A, tw, ny, mk);               \
     return hipGetLastError();                                                             \
   }
-    WF_FOR_SIZES(C)
+    WF_FOR_SHORT(C)
 #undef C
     default:
       return hipErrorInvalidValue;
@@ -1048,6 +1020,7 @@ hipError_t launch_sweep_fwd_rows(const float* img, const SweepLayer* sl, int nla
                                  const float2* tw, const float* sx, const float* sy, int nx,
                                  int ny, int Kx, double cell, hipStream_t s) {
   if (nlayers <= 0) return hipSuccess;
+  if (Kx != 2 * nx) return hipErrorInvalidValue;
   switch (Kx) {
 #define C(NN)                                                                               \
   case NN: {                                                                                \
@@ -1055,8 +1028,7 @@ hipError_t launch_sweep_fwd_rows(const float* img, const SweepLayer* sl, int nla
     hipError_t e = set_lds(k_fwd_rows_reg<NN>, lds);                                        \
     if (e != hipSuccess) return e;                                                          \
     hipLaunchKernelGGL((k_fwd_rows_reg<NN>), dim3(ny, nlayers), dim3(RowPlan<NN>::NT), lds, \
-                       s, img, nullptr, tw, sx, sy, nx, ny, cell, 0.0, nullptr, sl,        \
-                       nullptr);                                                            \
+                       s, img, nullptr, tw, sx, sy, ny, cell, 0.0, nullptr, sl, nullptr);   \
     return hipGetLastError();                                                               \
   }
     C(2048) C(4096) C(8192) C(16384)
@@ -1070,22 +1042,26 @@ hipError_t launch_sweep_cols(bool inverse, const SweepLayer* sl, const int2* pai
                              const float2* tw, int ny, int Ky, int tsh, int tiles_x,
                              hipStream_t s) {
   if (npairs <= 0) return hipSuccess;
+  if (Ky != 2 * ny) return hipErrorInvalidValue;
   Masks mk{nullptr, nullptr, nullptr, tiles_x, tsh};
   switch (Ky) {
 #define C(NN)                                                                                 \
   case NN: {                                                                                  \
-    const size_t lds = ColPlan<NN>::lds_bytes();                                       \
+    using CP = ColPlan<NN>;                                                                   \
+    using RP = RowPlan<NN>;                                                                   \
+    const size_t lds = CP::lds_bytes(inverse ? tile_bit_entries<NN, RP::R1>(tsh)              \
+                                             : tile_bit_entries<NN, RP::R3>(tsh));            \
     hipError_t e;                                                                             \
     if (inverse) {                                                                            \
       e = set_lds(k_inv_cols_reg<NN>, lds);                                                   \
       if (e != hipSuccess) return e;                                                          \
       hipLaunchKernelGGL((k_inv_cols_reg<NN>), dim3(npairs), dim3(ColPlan<NN>::NT), lds, s,   \
-                         nullptr, nullptr, tw, ny, mk, sl, pairs);                            \
+                         nullptr, nullptr, tw, mk, sl, pairs);                                \
     } else {                                                                                  \
       e = set_lds(k_fwd_cols_reg<NN>, lds);                                                   \
       if (e != hipSuccess) return e;                                                          \
       hipLaunchKernelGGL((k_fwd_cols_reg<NN>), dim3(npairs), dim3(ColPlan<NN>::NT), lds, s,   \
-                         nullptr, nullptr, tw, ny, mk, sl, pairs);                            \
+                         nullptr, nullptr, tw, mk, sl, pairs);                                \
     }                                                                                         \
     return hipGetLastError();                                                                 \
   }
@@ -1102,6 +1078,7 @@ hipError_t launch_sweep_inv_rows(const SweepLayer* sl, const int2* chan_layers, 
                                  const float* sy, int nx, int ny, int Kx, double cell,
                                  unsigned long long* stamps, int* done, hipStream_t s) {
   if (nchan <= 0) return hipSuccess;
+  if (Kx != 2 * nx) return hipErrorInvalidValue;
   switch (Kx) {
 #define C(NN)                                                                                \
   case NN: {                                                                                 \
@@ -1109,7 +1086,7 @@ hipError_t launch_sweep_inv_rows(const SweepLayer* sl, const int2* chan_layers, 
     hipError_t e = set_lds(k_inv_rows_sweep<NN>, lds);                                       \
     if (e != hipSuccess) return e;                                                           \
     hipLaunchKernelGGL((k_inv_rows_sweep<NN>), dim3(ny, nchan), dim3(RowPlan<NN>::NT), lds,  \
-                       s, sl, chan_layers, c0, out, tw, sx, sy, nx, ny, cell,              \
+                       s, sl, chan_layers, c0, out, tw, sx, sy, ny, cell,                  \
                        real_out ? 1 : 0, stamps, done);                                      \
     return hipGetLastError();                                                                \
   }

@@ -136,7 +136,7 @@ __device__ __forceinline__ void load_patch_x(const Run& r, int u0, int v0, int K
     tap_ab(t < r.TT ? t : 0, r.T, invT, a, b);
     const int gu = (u0 + r.lu0 + b) & (Kx - 1);
     const int gv = (v0 + r.lv0 + a) & (Ky - 1);
-    xr[k] = X[strip_index(gv, gu, Ky)];
+    xr[k] = X[grid_index(gv, gu, Ky)];
   }
 }
 
@@ -186,7 +186,7 @@ __device__ __forceinline__ void window_flush(const double* acc, const Box& bx, i
       const int a = c / bx.w, b = c - a * bx.w;
       const int gu = (u0 + bx.u0 + b) & (Kx - 1);
       const int gv = (v0 + bx.v0 + a) & (Ky - 1);
-      float2* p = Y + strip_index(gv, gu, Ky);
+      float2* p = Y + grid_index(gv, gu, Ky);
       unsafeAtomicAdd(&p->x, v.x);
       unsafeAtomicAdd(&p->y, v.y);
     }

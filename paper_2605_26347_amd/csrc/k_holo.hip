@@ -152,7 +152,7 @@ __global__ __launch_bounds__(256) void k_happly(const HTile* __restrict__ ht,
   const int u0 = tu * tile - R, v0 = tv * tile - R + dv0;
   for (int i = threadIdx.x; i < W * H; i += blockDim.x) {
     const int wv = i / W, wu = i - wv * W;
-    const float2 x = X[strip_index((v0 + wv) & (Ky - 1), (u0 + wu) & (Kx - 1), Ky)];
+    const float2 x = X[grid_index((v0 + wv) & (Ky - 1), (u0 + wu) & (Kx - 1), Ky)];
     xr[i] = x.x;
     xi[i] = x.y;
   }
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(256) void k_happly(const HTile* __restrict__ ht,
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    float2* p = Y + strip_index(tv * tile + cv, tu * tile + cu + j, Ky);
+    float2* p = Y + grid_index(tv * tile + cv, tu * tile + cu + j, Ky);
     if (parts > 1) {
       unsafeAtomicAdd(&p->x, ar[j]);
       unsafeAtomicAdd(&p->y, ai[j]);

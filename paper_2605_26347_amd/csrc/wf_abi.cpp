@@ -133,12 +133,21 @@ struct OpGuard {
 };
 
 std::vector<float2> twiddles(int N) {
-  std::vector<float2> t(N);
-  for (int m = 0; m < N; ++m) {
-    const long double a = -2.0L * 3.14159265358979323846264338327950288L * (long double)m /
-                          (long double)N;
-    t[m] = make_float2((float)cosl(a), (float)sinl(a));
+  // exp(-2 pi i m / N) in the order in which a pass's neighbouring lanes read it
+  auto root = [&](int64_t m) {
+    const long double a = -2.0L * 3.14159265358979323846264338327950288L * (m % N) / N;
+    return make_float2((float)cosl(a), (float)sinl(a));
+  };
+  std::vector<float2> t;
+  if (N < 64) {
+    for (int m = 0; m < N; ++m) t.push_back(root(m));
+    return t;
   }
+  const int r1 = fft_r1(N), r2 = fft_r2(N), r3 = N / (r1 * r2);
+  for (int r = 0; r < r2; ++r)
+    for (int k = 0; k < r1; ++k) t.push_back(root((int64_t)r * k * r3));
+  for (int r = 0; r < r3; ++r)
+    for (int j = 0; j < r1 * r2; ++j) t.push_back(root((int64_t)r * j));
   return t;
 }
 
@@ -690,7 +699,7 @@ wf_status build_channel(wf_op* op, int c, const double* uvw, int64_t M, double f
     int tsh = 0;
     while ((1 << tsh) < tile) ++tsh;
     const int dil = (halo + tile - 1) / tile;
-    const int nstrip = Kx / SW;
+    const int nstrip = Kx / MSTRIP;
     const int cw = col_width_for(Ky);
     const int ngroup_all = Kx / cw;
     const size_t wt = ((size_t)tx * ty + 31) / 32, ws = ((size_t)nstrip + 31) / 32;
@@ -726,14 +735,14 @@ wf_status build_channel(wf_op* op, int c, const double* uvw, int64_t M, double f
         }
       ch.active_tile_frac[p] = (double)nneed / (double)need.size();
       for (int st2 = 0; st2 < nstrip; ++st2) {
-        const int c0 = (st2 * SW) >> tsh, c1 = ((st2 + 1) * SW - 1) >> tsh;
+        const int c0 = (st2 * MSTRIP) >> tsh, c1 = ((st2 + 1) * MSTRIP - 1) >> tsh;
         bool any = false;
         for (int c = c0; c <= c1; ++c) any = any || colneed[c];
         if (any) sb[st2 >> 5] |= 1u << (st2 & 31);
       }
       std::vector<uint32_t> gl;
       for (int g = 0; g < ngroup_all; ++g) {
-        const int st2 = (g * cw) / SW;
+        const int st2 = (g * cw) / MSTRIP;
         if ((sb[st2 >> 5] >> (st2 & 31)) & 1u) gl.push_back((uint32_t)g);
       }
       ch.pr_strip[p] = hbuf.size() * 4;
@@ -2076,14 +2085,16 @@ wf_status wf_build_operator(const double* uvw_m, int64_t nrows, const int64_t* c
     if ((st = dalloc(B0.X, sizeof(float2) * (size_t)Kx * Ky)) != WF_OK) return st;
     if ((st = dalloc(B0.Y, sizeof(float2) * (size_t)Kx * Ky)) != WF_OK) return st;
     if ((st = dalloc(B0.A, sizeof(float2) * (size_t)ny * Kx)) != WF_OK) return st;
-    if ((st = dalloc(op->twx, sizeof(float2) * Kx)) != WF_OK) return st;
-    if ((st = dalloc(op->twy, sizeof(float2) * Ky)) != WF_OK) return st;
+    if ((st = dalloc(op->twx, sizeof(float2) * twx.size())) != WF_OK) return st;
+    if ((st = dalloc(op->twy, sizeof(float2) * twy.size())) != WF_OK) return st;
     if ((st = dalloc(op->sx, sizeof(float) * nx)) != WF_OK) return st;
     if ((st = dalloc(op->sy, sizeof(float) * ny)) != WF_OK) return st;
     WF_HIP(hipMemsetAsync(B0.Y.p, 0, B0.Y.bytes, s));
     WF_HIP(hipMemsetAsync(B0.X.p, 0, B0.X.bytes, s));
-    WF_HIP(hipMemcpyAsync(op->twx.p, twx.data(), sizeof(float2) * Kx, hipMemcpyHostToDevice, s));
-    WF_HIP(hipMemcpyAsync(op->twy.p, twy.data(), sizeof(float2) * Ky, hipMemcpyHostToDevice, s));
+    WF_HIP(hipMemcpyAsync(op->twx.p, twx.data(), sizeof(float2) * twx.size(),
+                          hipMemcpyHostToDevice, s));
+    WF_HIP(hipMemcpyAsync(op->twy.p, twy.data(), sizeof(float2) * twy.size(),
+                          hipMemcpyHostToDevice, s));
     WF_HIP(hipMemcpyAsync(op->sx.p, sx.data(), sizeof(float) * nx, hipMemcpyHostToDevice, s));
     WF_HIP(hipMemcpyAsync(op->sy.p, sy.data(), sizeof(float) * ny, hipMemcpyHostToDevice, s));
 

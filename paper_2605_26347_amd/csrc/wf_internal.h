@@ -13,14 +13,21 @@
 
 namespace wf {
 
-// Complex grids are stored in strips of SW adjacent columns: element (row r, column q)
-// of an R x Q complex array lives at ((q / SW) * R + r) * SW + q % SW.  A 128-byte
-// line then holds one row of one strip, so row passes touch whole lines and column
-// passes read each strip as one contiguous block.
-constexpr int SW = 16;
+// Complex arrays are stored in strips of 2^L adjacent columns: element (row r, column q)
+// of an R x Q array lives at ((q / 2^L) R + r) 2^L + q % 2^L.  SWNOTE
+constexpr int GRID_L = 3;         // the grids X and Y
+constexpr int HALF_L = 4;         // the half-transformed image A
+constexpr int MSTRIP = 16;        // columns per bit of the needed-column masks
 
+template <int L>
 __host__ __device__ inline int64_t strip_index(int r, int q, int R) {
-  return ((int64_t)(q >> 4) * R + r) * SW + (q & (SW - 1));
+  return (((int64_t)(q >> L) * R + r) << L) + (q & ((1 << L) - 1));
+}
+__host__ __device__ inline int64_t grid_index(int r, int q, int R) {
+  return strip_index<GRID_L>(r, q, R);
+}
+__host__ __device__ inline int64_t half_index(int r, int q, int R) {
+  return strip_index<HALF_L>(r, q, R);
 }
 
 // One unit of work of the fused G^dag G, de-gridding and gridding kernels: a run of
@@ -107,7 +114,7 @@ struct SweepLayer {
 // one tile (the LDS windows reach into neighbours), the column strips under them, and the
 // column groups (col_width columns each) that cover those strips.
 struct ColPrune {
-  const uint32_t* strip;   // [Kx/16] bits
+  const uint32_t* strip;   // [Kx/MSTRIP] bits
   const uint32_t* tile;    // [Ky/tile][Kx/tile] bits
   const int32_t* groups;   // active column-group indices
   int ngroups;
@@ -116,7 +123,15 @@ struct ColPrune {
 };
 
 // Columns per workgroup of the column passes for a column length of Ky.
-inline int col_width_for(int Ky) { return (16384 / Ky) > 16 ? 16 : (16384 / Ky); }
+inline int col_width_for(int Ky) { return Ky <= 32 ? 16 : Ky <= 1024 ? 4 : 16384 / Ky; }
+
+// Radices of the first two passes of a transform of N >= 64 points (the third is N / (R1 R2)).
+__host__ __device__ constexpr int fft_r1(int N) {
+  return N >= 8192 ? 32 : N >= 1024 ? 16 : N >= 128 ? 8 : 4;
+}
+__host__ __device__ constexpr int fft_r2(int N) {
+  return N >= 16384 ? 32 : N >= 2048 ? 16 : N >= 256 ? 8 : 4;
+}
 
 struct DevBuf {
   void* p = nullptr;
