@@ -45,3 +45,28 @@ def test_forward_backward_matches_oracle():
     say(f"[gpu] 10 FB iterations rel {e:.2e}")
     assert e <= 1e-4
     assert float(x.min()) >= 0.0
+
+
+@pytest.mark.parametrize("kw,sweep", [({}, False), ({"branches": 3}, False),
+                                      ({"strategy": "otf"}, False), ({}, True)])
+def test_dirty_image_is_the_adjoint_s_real_part(kw, sweep):
+    """Accumulated as a real image on every path (branches' partial sums, G on the fly, the
+    layer-batched sweep), and through buffers that overlap: the real part of the adjoint up
+    to the order of FP32 additions (2e-6)."""
+    n = 1024 if sweep else 64
+    obs = ws.widefield(n=n, nvis=5_000, fov_deg=3.0, sky=False)
+    op = gpu_operator(obs, 3, **kw)
+    if sweep:
+        op.set_sweep(True)
+    r = np.random.default_rng(2)
+    m = op.nrows_total
+    v = (r.standard_normal(m) + 1j * r.standard_normal(m)).astype(np.complex64)
+    vd = to_dev(v)
+    ref = op.adjoint(vd).cpu().numpy().real
+    for _ in range(2):
+        assert rel(op.dirty_image(vd).cpu().numpy(), ref) <= 2e-6
+    if not sweep:   # the image over the first visibilities
+        buf = to_dev(v.copy())
+        out = torch.view_as_real(buf).view(-1)[:n * n].view(1, n, n)
+        op.dirty_image(buf, out=out)
+        assert rel(out.cpu().numpy(), ref) <= 2e-6
