@@ -524,9 +524,9 @@ __global__ __launch_bounds__(RowPlan<N>::NT) void k_inv_rows_sweep(
 // Column passes of 64 points and more, register-resident like the row passes: CW columns
 // per workgroup (col_width_for), NT threads per column, interleaved so that the columns of
 // one strip are read and written by neighbouring lanes.  Bound by the lines that their narrow
-// accesses touch, then by HBM (at 4096 points the inverse pass moves 335 MB in 69 us).
-// Forward / inverse at 8192 points 115 / 163 us before, 97 / 139 now; 4096 points 52 / 84 ->
-// 52 / 69; 1024 points 24 / 25 -> 9 / 9 (64 workgroups of 16 columns before, 256 of 4 now).
+// accesses touch, then by HBM (at 4096 points the inverse pass moves 335 MB in 63 us).
+// Forward / inverse at 8192 points 115 / 163 us before, 88 / 119 now; 4096 points 52 / 84 ->
+// 48 / 63; 1024 points 24 / 25 -> 8 / 10 (64 workgroups of 16 columns before, 256 of 4 now).
 // Since N = 2 ny, the zero half of
 // each forward column and the discarded half of each inverse column follow the same
 // compile-time rule as rows.

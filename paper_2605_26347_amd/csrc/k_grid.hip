@@ -15,13 +15,21 @@
 //   * conj(g_k) y_k is accumulated in registers over the run and added into the LDS
 //     window of the tile (plus halo) once,
 // and the stored values of G are streamed from HBM exactly once.  A row's sum
-// y_k = sum_t g_k[t] X[t] is reduced across the wavefront with DPP within each
-// 16-lane row and four readlanes, which leaves y_k wave-uniform.  At the end the
+// y_k = sum_t g_k[t] X[t] is reduced across the wavefront by a half swap and DPP, which
+// leaves y_k wave-uniform.  At the end the
 // window is added into Y with global atomics (untouched cells skipped).
 //   fused G^dag G : gather + reduce + accumulate (Phi^dag Phi);
 //   de-gridding   : gather + reduce, y written to the caller's visibility order (Phi);
 //   gridding      : y read from the caller's order, accumulate (Phi^dag).
 // Values are stored as complex FP32, FP16 or BF16; all arithmetic is FP32.
+//
+// Bound by instruction issue and latency, not by the G stream: dense rows (4096^2, 30M rows,
+// FP16 fused) read G at 3.1 TB/s with the VALUs half busy, sparse rows (2048^2, 10 rows per
+// item) at 0.6 TB/s, where an item's chain of loads and its accumulator's clearing and
+// flushing are most of its time.  So a run's addresses are words formed once per patch side
+// plus scalars, both sums of a row share one reduction, the accumulator is cleared behind the
+// first loads, and the flush goes by grid lines.  Per w-layer, fused: 452 -> 421 us (dense),
+// 326 -> 297 us (sparse, channels of 1 to 3M rows).
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
@@ -79,18 +87,23 @@ __device__ __forceinline__ float2 widen(typename RawT<STORE>::type r) {
   }
 }
 
-// Sum over the wavefront, returned wave-uniform: DPP butterflies inside each row of 16
-// lanes (quad xor 1, quad xor 2, half-row mirror, row mirror) leave every lane with its
-// row's sum; broadcasting lane 15 into row 1 (and 47 into row 3), then lane 31 into rows
-// 2 and 3, leaves the total in lane 63, which is read into a scalar register.
-__device__ __forceinline__ float wave_sum_uniform(float v) {
+// Sums of x and of y over the wavefront, returned wave-uniform.  Swapping the upper half of
+// x with the lower half of y leaves one register that holds x's partial sums in lanes 0..31
+// and y's in lanes 32..63 after a single addition; DPP butterflies inside each row of 16
+// lanes (quad xor 1, quad xor 2, half-row mirror, row mirror) leave every lane with its row's
+// sum, and broadcasting lane 15 into row 1 (47 into row 3) leaves x's total in lane 31 and
+// y's in lane 63: seven instructions for both (twelve for two separate reductions).
+__device__ __forceinline__ void wave_sums_uniform(float x, float y, float& sx, float& sy) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false,
+                                                  false);
+  float v = __uint_as_float(p[0]) + __uint_as_float(p[1]);
   v += __builtin_amdgcn_update_dpp(0.f, v, 0xb1, 0xf, 0xf, false);
   v += __builtin_amdgcn_update_dpp(0.f, v, 0x4e, 0xf, 0xf, false);
   v += __builtin_amdgcn_update_dpp(0.f, v, 0x141, 0xf, 0xf, false);
   v += __builtin_amdgcn_update_dpp(0.f, v, 0x140, 0xf, 0xf, false);
   v += __builtin_amdgcn_update_dpp(0.f, v, 0x142, 0xa, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0.f, v, 0x143, 0xc, 0xf, false);
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+  sx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 31));
+  sy = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
 // A row's word: window-local patch origin lu0 | lv0 << 8 | patch side T << 16.
@@ -122,24 +135,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* vals, int
                                            TT * value_bytes<STORE>(), RSRC_WORD3);
 }
 
-// Load the grid values of a run's patch (one per lane and slot).  Slots past the patch
-// read its first cell: their stored value is zero, so they add nothing.
-template <int MK>
-__device__ __forceinline__ void load_patch_x(const Run& r, int u0, int v0, int Kx, int Ky,
-                                             const float2* __restrict__ X, int lane,
-                                             float2 (&xr)[MK]) {
-  const float invT = __builtin_amdgcn_rcpf((float)r.T);
-#pragma unroll
-  for (int k = 0; k < MK; ++k) {
-    const int t = lane + 64 * k;
-    int a, b;
-    tap_ab(t < r.TT ? t : 0, r.T, invT, a, b);
-    const int gu = (u0 + r.lu0 + b) & (Kx - 1);
-    const int gv = (v0 + r.lv0 + a) & (Ky - 1);
-    xr[k] = X[grid_index(gv, gu, Ky)];
-  }
-}
-
 // The work item's bounding box of patch cells in its window (packed by the host as
 // origin u, origin v, width, height, 8 bits each).  The LDS accumulator holds exactly
 // this box, as two planes of FP64 (real parts, then imaginary parts): LDS float atomics
@@ -153,23 +148,75 @@ __device__ __forceinline__ Box box_of(int32_t packed) {
   return Box{(int)(b & 0xff), (int)((b >> 8) & 0xff), (int)((b >> 16) & 0xff), (int)(b >> 24)};
 }
 
-// Add a run's register accumulator into the box accumulator.
+// Where the lane's taps of a T x T patch sit, one word per slot: byte offset of the cell in
+// a plane of the box accumulator (16 bits: 36 rows of 101 cells at most), patch row a << 16,
+// patch column b << 24.  It depends on T and the box alone, so it is formed when T changes
+// (an item's rows are sorted by T) and a run only adds its origin.  Slots past the patch hold
+// its last cell: they read X there (their stored value is zero) and never scatter.
 template <int MK>
-__device__ __forceinline__ void scatter_run(const Run& r, const Box& bx, int lane,
-                                            const float2 (&ac)[MK], double* acc) {
-  const float invT = __builtin_amdgcn_rcpf((float)r.T);
-  double* acci = acc + bx.w * bx.h;
-  const int base = (r.lv0 - bx.v0) * bx.w + (r.lu0 - bx.u0);
+struct Slots {
+  uint32_t w[MK];
+  int T = 0;
+  __device__ __forceinline__ void set(int side, int box_w, int lane) {
+    if (side == T) return;
+    T = side;
+    const float invT = __builtin_amdgcn_rcpf((float)side);
+    const int last = side * side - 1;
+#pragma unroll
+    for (int k = 0; k < MK; ++k) {
+      int a, b;
+      tap_ab(min(lane + 64 * k, last), side, invT, a, b);
+      w[k] = (uint32_t)((a * box_w + b) * 8) | ((uint32_t)a << 16) | ((uint32_t)b << 24);
+    }
+  }
+};
+
+// Load the grid values of a run's patch (one per lane and slot).  Away from the grid's edge
+// the patch's origin rides in a scalar base.
+template <int MK>
+__device__ __forceinline__ void load_patch_x(const Run& r, const Slots<MK>& sl, int u0, int v0,
+                                             int Kx, int Ky, int ksh,
+                                             const float2* __restrict__ X, float2 (&xr)[MK]) {
+  constexpr uint32_t M = (1u << GRID_L) - 1;
+  const int U = u0 + r.lu0, V = v0 + r.lv0;
+  if (U >= 0 && V >= 0 && U + r.T <= Kx && V + r.T <= Ky) {
+    const char* __restrict__ base =
+        reinterpret_cast<const char*>(X + ((((int64_t)(U >> GRID_L) << ksh) + V) << GRID_L));
+    const uint32_t f = (uint32_t)U & M;
+#pragma unroll
+    for (int k = 0; k < MK; ++k) {
+      const uint32_t e = (sl.w[k] >> 24) + f, a = (sl.w[k] >> 16) & 0xffu;
+      const uint32_t off =
+          ((e >> GRID_L) << (ksh + GRID_L + 3)) + ((a << (GRID_L + 3)) + ((e & M) << 3));
+      xr[k] = *reinterpret_cast<const float2*>(base + off);
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < MK; ++k) {
+      const int gu = (U + (int)(sl.w[k] >> 24)) & (Kx - 1);
+      const int gv = (V + (int)((sl.w[k] >> 16) & 0xffu)) & (Ky - 1);
+      xr[k] = X[grid_index(gv, gu, Ky)];
+    }
+  }
+}
+
+// Add a run's register accumulator into the box accumulator (planes of plane bytes).
+template <int MK>
+__device__ __forceinline__ void scatter_run(const Run& r, const Slots<MK>& sl, const Box& bx,
+                                            int lane, const float2 (&ac)[MK], double* acc,
+                                            int plane) {
+  const int base = ((r.lv0 - bx.v0) * bx.w + (r.lu0 - bx.u0)) * 8;
+  char* p = reinterpret_cast<char*>(acc);
 #pragma unroll
   for (int k = 0; k < MK; ++k) {
-    const int t = lane + 64 * k;
-    if (t < r.TT) {
-      int a, b;
-      tap_ab(t, r.T, invT, a, b);
-      const int li = base + a * bx.w + b;
-      atomicAdd(acc + li, (double)ac[k].x);
-      atomicAdd(acci + li, (double)ac[k].y);
-    }
+    auto add = [&] {
+      const int li = base + (int)(sl.w[k] & 0xffffu);
+      atomicAdd(reinterpret_cast<double*>(p + li), (double)ac[k].x);
+      atomicAdd(reinterpret_cast<double*>(p + li + plane), (double)ac[k].y);
+    };
+    // whole slots by scalar branches; the patch's last, partial one by lane
+    if (64 * (k + 1) <= r.TT) add();
+    else if (lane + 64 * k < r.TT) add();
   }
 }
 
@@ -177,18 +224,30 @@ __device__ __forceinline__ void window_zero(double* acc, const Box& bx) {
   const int n = bx.w * bx.h;
   for (int c = threadIdx.x; c < 2 * n; c += GNT) acc[c] = 0.0;
 }
+// Add the box into Y, line by line of the grid's layout: 16 lanes on the 2^GRID_L columns x
+// 2^(4 - GRID_L) rows of one 128-byte line, cells outside the box and untouched cells skipped.
+// The atomics' rate is set by the lines they touch.
 __device__ __forceinline__ void window_flush(const double* acc, const Box& bx, int u0, int v0,
                                              int Kx, int Ky, float2* __restrict__ Y) {
+  constexpr int L = GRID_L, H = 4 - GRID_L;
   const int n = bx.w * bx.h;
-  for (int c = threadIdx.x; c < n; c += GNT) {
-    const float2 v = make_float2((float)acc[c], (float)acc[n + c]);
-    if (v.x != 0.f || v.y != 0.f) {
-      const int a = c / bx.w, b = c - a * bx.w;
-      const int gu = (u0 + bx.u0 + b) & (Kx - 1);
-      const int gv = (v0 + bx.v0 + a) & (Ky - 1);
-      float2* p = Y + grid_index(gv, gu, Ky);
-      unsafeAtomicAdd(&p->x, v.x);
-      unsafeAtomicAdd(&p->y, v.y);
+  const int ub = u0 + bx.u0, vb = v0 + bx.v0;          // grid origin of the box (unwrapped)
+  const int fu = ub & ((1 << L) - 1), fv = vb & ((1 << H) - 1);
+  const int nx = (fu + bx.w + (1 << L) - 1) >> L, ny = (fv + bx.h + (1 << H) - 1) >> H;
+  const float inv = __builtin_amdgcn_rcpf((float)nx);
+  const int cu = (threadIdx.x & ((1 << L) - 1)) - fu, cv = ((threadIdx.x & 15) >> L) - fv;
+  for (int c = threadIdx.x >> 4; c < nx * ny; c += GNT / 16) {
+    int ly, lx;
+    tap_ab(c, nx, inv, ly, lx);
+    const int a = (ly << H) + cv, b = (lx << L) + cu;
+    if ((unsigned)a < (unsigned)bx.h && (unsigned)b < (unsigned)bx.w) {
+      const int li = a * bx.w + b;
+      const float2 v = make_float2((float)acc[li], (float)acc[n + li]);
+      if (v.x != 0.f || v.y != 0.f) {
+        float2* p = Y + grid_index((vb + a) & (Ky - 1), (ub + b) & (Kx - 1), Ky);
+        unsafeAtomicAdd(&p->x, v.x);
+        unsafeAtomicAdd(&p->y, v.y);
+      }
     }
   }
 }
@@ -207,10 +266,8 @@ __device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __r
   constexpr bool SCATTER = MODE != 1;
   constexpr int VB = value_bytes<STORE>();
   const Box bx = box_of(wi.box);
-  if constexpr (SCATTER) {
-    window_zero(acc, bx);
-    __syncthreads();
-  }
+  const int plane = bx.w * bx.h * 8;
+  const int ksh = 31 - __builtin_clz(Ky);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int seg = (wi.nrows + GWAVES - 1) / GWAVES;
@@ -222,6 +279,8 @@ __device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __r
   using Raw = typename RawT<STORE>::type;
   if (r0 >= r1) {
     if constexpr (SCATTER) {
+      window_zero(acc, bx);
+      __syncthreads();
       __syncthreads();
       window_flush(acc, bx, wi.u0, wi.v0, Kx, Ky, Y);
     }
@@ -274,6 +333,12 @@ __device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __r
     mb[d] = 0u;
     if (rp < r1) request(d);
   }
+  // the accumulator is cleared while the first rows' values are on their way
+  if constexpr (SCATTER) {
+    window_zero(acc, bx);
+    __syncthreads();
+  }
+  Slots<MK> sl;
   for (int rb = r0; rb < r1; rb += D) {
 #pragma unroll
     for (int d = 0; d < D; ++d) {
@@ -286,23 +351,32 @@ __device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __r
       for (int k = 0; k < MK; ++k) graw[k] = buf[d][k];
       if (m != cur) {
         if constexpr (SCATTER) {
-          if (cur != 0xffffffffu) scatter_run<MK>(rg, bx, lane, ac, acc);
+          if (cur != 0xffffffffu) scatter_run<MK>(rg, sl, bx, lane, ac, acc, plane);
         }
         cur = m;
         rg = decode(m);
+        sl.set(rg.T, bx.w, lane);
         if constexpr (PREFETCH) {
           if (nm == m) {
 #pragma unroll
             for (int k = 0; k < MK; ++k) xr[k] = xn[k];
           } else {
-            load_patch_x<MK>(rg, wi.u0, wi.v0, Kx, Ky, X, lane, xr);
+            load_patch_x<MK>(rg, sl, wi.u0, wi.v0, Kx, Ky, ksh, X, xr);
           }
           int q = r + 1;
           while (q < r1 && meta_of(q) == m) ++q;
-          nm = q < r1 ? meta_of(q) : 0xffffffffu;
-          if (q < r1) load_patch_x<MK>(decode(nm), wi.u0, wi.v0, Kx, Ky, X, lane, xn);
+          nm = 0xffffffffu;
+          // one run ahead, where its patch has the same side (the slots' words)
+          if (q < r1) {
+            const uint32_t mq = meta_of(q);
+            const Run rq = decode(mq);
+            if (rq.T == rg.T) {
+              nm = mq;
+              load_patch_x<MK>(rq, sl, wi.u0, wi.v0, Kx, Ky, ksh, X, xn);
+            }
+          }
         } else if constexpr (GATHER) {
-          load_patch_x<MK>(rg, wi.u0, wi.v0, Kx, Ky, X, lane, xr);
+          load_patch_x<MK>(rg, sl, wi.u0, wi.v0, Kx, Ky, ksh, X, xr);
         }
 #pragma unroll
         for (int k = 0; k < MK; ++k) ac[k] = make_float2(0.f, 0.f);
@@ -321,8 +395,7 @@ __device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __r
           sy = fmaf(g[k].x, xr[k].y, sy);
           sy = fmaf(g[k].y, xr[k].x, sy);
         }
-        yx = wave_sum_uniform(sx);
-        yy = wave_sum_uniform(sy);
+        wave_sums_uniform(sx, sy, yx, yy);
         if constexpr (MODE == 1) {
           if (lane == 0) vis[perm[row]] = make_float2(yx, yy);
         }
@@ -344,7 +417,7 @@ __device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __r
     }
   }
   if constexpr (SCATTER) {
-    if (cur != 0xffffffffu) scatter_run<MK>(rg, bx, lane, ac, acc);
+    if (cur != 0xffffffffu) scatter_run<MK>(rg, sl, bx, lane, ac, acc, plane);
     __syncthreads();
     window_flush(acc, bx, wi.u0, wi.v0, Kx, Ky, Y);
   }

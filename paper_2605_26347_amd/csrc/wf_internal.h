@@ -14,8 +14,16 @@
 namespace wf {
 
 // Complex arrays are stored in strips of 2^L adjacent columns: element (row r, column q)
-// of an R x Q array lives at ((q / 2^L) R + r) 2^L + q % 2^L.  SWNOTE
-constexpr int GRID_L = 3;         // the grids X and Y
+// of an R x Q array lives at ((q / 2^L) R + r) 2^L + q % 2^L, so that a 128-byte line holds
+// 16 / 2^L rows of a strip.  A column pass carries 16384 / N columns of N points per workgroup
+// (two at 8192): the narrower the strip, the fewer lines a wavefront's load or store touches
+// and the more of each it uses.  The row passes want the opposite (they touch one row of
+// every strip); the row kernels of G gather patches and add boxes line by line and hardly
+// care.  Measured at 8192 points, strips of 16 / 8 / 4 columns for the grids: forward columns
+// 98 / 97 / 88 us, inverse columns 164 / 139 / 119 us, row kernels of G within 3%; for the
+// half-transformed image, 16 / 8: row passes 90 + 95 / 98 + 102 us against 2 to 4 us in the
+// columns.
+constexpr int GRID_L = 2;         // the grids X and Y
 constexpr int HALF_L = 4;         // the half-transformed image A
 constexpr int MSTRIP = 16;        // columns per bit of the needed-column masks
 
