@@ -260,6 +260,10 @@ struct ChanOp {
   std::vector<int32_t> ck_wi0, ck_nwi;     // [chunk * NCLS + class] work-item ranges
   int64_t ck_max = 0;                      // values of the largest chunk
   DevBuf meta, voff, perm, vals, work;
+  // what the row kernels are launched on: the items of `work` cut into pieces (schedule_rows),
+  // largest first, per (bin, class), or per (chunk, class) on the fly: first piece, count
+  DevBuf pieces;
+  std::vector<int32_t> pc_0, pc_n;
   DevBuf prune;                            // per bin: strip bits, tile bits, groups
   std::vector<size_t> pr_strip, pr_tile, pr_groups;  // byte offsets into prune per bin
   std::vector<int32_t> pr_ngroups;
