@@ -6,14 +6,18 @@
 // (lane l supplies A[l % 32][l / 32] and B[l / 32][l % 32] of a 32 x 2 x 32 step;
 // accumulator element i of lane l is C[8 (i / 4) + 4 (l / 32) + i % 4][l % 32]).
 //
-// Inference: one workgroup of four wavefronts carries 64 rows through the whole network
+// Inference: one workgroup of eight wavefronts carries 64 rows through the whole network
 // with the activations in LDS as BF16.  The first layer (5 inputs) runs in FP32 so that
 // the inputs keep their precision; the hidden and output layers use
 // v_mfma_f32_32x32x16_bf16 (lane l supplies A[l % 32][8 (l / 32) .. + 7] and
-// B[8 (l / 32) .. + 7][l % 32]) with FP32 accumulation, weights read from a transposed
-// BF16 copy that stays resident in L2.  Plain BF16 operands leave a relative output error
-// near 1e-3; the split form (hi + lo BF16 parts, three products per step) brings it to
-// the FP32 level at three times the matrix-core work.
+// B[8 (l / 32) .. + 7][l % 32]) with FP32 accumulation, weights read from a BF16
+// copy in fragment order that stays resident in L2.  Plain BF16 operands leave a relative
+// output error near 1e-3; the split form (hi + lo BF16 parts, three products per step) brings
+// it to the FP32 level at three times the matrix-core work.
+// 200,000 rows, split: matrix cores 156 us, VALU (GELU, splits) 150 us, LDS reads 104 us and
+// the output's stores 53 us, which two workgroups per compute unit overlap in part: 451 us.
+// Before, 679 us: four wavefronts with two column tiles each (two waves per SIMD), weights by
+// columns (a fragment touched 32 lines), activations split and stored value by value.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -28,6 +32,8 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float gelu(float z) {
   return 0.5f * z * (1.0f + erff(z * 0.7071067811865475f));
@@ -268,18 +274,21 @@ __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float(
 
 constexpr int64_t WT_HALF = 3LL * MLP_HID * MLP_HID + 512LL * MLP_HID;
 
-// Transposed BF16 copies of the hidden and output weights: layer l = 1..4 goes to
-// wt + (l - 1) * 256 * 256 as [n][k] (the output layer padded to 512 rows of zeros); the
-// second half holds the residuals w - bf16(w), also in BF16 (the low parts of the split
-// operands).
+// BF16 copies of the hidden and output weights in the order in which the inference's
+// wavefronts read them: layer l = 1..4 starts at (l - 1) * 256 * 256 (the output layer padded
+// to 512 columns of zeros); per column tile of 32 and step of 16 along k, the 64 lanes' eight
+// values each (lane: column n % 32, k half (k % 16) / 8), so that a fragment is one contiguous
+// kilobyte.  The second half holds the residuals w - bf16(w), also in BF16 (the low parts of
+// the split operands).
 __global__ __launch_bounds__(256) void k_prep_bf16(const float* __restrict__ params,
                                                    uint16_t* __restrict__ wt) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < WT_HALF;
        i += (int64_t)gridDim.x * blockDim.x) {
     const int l = i < 3LL * MLP_HID * MLP_HID ? 1 + (int)(i / (MLP_HID * MLP_HID)) : 4;
     const int64_t base = (int64_t)(l - 1) * MLP_HID * MLP_HID;
-    const int64_t j = i - base;
-    const int n = (int)(j / MLP_HID), k = (int)(j - (int64_t)n * MLP_HID);
+    const int j = (int)(i - base);
+    const int lane = (j >> 3) & 63, step = (j >> 9) & 15, tile = j >> 13;
+    const int n = tile * 32 + (lane & 31), k = step * 16 + 8 * (lane >> 5) + (j & 7);
     const int fo = mlp_fan_out(l);
     const float w = n < fo ? params[mlp_w_offset(l) + (int64_t)k * fo + n] : 0.f;
     const uint16_t hi = to_bf16(w);
@@ -288,7 +297,20 @@ __global__ __launch_bounds__(256) void k_prep_bf16(const float* __restrict__ par
   }
 }
 
+// Two FP32 values as a pair of BF16 (round to nearest even) and the pair of their residuals.
+__device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& lo) {
+  auto pack = [](float x, float y) {
+    const bf16x2 h = __builtin_convertvector((f32x2){x, y}, bf16x2);
+    uint32_t r;
+    __builtin_memcpy(&r, &h, 4);
+    return r;
+  };
+  hi = pack(a, b);
+  lo = pack(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
+}
+
 constexpr int IR = 64;               // rows per inference workgroup
+constexpr int IW = 8;                // its wavefronts, one column tile of 32 each
 constexpr int HS = MLP_HID + 8;      // LDS row stride (bf16 elements)
 
 // SPLIT: every operand is carried as a high BF16 part and a BF16 residual, and each
@@ -310,7 +332,7 @@ __device__ __forceinline__ float gelu_infer(float z) {
 }
 
 template <bool SPLIT>
-__global__ __launch_bounds__(256, 2) void k_infer_bf16(const float* __restrict__ x, int64_t n,
+__global__ __launch_bounds__(64 * IW, 4) void k_infer_bf16(const float* __restrict__ x, int64_t n,
                                                     const float* __restrict__ params,
                                                     const uint16_t* __restrict__ wt,
                                                     float* __restrict__ out) {
@@ -318,125 +340,131 @@ __global__ __launch_bounds__(256, 2) void k_infer_bf16(const float* __restrict__
   uint16_t* Hl = H + IR * HS;
   const int64_t r0 = (int64_t)blockIdx.x * IR;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  auto put = [&](int row, int col, float v) {
-    const uint16_t hi = to_bf16(v);
-    H[row * HS + col] = hi;
-    if (SPLIT) Hl[row * HS + col] = to_bf16(v - from_bf16(hi));
-  };
-  // layer 0 in FP32: thread tid owns hidden unit tid; the tile's inputs are staged in
-  // LDS once (rows past n read as zero and are never written out)
+  // layer 0 in FP32: a thread owns two adjacent hidden units for a share of the rows; the
+  // tile's inputs are staged in LDS once (rows past n read as zero and are never written out)
   {
     __shared__ float xs[IR * MLP_IN];
-    for (int i = tid; i < IR * MLP_IN; i += 256) {
+    for (int i = tid; i < IR * MLP_IN; i += 64 * IW) {
       const int64_t row = r0 + i / MLP_IN;
       xs[i] = row < n ? x[r0 * MLP_IN + i] : 0.f;
     }
-    float w[MLP_IN];
+    const int u = 2 * (tid & 127);
+    float2 w[MLP_IN];
 #pragma unroll
-    for (int i = 0; i < MLP_IN; ++i) w[i] = params[(int64_t)i * MLP_HID + tid];
-    const float b0 = params[mlp_b_offset(0) + tid];
+    for (int i = 0; i < MLP_IN; ++i)
+      w[i] = make_float2(params[(int64_t)i * MLP_HID + u], params[(int64_t)i * MLP_HID + u + 1]);
+    const float b0 = params[mlp_b_offset(0) + u], b1 = params[mlp_b_offset(0) + u + 1];
     __syncthreads();
+    constexpr int RS = IR / (IW / 2);   // rows of a thread
+    const int ra = (tid >> 7) * RS;
 #pragma unroll 4
-    for (int r = 0; r < IR; ++r) {
-      float z = b0;
+    for (int r = ra; r < ra + RS; ++r) {
+      float z0 = b0, z1 = b1;
 #pragma unroll
-      for (int i = 0; i < MLP_IN; ++i) z += xs[r * MLP_IN + i] * w[i];
-      put(r, tid, gelu_infer(z));
+      for (int i = 0; i < MLP_IN; ++i) {
+        z0 += xs[r * MLP_IN + i] * w[i].x;
+        z1 += xs[r * MLP_IN + i] * w[i].y;
+      }
+      uint32_t hi, lo;
+      split2(gelu_infer(z0), gelu_infer(z1), hi, lo);
+      *reinterpret_cast<uint32_t*>(&H[r * HS + u]) = hi;
+      if (SPLIT) *reinterpret_cast<uint32_t*>(&Hl[r * HS + u]) = lo;
     }
   }
   __syncthreads();
   const int am = lane & 31, ak = 8 * (lane >> 5);
-  // layers 1..4: wave wv computes NB column tiles starting at column wv * 32 * NB
-  auto layer = [&](const uint16_t* W, int col0, auto nbt,
-                   f32x16 (&acc)[2][decltype(nbt)::value]) {
-    constexpr int NB = decltype(nbt)::value;
+  // layers 1..4: a wavefront computes column tile t0 (32 columns) of all 64 rows:
+  // acc[row half].  FEAT: the products are formed as weights^T times activations^T, so that
+  // a lane holds one row and groups of four adjacent columns (packed stores of the next
+  // layer's input); otherwise a lane holds one column (whole lines of the output).
+  auto layer = [&](const uint16_t* W, int t0, auto feat, f32x16 (&acc)[2]) {
+    constexpr bool FEAT = decltype(feat)::value;
+    constexpr int STEPS = MLP_HID / 16;
+    const uint16_t* __restrict__ w0 = W + t0 * STEPS * 64 * 8 + lane * 8;
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-      for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-    // the weights (L2-resident) of step k0 + 16 are requested before the products of
-    // step k0, so that their latency hides behind the matrix-core work
-    bf16x8 fb[NB], lb[NB];
-    auto load_b = [&](int k0, bf16x8 (&b0)[NB], bf16x8 (&b1)[NB]) {
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const int64_t o = (int64_t)(col0 + wv * 32 * NB + b * 32 + am) * MLP_HID + k0 + ak;
-        b0[b] = *reinterpret_cast<const bf16x8*>(&W[o]);
-        if (SPLIT) b1[b] = *reinterpret_cast<const bf16x8*>(&W[WT_HALF + o]);
-      }
+      for (int i = 0; i < 16; ++i) acc[a][i] = 0.f;
+    auto mm = [&](bf16x8 act, bf16x8 w, f32x16 c) {
+      return FEAT ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, act, c, 0, 0, 0)
+                  : __builtin_amdgcn_mfma_f32_32x32x16_bf16(act, w, c, 0, 0, 0);
     };
-    load_b(0, fb, lb);
-#pragma unroll 2
-    for (int k0 = 0; k0 < MLP_HID; k0 += 16) {
-      bf16x8 fa[2], la[2], nfb[NB], nlb[NB];
-      if (k0 + 16 < MLP_HID) load_b(k0 + 16, nfb, nlb);
+    // the weights (L2-resident) of step st + WD are requested before the products of step
+    // st, so that their latency hides behind the matrix-core work
+    constexpr int WD = 2;
+    bf16x8 wh[WD + 1], wl[WD + 1];
+    auto load_w = [&](int st, int slot) {
+      wh[slot] = *reinterpret_cast<const bf16x8*>(w0 + st * 64 * 8);
+      if (SPLIT) wl[slot] = *reinterpret_cast<const bf16x8*>(w0 + st * 64 * 8 + WT_HALF);
+    };
+#pragma unroll
+    for (int d = 0; d < WD; ++d) load_w(d, d);
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+      if (st + WD < STEPS) load_w(st + WD, (st + WD) % (WD + 1));
+      const int d = st % (WD + 1);
+      bf16x8 fa[2], la[2];
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
-        const int o = (a * 32 + am) * HS + k0 + ak;
+        const int o = (a * 32 + am) * HS + st * 16 + ak;
         fa[a] = *reinterpret_cast<const bf16x8*>(&H[o]);
         if (SPLIT) la[a] = *reinterpret_cast<const bf16x8*>(&Hl[o]);
       }
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
-          if (SPLIT) {
-            acc[a][b] =
-                __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], lb[b], acc[a][b], 0, 0, 0);
-            acc[a][b] =
-                __builtin_amdgcn_mfma_f32_32x32x16_bf16(la[a], fb[b], acc[a][b], 0, 0, 0);
-          }
-        }
-      if (k0 + 16 < MLP_HID) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          fb[b] = nfb[b];
-          if (SPLIT) lb[b] = nlb[b];
+      for (int a = 0; a < 2; ++a) {
+        acc[a] = mm(fa[a], wh[d], acc[a]);
+        if (SPLIT) {
+          acc[a] = mm(fa[a], wl[d], acc[a]);
+          acc[a] = mm(la[a], wh[d], acc[a]);
         }
       }
     }
   };
   for (int l = 1; l < MLP_LAYERS; ++l) {
-    f32x16 acc[2][2];
-    layer(wt + (int64_t)(l - 1) * MLP_HID * MLP_HID, 0, std::integral_constant<int, 2>{}, acc);
+    f32x16 acc[2];
+    layer(wt + (int64_t)(l - 1) * MLP_HID * MLP_HID, wv, std::true_type{}, acc);
     __syncthreads();
     const float* bias = params + mlp_b_offset(l);
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int col = wv * 64 + b * 32 + am;
-      const float bb = bias[col];
+    for (int g = 0; g < 4; ++g) {
+      // accumulator elements 4 g .. 4 g + 3 of a lane: adjacent columns of its row
+      const int col = wv * 32 + 8 * g + 4 * (lane >> 5);
+      float bb[4];
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int i = 0; i < 4; ++i) bb[i] = bias[col + i];
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-          put(a * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3), col,
-              gelu_infer(acc[a][b][i] + bb));
+      for (int a = 0; a < 2; ++a) {
+        uint2 hi, lo;
+        split2(gelu_infer(acc[a][4 * g] + bb[0]), gelu_infer(acc[a][4 * g + 1] + bb[1]), hi.x,
+               lo.x);
+        split2(gelu_infer(acc[a][4 * g + 2] + bb[2]), gelu_infer(acc[a][4 * g + 3] + bb[3]),
+               hi.y, lo.y);
+        const int o = (a * 32 + am) * HS + col;
+        *reinterpret_cast<uint2*>(&H[o]) = hi;
+        if (SPLIT) *reinterpret_cast<uint2*>(&Hl[o]) = lo;
+      }
     }
     __syncthreads();
   }
-  // output layer in two halves of 256 columns (451 real): in half h, wave wv computes
-  // columns [256 h + 64 wv, 256 h + 64 wv + 64), so that the accumulators of one half
-  // (64 registers) leave room for two waves per SIMD
+  // output layer in two halves of 256 columns (451 real), a tile of 32 per wavefront each
   const float* bias = params + mlp_b_offset(MLP_LAYERS);
+  const bool whole = r0 + IR <= n;
   for (int h = 0; h < 2; ++h) {
-    f32x16 acc[2][2];
-    layer(wt + 3LL * MLP_HID * MLP_HID, 256 * h, std::integral_constant<int, 2>{}, acc);
+    const int col = 256 * h + wv * 32 + am;
+    if (256 * h + wv * 32 >= MLP_OUT) continue;
+    f32x16 acc[2];
+    layer(wt + 3LL * MLP_HID * MLP_HID, 8 * h + wv, std::false_type{}, acc);
+    if (col >= MLP_OUT) continue;
+    const float bb = bias[col];
+    float* __restrict__ po = out + (r0 + 4 * (lane >> 5)) * MLP_OUT + col;
+    const int left = (int)min((int64_t)IR, n - r0) - 4 * (lane >> 5);
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int col = 256 * h + wv * 64 + b * 32 + am;
-      if (col >= MLP_OUT) continue;
-      const float bb = bias[col];
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int64_t row = r0 + a * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-          if (row < n) out[row * MLP_OUT + col] = acc[a][b][i] + bb;
-        }
-    }
+      for (int i = 0; i < 16; ++i) {
+        const int r = a * 32 + 8 * (i >> 2) + (i & 3);
+        if (whole || r < left) po[r * MLP_OUT] = acc[a][i] + bb;
+      }
   }
 }
 
@@ -516,10 +544,10 @@ hipError_t launch_mlp_infer_bf16(const float* x, int64_t n, const float* params,
   if (n <= 0) return hipSuccess;
   const int64_t nb = (n + IR - 1) / IR;
   if (split)
-    hipLaunchKernelGGL(k_infer_bf16<true>, dim3((unsigned)nb), dim3(256), 0, s, x, n, params, wt,
+    hipLaunchKernelGGL(k_infer_bf16<true>, dim3((unsigned)nb), dim3(64 * IW), 0, s, x, n, params, wt,
                        out);
   else
-    hipLaunchKernelGGL(k_infer_bf16<false>, dim3((unsigned)nb), dim3(256), 0, s, x, n, params,
+    hipLaunchKernelGGL(k_infer_bf16<false>, dim3((unsigned)nb), dim3(64 * IW), 0, s, x, n, params,
                        wt, out);
   return hipGetLastError();
 }

@@ -376,7 +376,7 @@ struct wf_op {
 };
 
 // Residual-kernel network: FP32 parameters with Adam state, per-batch activations, and
-// the transposed BF16 weights of the inference kernel (refreshed when the parameters
+// the BF16 weights of the inference kernel in fragment order (refreshed when the parameters
 // change).
 struct wf_mlp {
   int device = 0;

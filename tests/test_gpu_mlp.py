@@ -267,3 +267,19 @@ def test_loss_grad_batch_edges(params, B):
         for n in (a * b, b):
             assert rel(g[o:o + n], go[o:o + n]) <= 1e-4, (B, a, b, n)
             o += n
+
+
+@pytest.mark.parametrize("n", [1, 31, 64, 65, 191])
+def test_inference_row_tiles(params, n):
+    """Inference around its tiles of 64 rows, against the FP64 forward pass (as above: 2e-2
+    plain BF16, 2e-5 split), rows past n left alone."""
+    net = _net()(seed=1)
+    net.set_params(params.astype(np.float32))
+    w, L, fu, fv = _examples(n + 3, 20 + n)
+    xo = omlp.features(w, L, fu, fv)[0].astype(np.float32)[3:]
+    ref, _ = omlp.forward(params.astype(np.float32).astype(np.float64), xo.astype(np.float64))
+    for form, tol in ((1, 2e-2), (2, 2e-5)):
+        buf = torch.full((n + 70, 451), 7.0, device="cuda:0")
+        net.infer(to_dev(xo), bf16=form, out=buf[:n])
+        assert rel(buf[:n].cpu().numpy(), ref) <= tol
+        assert bool((buf[n:] == 7.0).all())
