@@ -224,9 +224,11 @@ __device__ __forceinline__ void window_zero(double* acc, const Box& bx) {
   const int n = bx.w * bx.h;
   for (int c = threadIdx.x; c < 2 * n; c += GNT) acc[c] = 0.0;
 }
-// Add the box into Y, line by line of the grid's layout: 16 lanes on the 2^GRID_L columns x
-// 2^(4 - GRID_L) rows of one 128-byte line, cells outside the box and untouched cells skipped.
-// The atomics' rate is set by the lines they touch.
+// Add the box into Y, line by line of the grid's layout: 32 lanes on the 32 floats of one
+// 128-byte line (2^GRID_L columns x 2^(4 - GRID_L) rows of complex cells), floats outside the
+// box and untouched ones skipped.  An atomic costs by the 64-byte segments that it touches, so
+// a line is sent whole: real parts and imaginary parts in instructions of their own touched
+// every segment twice.
 __device__ __forceinline__ void window_flush(const double* acc, const Box& bx, int u0, int v0,
                                              int Kx, int Ky, float2* __restrict__ Y) {
   constexpr int L = GRID_L, H = 4 - GRID_L;
@@ -235,19 +237,18 @@ __device__ __forceinline__ void window_flush(const double* acc, const Box& bx, i
   const int fu = ub & ((1 << L) - 1), fv = vb & ((1 << H) - 1);
   const int nx = (fu + bx.w + (1 << L) - 1) >> L, ny = (fv + bx.h + (1 << H) - 1) >> H;
   const float inv = __builtin_amdgcn_rcpf((float)nx);
-  const int cu = (threadIdx.x & ((1 << L) - 1)) - fu, cv = ((threadIdx.x & 15) >> L) - fv;
-  for (int c = threadIdx.x >> 4; c < nx * ny; c += GNT / 16) {
+  const int part = threadIdx.x & 1, cell = (threadIdx.x >> 1) & 15;
+  const int cu = (cell & ((1 << L) - 1)) - fu, cv = (cell >> L) - fv;
+  const double* __restrict__ plane = acc + part * n;
+  float* __restrict__ Yp = reinterpret_cast<float*>(Y) + part;
+  for (int c = threadIdx.x >> 5; c < nx * ny; c += GNT / 32) {
     int ly, lx;
     tap_ab(c, nx, inv, ly, lx);
     const int a = (ly << H) + cv, b = (lx << L) + cu;
     if ((unsigned)a < (unsigned)bx.h && (unsigned)b < (unsigned)bx.w) {
-      const int li = a * bx.w + b;
-      const float2 v = make_float2((float)acc[li], (float)acc[n + li]);
-      if (v.x != 0.f || v.y != 0.f) {
-        float2* p = Y + grid_index((vb + a) & (Ky - 1), (ub + b) & (Kx - 1), Ky);
-        unsafeAtomicAdd(&p->x, v.x);
-        unsafeAtomicAdd(&p->y, v.y);
-      }
+      const float v = (float)plane[a * bx.w + b];
+      if (v != 0.f)
+        unsafeAtomicAdd(Yp + 2 * grid_index((vb + a) & (Ky - 1), (ub + b) & (Kx - 1), Ky), v);
     }
   }
 }
