@@ -13,7 +13,7 @@
 // falling in one grid cell).  Per run
 //   * the grid values X of the run's patch are gathered once,
 //   * conj(g_k) y_k is accumulated in registers over the run and added into the LDS
-//     window of the tile (plus halo) once,
+//     window of the tile (plus halo) once (wide patches: row by row),
 // and the stored values of G are streamed from HBM exactly once.  A row's sum
 // y_k = sum_t g_k[t] X[t] is reduced across the wavefront by a half swap and DPP, which
 // leaves y_k wave-uniform.  At the end the
@@ -24,12 +24,13 @@
 // Values are stored as complex FP32, FP16 or BF16; all arithmetic is FP32.
 //
 // Bound by instruction issue and latency, not by the G stream: dense rows (4096^2, 30M rows,
-// FP16 fused) read G at 3.1 TB/s with the VALUs half busy, sparse rows (2048^2, 10 rows per
-// item) at 0.6 TB/s, where an item's chain of loads and its accumulator's clearing and
+// FP16 fused) read G at 3.6 TB/s with the VALUs half busy, sparse rows (2048^2, 10 rows per
+// item) at 0.9 TB/s, where an item's chain of loads and its accumulator's clearing and
 // flushing are most of its time.  So a run's addresses are words formed once per patch side
 // plus scalars, both sums of a row share one reduction, the accumulator is cleared behind the
-// first loads, and the flush goes by grid lines.  Per w-layer, fused: 452 -> 421 us (dense),
-// 326 -> 297 us (sparse, channels of 1 to 3M rows).
+// first loads, the flush goes by grid lines, and each class is held to the registers that let
+// two or three workgroups share a compute unit (row_form).  Per w-layer, fused: 452 -> 365 us
+// (dense), 326 -> 205 us (sparse, channels of 1 to 3M rows).
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
@@ -200,19 +201,19 @@ __device__ __forceinline__ void load_patch_x(const Run& r, const Slots<MK>& sl, 
   }
 }
 
-// Add a run's register accumulator into the box accumulator (planes of plane bytes).
-template <int MK>
-__device__ __forceinline__ void scatter_run(const Run& r, const Slots<MK>& sl, const Box& bx,
-                                            int lane, const float2 (&ac)[MK], double* acc,
-                                            int plane) {
+// Add a patch of values (value(k): slot k's) into the box accumulator (planes of plane bytes).
+template <int MK, typename V>
+__device__ __forceinline__ void scatter_patch(const Run& r, const Slots<MK>& sl, const Box& bx,
+                                              int lane, V&& value, double* acc, int plane) {
   const int base = ((r.lv0 - bx.v0) * bx.w + (r.lu0 - bx.u0)) * 8;
   char* p = reinterpret_cast<char*>(acc);
 #pragma unroll
   for (int k = 0; k < MK; ++k) {
     auto add = [&] {
       const int li = base + (int)(sl.w[k] & 0xffffu);
-      atomicAdd(reinterpret_cast<double*>(p + li), (double)ac[k].x);
-      atomicAdd(reinterpret_cast<double*>(p + li + plane), (double)ac[k].y);
+      const float2 v = value(k);
+      atomicAdd(reinterpret_cast<double*>(p + li), (double)v.x);
+      atomicAdd(reinterpret_cast<double*>(p + li + plane), (double)v.y);
     };
     // whole slots by scalar branches; the patch's last, partial one by lane
     if (64 * (k + 1) <= r.TT) add();
@@ -251,6 +252,36 @@ __device__ __forceinline__ void window_flush(const double* acc, const Box& bx, i
         unsafeAtomicAdd(Yp + 2 * grid_index((vb + a) & (Ky - 1), (ub + b) & (Kx - 1), Ky), v);
     }
   }
+}
+
+// How a row kernel is held to the registers that let its workgroups (two wavefronts per SIMD
+// each) share a compute unit: at most 80 registers for three, 128 for two, 256 for one.  A
+// sparse row is a chain of loads, sums and LDS atomics that only other wavefronts hide.
+//   direct: a row's products go straight into the box accumulator instead of a run
+//           accumulator in registers (2 MK of them), and its buffer is loaded again only once
+//           they have, which saves a copy of it (MK to 2 MK).
+//   depth:  rows of values in flight.
+//   waves:  wavefronts per SIMD that the compiler has to allow; 2 leaves it its choice.
+// Each form is the one with the most workgroups that needs no scratch memory (one that does
+// runs two to three times slower), and among those the faster.  Fused, FP16, us per launch
+// (2048^2 with four channels of 1 to 3M rows; 4096^2 with 30M rows), before with one workgroup
+// (a run accumulator, the next run's grid values a run ahead) and now: MK 7 43 -> 38 and
+// 94 -> 86, MK 12 69 -> 47 and 108 -> 76, MK 16 49 -> 33 and 72 -> 57, MK 22 120 -> 77 and
+// 120 -> 96.  MK 12 keeps its run accumulator in FP16, where it fits: without it 83 for 76.
+// Fused MK 22 of FP32 and BF16 needs 164 registers.  De-gridding MK 22 in FP32 fits 128 by its
+// late loads, which cost more than the second workgroup gives (37 us for 33).
+struct RowForm {
+  bool direct;
+  int depth, waves;
+};
+constexpr RowForm row_form(int store, int mk, int mode) {
+  const bool f16 = store == WF_STORE_F16, f32 = store == WF_STORE_F32;
+  if (mk <= 4) return {false, 4, 2};
+  if (mk == 7) return {false, 2, f16 || (!f32 && mode != 0) ? 6 : 4};
+  if (mk == 12) return {!f16, 2, 4};
+  if (mk == 16) return {true, 1, 4};
+  if (mode == 1 && f32) return {false, 1, 2};
+  return {true, 1, f16 || mode == 2 ? 4 : 2};
 }
 
 // One work item on one workgroup.  MODE 0: fused G^dag G; 1: de-gridding; 2: gridding.
@@ -293,10 +324,11 @@ __device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __r
   // the LDS/scalar counter that the window atomics use.  Value offsets are the running
   // sum of T^2 inside the item; the values of row r + D are requested (after a new run's
   // grid values) before row r is reduced.
-  constexpr int D = MK <= 4 ? 4 : (MK <= 16 || STORE != WF_STORE_F32 ? 2 : 1);
+  constexpr RowForm F = row_form(STORE, MK, MODE);
+  constexpr int D = F.depth;
   // the next run's grid values are gathered while the current run is reduced (one run
-  // ahead), where registers allow
-  constexpr bool PREFETCH = GATHER && (MK <= 12 || (MK <= 16 && STORE != WF_STORE_F32));
+  // ahead), where that costs no workgroup its registers
+  constexpr bool PREFETCH = GATHER && MK <= 4;
   const int nseg = r1 - r0;
   const uint32_t* __restrict__ mrow = meta + wi.row0 + r0;
   const uint32_t mv0 = mrow[min(lane, nseg - 1)];
@@ -347,12 +379,15 @@ __device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __r
       if (r >= r1) break;
       const int row = wi.row0 + r;
       const uint32_t m = mb[d];
-      Raw graw[MK];
+      Raw graw[F.direct ? 1 : MK];
+      if constexpr (!F.direct) {
 #pragma unroll
-      for (int k = 0; k < MK; ++k) graw[k] = buf[d][k];
+        for (int k = 0; k < MK; ++k) graw[k] = buf[d][k];
+      }
       if (m != cur) {
         if constexpr (SCATTER) {
-          if (cur != 0xffffffffu) scatter_run<MK>(rg, sl, bx, lane, ac, acc, plane);
+          if (!F.direct && cur != 0xffffffffu)
+            scatter_patch<MK>(rg, sl, bx, lane, [&](int k) { return ac[k]; }, acc, plane);
         }
         cur = m;
         rg = decode(m);
@@ -382,10 +417,12 @@ __device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __r
 #pragma unroll
         for (int k = 0; k < MK; ++k) ac[k] = make_float2(0.f, 0.f);
       }
-      if (rp < r1) request(d);   // row r + D (in-bounds: past a row's taps reads zero)
+      // row r + D (in-bounds: past a row's taps reads zero)
+      if (!F.direct && rp < r1) request(d);
       float2 g[MK];
 #pragma unroll
-      for (int k = 0; k < MK; ++k) g[k] = widen<STORE>(graw[k]);
+      for (int k = 0; k < MK; ++k)
+        g[k] = widen<STORE>(F.direct ? buf[d][k] : graw[F.direct ? 0 : k]);
       float yx, yy;
       if constexpr (GATHER) {
         float sx = 0.f, sy = 0.f;
@@ -406,7 +443,11 @@ __device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __r
         yx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(yv.x), i & 63));
         yy = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(yv.y), i & 63));
       }
-      if constexpr (SCATTER) {
+      if constexpr (SCATTER && F.direct) {
+        scatter_patch<MK>(rg, sl, bx, lane, [&](int k) {  // conj(g) y
+          return make_float2(fmaf(g[k].y, yy, g[k].x * yx), fmaf(-g[k].y, yx, g[k].x * yy));
+        }, acc, plane);
+      } else if constexpr (SCATTER) {
 #pragma unroll
         for (int k = 0; k < MK; ++k) {  // += conj(g) y
           ac[k].x = fmaf(g[k].x, yx, ac[k].x);
@@ -415,17 +456,20 @@ __device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __r
           ac[k].y = fmaf(-g[k].y, yx, ac[k].y);
         }
       }
+      if (F.direct && rp < r1) request(d);
     }
   }
   if constexpr (SCATTER) {
-    if (cur != 0xffffffffu) scatter_run<MK>(rg, sl, bx, lane, ac, acc, plane);
+    if (!F.direct && cur != 0xffffffffu)
+      scatter_patch<MK>(rg, sl, bx, lane, [&](int k) { return ac[k]; }, acc, plane);
     __syncthreads();
     window_flush(acc, bx, wi.u0, wi.v0, Kx, Ky, Y);
   }
 }
 
 template <int STORE, int MK, int MODE>
-__global__ __launch_bounds__(GNT) void k_rows(const WorkItem* __restrict__ wis,
+__global__ __launch_bounds__(GNT)
+__attribute__((amdgpu_waves_per_eu(row_form(STORE, MK, MODE).waves))) void k_rows(const WorkItem* __restrict__ wis,
                                               const uint32_t* __restrict__ meta,
                                               const uint32_t* __restrict__ voff,
                                               const int32_t* __restrict__ perm,
