@@ -255,13 +255,13 @@ __device__ __forceinline__ void window_flush(const double* acc, const Box& bx, i
 }
 
 // How a row kernel is held to the registers that let its workgroups (two wavefronts per SIMD
-// each) share a compute unit: at most 80 registers for three, 128 for two, 256 for one.  A
+// each) share a compute unit: 64 registers for four, 80 for three, 128 for two, 256 for one.  A
 // sparse row is a chain of loads, sums and LDS atomics that only other wavefronts hide.
 //   direct: a row's products go straight into the box accumulator instead of a run
 //           accumulator in registers (2 MK of them), and its buffer is loaded again only once
 //           they have, which saves a copy of it (MK to 2 MK).
 //   depth:  rows of values in flight.
-//   waves:  wavefronts per SIMD that the compiler has to allow; 2 leaves it its choice.
+//   waves:  wavefronts per SIMD that the compiler has to allow.
 // Each form is the one with the most workgroups that needs no scratch memory (one that does
 // runs two to three times slower), and among those the faster.  Fused, FP16, us per launch
 // (2048^2 with four channels of 1 to 3M rows; 4096^2 with 30M rows), before with one workgroup
@@ -276,8 +276,9 @@ struct RowForm {
 };
 constexpr RowForm row_form(int store, int mk, int mode) {
   const bool f16 = store == WF_STORE_F16, f32 = store == WF_STORE_F32;
-  if (mk <= 4) return {false, 4, 2};
-  if (mk == 7) return {false, 2, f16 || (!f32 && mode != 0) ? 6 : 4};
+  const bool thin = f16 || (!f32 && mode != 0);   // the classes below fit one workgroup more
+  if (mk <= 4) return {false, 4, f32 && mode == 0 ? 4 : !f32 && thin && mode != 2 ? 8 : 6};
+  if (mk == 7) return {false, 2, thin ? 6 : 4};
   if (mk == 12) return {!f16, 2, 4};
   if (mk == 16) return {true, 1, 4};
   if (mode == 1 && f32) return {false, 1, 2};
@@ -467,20 +468,52 @@ __device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __r
   }
 }
 
-template <int STORE, int MK, int MODE>
+// The classes that share a launch, from c0 on: those held to the same registers, except where
+// four workgroups share a compute unit (4096^2 psf 16.21 -> 16.37 ms with those two merged).
+constexpr int group_end(int store, int mode, int c0) {
+  const int w = row_form(store, class_mk(c0), mode).waves;
+  int c = c0 + 1;
+  while (w < 8 && c < NCLS && row_form(store, class_mk(c), mode).waves == w) ++c;
+  return c;
+}
+
+// One launch over the pieces of the classes [C0, C1), the widest patches first: the workgroups
+// of one class run beside the last ones of another instead of behind them.  Classes of fewer
+// registers stay apart, where they would lose workgroups (all of them at 128: 4096^2 psf
+// 16.1 -> 17.5 ms).  Measured against a launch per class: 512^2 iteration (FP32, 460 pieces in
+// all) 172 -> 142 us, 1024^2 adjoint 940 -> 881 us, 2048^2 wideband 16.82 -> 16.66 ms.
+template <int STORE, int MODE, int C0, int C1>
+__device__ __forceinline__ void row_block(int b, const RowPieces& pc,
+                                          const uint32_t* __restrict__ meta,
+                                          const uint32_t* __restrict__ voff,
+                                          const int32_t* __restrict__ perm,
+                                          const void* __restrict__ vals,
+                                          const float2* __restrict__ X, float2* __restrict__ Y,
+                                          float2* __restrict__ vis, int Kx, int Ky,
+                                          double* acc) {
+  if constexpr (C1 > C0) {
+    constexpr int C = C1 - 1;
+    if (b < pc.n[C])
+      row_item<STORE, class_mk(C), MODE>(pc.items[pc.first[C] + b], meta, voff, perm, vals, X,
+                                         Y, vis, Kx, Ky, acc);
+    else
+      row_block<STORE, MODE, C0, C>(b - pc.n[C], pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky,
+                                    acc);
+  }
+}
+
+template <int STORE, int MODE, int C0, int C1>
 __global__ __launch_bounds__(GNT)
-__attribute__((amdgpu_waves_per_eu(row_form(STORE, MK, MODE).waves))) void k_rows(const WorkItem* __restrict__ wis,
-                                              const uint32_t* __restrict__ meta,
-                                              const uint32_t* __restrict__ voff,
-                                              const int32_t* __restrict__ perm,
-                                              const void* __restrict__ vals,
-                                              const float2* __restrict__ X,
-                                              float2* __restrict__ Y,
-                                              float2* __restrict__ vis, int Kx, int Ky) {
+__attribute__((amdgpu_waves_per_eu(row_form(STORE, class_mk(C0), MODE).waves))) void k_rows(
+    RowPieces pc, const uint32_t* __restrict__ meta, const uint32_t* __restrict__ voff,
+    const int32_t* __restrict__ perm, const void* __restrict__ vals,
+    const float2* __restrict__ X, float2* __restrict__ Y, float2* __restrict__ vis, int Kx,
+    int Ky) {
   extern __shared__ double acc[];
-  // Items are ordered largest first and dealt round-robin over the XCDs by the hardware,
-  // which spreads the dense uv core (many items) evenly and schedules longest first.
-  row_item<STORE, MK, MODE>(wis[blockIdx.x], meta, voff, perm, vals, X, Y, vis, Kx, Ky, acc);
+  // A class's pieces are ordered largest first and dealt round-robin over the XCDs by the
+  // hardware, which spreads the dense uv core (many items) evenly and schedules longest first.
+  row_block<STORE, MODE, C0, C1>(blockIdx.x, pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky,
+                                 acc);
 }
 
 // Persistent form over the items of every layer of a sweep (one patch class): resident
@@ -533,56 +566,54 @@ constexpr int class_tmax(int mk) {
   return t;
 }
 
-template <int STORE, int MK, int MODE>
-static hipError_t launch_one(const WorkItem* wi, int nwi, const uint32_t* meta,
-                             const uint32_t* voff, const int32_t* perm, const void* vals,
-                             const float2* X, float2* Y, float2* vis, int Kx, int Ky, int tile,
-                             hipStream_t s) {
-  // the box accumulator of an item: rows' cells lie in one tile and their patches of
-  // side <= class_tmax reach tile + side - 1 cells per axis; two FP64 planes
-  const size_t side = (size_t)tile + class_tmax(MK) - 1;
-  const size_t lds = MODE == 1 ? 0 : side * side * 2 * sizeof(double);
-  hipError_t e = set_lds(k_rows<STORE, MK, MODE>, lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_rows<STORE, MK, MODE>), dim3(nwi), dim3(GNT), lds, s, wi, meta, voff,
-                     perm, vals, X, Y, vis, Kx, Ky);
-  return hipGetLastError();
+// Bytes of the box accumulator of a class's items: rows' cells lie in one tile and their
+// patches of side <= class_tmax reach tile + side - 1 cells per axis; two FP64 planes.
+constexpr size_t box_bytes(int mk, int mode, int tile) {
+  const size_t side = (size_t)tile + class_tmax(mk) - 1;
+  return mode == 1 ? 0 : side * side * 2 * sizeof(double);
 }
 
-template <int STORE, int MODE>
-static hipError_t launch_cls(int cls, const WorkItem* wi, int nwi, const uint32_t* meta,
-                             const uint32_t* voff, const int32_t* perm, const void* vals,
-                             const float2* X, float2* Y, float2* vis, int Kx, int Ky, int tile,
-                             hipStream_t s) {
-#define WF_ONE(MK) \
-  launch_one<STORE, MK, MODE>(wi, nwi, meta, voff, perm, vals, X, Y, vis, Kx, Ky, tile, s)
-  switch (cls) {
-    case 0: return WF_ONE(2);
-    case 1: return WF_ONE(4);
-    case 2: return WF_ONE(7);
-    case 3: return WF_ONE(12);
-    case 4: return WF_ONE(16);
-    default: return WF_ONE(22);
+template <int STORE, int MODE, int C0 = 0>
+static hipError_t launch_groups(const RowPieces& pc, const uint32_t* meta, const uint32_t* voff,
+                                const int32_t* perm, const void* vals, const float2* X,
+                                float2* Y, float2* vis, int Kx, int Ky, int tile,
+                                hipStream_t s) {
+  if constexpr (C0 < NCLS) {
+    constexpr int C1 = group_end(STORE, MODE, C0);
+    int blocks = 0;
+    size_t lds = 0;
+    for (int c = C0; c < C1; ++c) {
+      blocks += pc.n[c];
+      if (pc.n[c] > 0) lds = box_bytes(class_mk(c), MODE, tile);
+    }
+    if (blocks > 0) {
+      hipError_t e = set_lds(k_rows<STORE, MODE, C0, C1>, lds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL((k_rows<STORE, MODE, C0, C1>), dim3(blocks), dim3(GNT), lds, s, pc,
+                         meta, voff, perm, vals, X, Y, vis, Kx, Ky);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return launch_groups<STORE, MODE, C1>(pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky, tile,
+                                          s);
   }
-#undef WF_ONE
+  return hipSuccess;
 }
 
 template <int MODE>
-static hipError_t launch_mode(int cls, const WorkItem* wi, int nwi, const uint32_t* meta,
-                              const uint32_t* voff, const int32_t* perm, const void* vals,
-                              wf_store store, const float2* X, float2* Y, float2* vis, int Kx,
-                              int Ky, int tile, hipStream_t s) {
-  if (nwi <= 0) return hipSuccess;
+static hipError_t launch_mode(const RowPieces& pc, const uint32_t* meta, const uint32_t* voff,
+                              const int32_t* perm, const void* vals, wf_store store,
+                              const float2* X, float2* Y, float2* vis, int Kx, int Ky, int tile,
+                              hipStream_t s) {
   switch (store) {
     case WF_STORE_F32:
-      return launch_cls<WF_STORE_F32, MODE>(cls, wi, nwi, meta, voff, perm, vals, X, Y, vis,
-                                            Kx, Ky, tile, s);
+      return launch_groups<WF_STORE_F32, MODE>(pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky,
+                                               tile, s);
     case WF_STORE_F16:
-      return launch_cls<WF_STORE_F16, MODE>(cls, wi, nwi, meta, voff, perm, vals, X, Y, vis,
-                                            Kx, Ky, tile, s);
+      return launch_groups<WF_STORE_F16, MODE>(pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky,
+                                               tile, s);
     default:
-      return launch_cls<WF_STORE_BF16, MODE>(cls, wi, nwi, meta, voff, perm, vals, X, Y, vis,
-                                             Kx, Ky, tile, s);
+      return launch_groups<WF_STORE_BF16, MODE>(pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky,
+                                                tile, s);
   }
 }
 
@@ -590,8 +621,7 @@ template <int STORE, int MK, int MODE>
 static hipError_t launch_sweep_one(const WorkItem* wi, int nwi, const SweepLayer* layers,
                                    float2* vis_base, int* queue, int Kx, int Ky, int tile,
                                    int grid_cap, hipStream_t s) {
-  const size_t side = (size_t)tile + class_tmax(MK) - 1;
-  const size_t lds = MODE == 1 ? 0 : side * side * 2 * sizeof(double);
+  const size_t lds = box_bytes(MK, MODE, tile);
   hipError_t e = set_lds(k_rows_sweep<STORE, MK, MODE>, lds);
   if (e != hipSuccess) return e;
   // resident workgroups only: as many as the device holds at once, capped by the items
@@ -644,26 +674,22 @@ hipError_t launch_rows_sweep(int mode, int cls, const WorkItem* wi, int nwi,
   }
 }
 
-hipError_t launch_gtg(int cls, const WorkItem* wi, int nwi, const uint32_t* meta,
-                      const uint32_t* voff, const void* vals, wf_store store, const float2* X,
-                      float2* Y, int Kx, int Ky, int tile, hipStream_t s) {
-  return launch_mode<0>(cls, wi, nwi, meta, voff, nullptr, vals, store, X, Y, nullptr, Kx, Ky,
-                        tile, s);
+hipError_t launch_gtg(const RowPieces& pc, const uint32_t* meta, const uint32_t* voff,
+                      const void* vals, wf_store store, const float2* X, float2* Y, int Kx,
+                      int Ky, int tile, hipStream_t s) {
+  return launch_mode<0>(pc, meta, voff, nullptr, vals, store, X, Y, nullptr, Kx, Ky, tile, s);
 }
 
-hipError_t launch_degrid(int cls, const WorkItem* wi, int nwi, const uint32_t* meta,
-                         const uint32_t* voff, const int32_t* perm, const void* vals,
-                         wf_store store, const float2* X, float2* vis, int Kx, int Ky,
-                         hipStream_t s) {
-  return launch_mode<1>(cls, wi, nwi, meta, voff, perm, vals, store, X, nullptr, vis, Kx, Ky,
-                        0, s);
+hipError_t launch_degrid(const RowPieces& pc, const uint32_t* meta, const uint32_t* voff,
+                         const int32_t* perm, const void* vals, wf_store store, const float2* X,
+                         float2* vis, int Kx, int Ky, hipStream_t s) {
+  return launch_mode<1>(pc, meta, voff, perm, vals, store, X, nullptr, vis, Kx, Ky, 0, s);
 }
 
-hipError_t launch_grid(int cls, const WorkItem* wi, int nwi, const uint32_t* meta,
-                       const uint32_t* voff, const int32_t* perm, const void* vals,
-                       wf_store store, const float2* vis, float2* Y, int Kx, int Ky, int tile,
-                       hipStream_t s) {
-  return launch_mode<2>(cls, wi, nwi, meta, voff, perm, vals, store, nullptr, Y,
+hipError_t launch_grid(const RowPieces& pc, const uint32_t* meta, const uint32_t* voff,
+                       const int32_t* perm, const void* vals, wf_store store, const float2* vis,
+                       float2* Y, int Kx, int Ky, int tile, hipStream_t s) {
+  return launch_mode<2>(pc, meta, voff, perm, vals, store, nullptr, Y,
                         const_cast<float2*>(vis), Kx, Ky, tile, s);
 }
 

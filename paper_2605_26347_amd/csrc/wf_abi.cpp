@@ -180,8 +180,8 @@ struct ProfScope {
 // Split the channel's row groups into work items of at most maxrows rows and 2^17
 // values (so that the classes of wide patches, few rows each, still fill the device; the
 // row kernels keep a wavefront's metadata for at most 128 rows in registers), then order
-// them by (bin, patch class) -- one launch per class -- with the largest items of a
-// launch first so that the hardware's in-order dispatch starts the longest work first.
+// them by (bin, patch class) with the largest items of a class first so that the hardware's
+// in-order dispatch starts the longest work first.
 // An item covers the rows of one patch class in one aligned block of 2^s x 2^s base
 // tiles (s = ch.bin_tsh of its bin, 0 when empty); the rows of such a block are
 // consecutive because the sort orders each class's tiles by interleaved index.
@@ -298,8 +298,8 @@ void split_items(ChanOp& ch, const uint8_t* trow, const uint32_t* meta_base, int
 // The row kernels' launches over a channel's items: each (bin, class) range of items (each
 // (chunk, class) range on the fly) is cut into pieces of consecutive rows and sent largest
 // first.  A launch ends with its longest workgroup, and an item of 1024 rows keeps one busy
-// for up to 100 us: where a launch has few rows it would leave the chip idle behind it, so a
-// piece holds at most a 768th of the launch's rows (three workgroups per compute unit), and
+// for up to 100 us: where a class has few rows it would leave the chip idle behind it, so a
+// piece holds at most a 768th of the class's rows (three workgroups per compute unit), and
 // at least 64 (eight per wavefront): a piece clears and flushes an accumulator of its own.
 // Measured against whole items: 64^2 psf 81 -> 35 us (27 items), 512^2 iteration 296 -> 212 us,
 // 1024^2 forward 1682 -> 1419 us, 4096^2 psf with 30M rows unchanged (its items average 139
@@ -360,6 +360,16 @@ wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint
                         hipMemcpyHostToDevice, s));
   WF_HIP(hipStreamSynchronize(s));
   return WF_OK;
+}
+
+// The pieces of bin (on the fly: chunk) k.
+RowPieces pieces_of(const ChanOp& ch, int64_t k) {
+  RowPieces pc{(const WorkItem*)ch.pieces.p, {}, {}};
+  for (int c = 0; c < NCLS; ++c) {
+    pc.first[c] = ch.pc_0[(size_t)k * NCLS + c];
+    pc.n[c] = ch.pc_n[(size_t)k * NCLS + c];
+  }
+  return pc;
 }
 
 // Data weights and flags of one channel (Sect. 2): the rows that are built and the
@@ -1327,23 +1337,19 @@ wf_status otf_bin_apply(wf_op* op, int kind, const Lane& L, const ChanOp& ch, in
     }
     // item value offsets are absolute: shift the base so that they land in the buffer
     const void* vals = (const char*)L.gbuf - (size_t)ch.ck_vbase[k] * b_v;
-    for (int c = 0; c < NCLS; ++c) {
-      const int n = ch.pc_n[(size_t)k * NCLS + c];
-      if (n == 0) continue;
-      const WorkItem* items = (const WorkItem*)ch.pieces.p + ch.pc_0[(size_t)k * NCLS + c];
-      if (kind == WF_APPLY_FORWARD) {
-        WF_HIP(launch_degrid(c, items, n, (const uint32_t*)ch.meta.p,
-                             (const uint32_t*)ch.voff.p, (const int32_t*)ch.perm.p, vals, store,
-                             L.X, (float2*)out, op->Kx, op->Ky, L.s));
-      } else if (from_vis(kind)) {
-        WF_HIP(launch_grid(c, items, n, (const uint32_t*)ch.meta.p, (const uint32_t*)ch.voff.p,
-                           (const int32_t*)ch.perm.p, vals, store, (const float2*)in, L.Y,
-                           op->Kx, op->Ky, op->tile, L.s));
-      } else {
-        ProfScope ps(prof_of(op, 0), L.s);
-        WF_HIP(launch_gtg(c, items, n, (const uint32_t*)ch.meta.p, (const uint32_t*)ch.voff.p,
-                          vals, store, L.X, L.Y, op->Kx, op->Ky, op->tile, L.s));
-      }
+    const RowPieces pc = pieces_of(ch, k);
+    if (kind == WF_APPLY_FORWARD) {
+      WF_HIP(launch_degrid(pc, (const uint32_t*)ch.meta.p, (const uint32_t*)ch.voff.p,
+                           (const int32_t*)ch.perm.p, vals, store, L.X, (float2*)out, op->Kx,
+                           op->Ky, L.s));
+    } else if (from_vis(kind)) {
+      WF_HIP(launch_grid(pc, (const uint32_t*)ch.meta.p, (const uint32_t*)ch.voff.p,
+                         (const int32_t*)ch.perm.p, vals, store, (const float2*)in, L.Y, op->Kx,
+                         op->Ky, op->tile, L.s));
+    } else {
+      ProfScope ps(prof_of(op, 0), L.s);
+      WF_HIP(launch_gtg(pc, (const uint32_t*)ch.meta.p, (const uint32_t*)ch.voff.p, vals, store,
+                        L.X, L.Y, op->Kx, op->Ky, op->tile, L.s));
     }
   }
   if (kind == WF_APPLY_FORWARD) return WF_OK;
@@ -1359,29 +1365,20 @@ wf_status bin_apply(wf_op* op, int kind, const Lane& L, const ChanOp& ch, int p,
   wf_status st;
   const ColPrune pr = prune_of(op, ch, p);
   const double wp = ch.centroids[p];
-  const WorkItem* wk = (const WorkItem*)ch.pieces.p;
   const float2* ct = ctab_of(op, ch, p);
   if (kind == WF_APPLY_FORWARD) {
     if ((st = layer_forward(op, L, in, wp, &pr, ct)) != WF_OK) return st;
-    for (int c = 0; c < NCLS; ++c) {
-      const int n = ch.pc_n[p * NCLS + c];
-      if (n == 0) continue;
-      WF_HIP(launch_degrid(c, wk + ch.pc_0[p * NCLS + c], n, (const uint32_t*)ch.meta.p,
-                           (const uint32_t*)ch.voff.p, (const int32_t*)ch.perm.p, ch.vals.p,
-                           op->opt.store, L.X, (float2*)out, op->Kx, op->Ky, L.s));
-    }
+    WF_HIP(launch_degrid(pieces_of(ch, p), (const uint32_t*)ch.meta.p,
+                         (const uint32_t*)ch.voff.p, (const int32_t*)ch.perm.p, ch.vals.p,
+                         op->opt.store, L.X, (float2*)out, op->Kx, op->Ky, L.s));
     return WF_OK;
   }
   const int mode = (real_out(kind) ? 2 : 0) + (first ? 0 : 1);
   if (from_vis(kind)) {
-    for (int c = 0; c < NCLS; ++c) {
-      const int n = ch.pc_n[p * NCLS + c];
-      if (n == 0) continue;
-      WF_HIP(launch_grid(c, wk + ch.pc_0[p * NCLS + c], n, (const uint32_t*)ch.meta.p,
-                         (const uint32_t*)ch.voff.p, (const int32_t*)ch.perm.p, ch.vals.p,
-                         op->opt.store, (const float2*)in, L.Y, op->Kx, op->Ky,
-                         bin_tile(op, ch, p), L.s));
-    }
+    WF_HIP(launch_grid(pieces_of(ch, p), (const uint32_t*)ch.meta.p,
+                       (const uint32_t*)ch.voff.p, (const int32_t*)ch.perm.p, ch.vals.p,
+                       op->opt.store, (const float2*)in, L.Y, op->Kx, op->Ky,
+                       bin_tile(op, ch, p), L.s));
     return layer_adjoint(op, L, out, wp, mode, &pr, ct);
   }
   if ((st = layer_forward(op, L, in, wp, &pr, ct)) != WF_OK) return st;
@@ -1394,13 +1391,9 @@ wf_status bin_apply(wf_op* op, int kind, const Lane& L, const ChanOp& ch, int p,
                          op->Ky, L.s));
   } else {
     ProfScope ps(prof_of(op, 0), L.s);
-    for (int c = 0; c < NCLS; ++c) {
-      const int n = ch.pc_n[p * NCLS + c];
-      if (n == 0) continue;
-      WF_HIP(launch_gtg(c, wk + ch.pc_0[p * NCLS + c], n, (const uint32_t*)ch.meta.p,
-                        (const uint32_t*)ch.voff.p, ch.vals.p, op->opt.store, L.X, L.Y,
-                        op->Kx, op->Ky, bin_tile(op, ch, p), L.s));
-    }
+    WF_HIP(launch_gtg(pieces_of(ch, p), (const uint32_t*)ch.meta.p, (const uint32_t*)ch.voff.p,
+                      ch.vals.p, op->opt.store, L.X, L.Y, op->Kx, op->Ky, bin_tile(op, ch, p),
+                      L.s));
   }
   return layer_adjoint(op, L, out, wp, mode, &pr, ct);
 }
@@ -1979,14 +1972,9 @@ wf_status retune_channel(wf_op* op, int c, int32_t maxrows, const int8_t* tsh = 
 // The fused G^dag G launches of bin p alone on lane L (autotuning: X is read as it is,
 // Y is added into).
 wf_status bin_gtg(wf_op* op, const ChanOp& ch, int p, const Lane& L) {
-  const WorkItem* wk = (const WorkItem*)ch.pieces.p;
-  for (int c = 0; c < NCLS; ++c) {
-    const int n = ch.pc_n[p * NCLS + c];
-    if (n == 0) continue;
-    WF_HIP(launch_gtg(c, wk + ch.pc_0[p * NCLS + c], n, (const uint32_t*)ch.meta.p,
-                      (const uint32_t*)ch.voff.p, ch.vals.p, op->opt.store, L.X, L.Y,
-                      op->Kx, op->Ky, bin_tile(op, ch, p), L.s));
-  }
+  WF_HIP(launch_gtg(pieces_of(ch, p), (const uint32_t*)ch.meta.p, (const uint32_t*)ch.voff.p,
+                    ch.vals.p, op->opt.store, L.X, L.Y, op->Kx, op->Ky, bin_tile(op, ch, p),
+                    L.s));
   return WF_OK;
 }
 

@@ -97,6 +97,11 @@ __host__ __device__ inline uint32_t pack_meta(int lu0, int lv0, int T) {
 __host__ __device__ constexpr int class_mk(int c) {
   return c == 0 ? 2 : c == 1 ? 4 : c == 2 ? 7 : c == 3 ? 12 : c == 4 ? 16 : 22;
 }
+// What a launch of the row kernels goes over: of each class the first piece and their count.
+struct RowPieces {
+  const WorkItem* items;
+  int32_t first[NCLS], n[NCLS];
+};
 // One (channel, bin) layer of a sweep: its work grids, pruning masks, row data of G,
 // w-layer centroid, channel, and the offset of its channel's visibilities.  A sweep
 // holds the grids of every layer at once so that each stage of the apply runs as one
@@ -412,19 +417,17 @@ hipError_t launch_inv_rows(const float2* A, void* out, const float2* tw, const f
                            int mode, const uint32_t* smask, const float2* ctab,
                            hipStream_t s);
 
-// Row kernels over the work items of one patch-size class `cls`; `tile` is the grid
-// tile side of the sort (it sizes each item's LDS accumulator).
-hipError_t launch_gtg(int cls, const WorkItem* wi, int nwi, const uint32_t* meta,
-                      const uint32_t* voff, const void* vals, wf_store store, const float2* X,
-                      float2* Y, int Kx, int Ky, int tile, hipStream_t s);
-hipError_t launch_degrid(int cls, const WorkItem* wi, int nwi, const uint32_t* meta,
-                         const uint32_t* voff, const int32_t* perm, const void* vals,
-                         wf_store store, const float2* X, float2* vis, int Kx, int Ky,
-                         hipStream_t s);
-hipError_t launch_grid(int cls, const WorkItem* wi, int nwi, const uint32_t* meta,
-                       const uint32_t* voff, const int32_t* perm, const void* vals,
-                       wf_store store, const float2* vis, float2* Y, int Kx, int Ky, int tile,
-                       hipStream_t s);
+// Row kernels over the pieces of a bin (or chunk), all patch-size classes; `tile` is the grid
+// tile side of the sort (it sizes each piece's LDS accumulator).
+hipError_t launch_gtg(const RowPieces& pc, const uint32_t* meta, const uint32_t* voff,
+                      const void* vals, wf_store store, const float2* X, float2* Y, int Kx,
+                      int Ky, int tile, hipStream_t s);
+hipError_t launch_degrid(const RowPieces& pc, const uint32_t* meta, const uint32_t* voff,
+                         const int32_t* perm, const void* vals, wf_store store, const float2* X,
+                         float2* vis, int Kx, int Ky, hipStream_t s);
+hipError_t launch_grid(const RowPieces& pc, const uint32_t* meta, const uint32_t* voff,
+                       const int32_t* perm, const void* vals, wf_store store, const float2* vis,
+                       float2* Y, int Kx, int Ky, int tile, hipStream_t s);
 hipError_t launch_fill_zero(void* p, int64_t nfloats, hipStream_t s);
 // out[idx[i]] = 0 for the n complex values listed (flagged visibilities).
 hipError_t launch_scatter_zero(float2* out, const int32_t* idx, int64_t n, hipStream_t s);
