@@ -811,12 +811,18 @@ __device__ __forceinline__ float2 load_val(const void* __restrict__ v, int64_t i
 // launch has few rows, so that every SIMD still holds several wavefronts): lane i reads
 // the i-th row's words and taps.  The rows are then expanded SL at a time,
 // one per slot of TM = NK + JT - 1 lanes (the largest patch side of the class), lane a_u
-// of a slot computing patch column a_u: first t[m] = sum_d ku[d] c[m][a_u - d] for the
-// kernel rows m (c staged in LDS), then G[a_v][a_u] = sum_d kv[d] t[a_v - d] in registers,
+// of a slot computing patch column a_u: t[m] = sum_d ku[d] c[m][a_u - d] for the kernel
+// rows m (c staged in LDS) and G[a_v][a_u] = sum_d kv[d] t[a_v - d] in registers,
 // so that the lanes of a slot write each patch row with consecutive values.  Loops run
 // to the largest n' and T among the wavefront's slots.  The next rows' kernels are
 // loaded while the current ones are expanded.  JT >= J taps are carried (zero past J).
 // over counts values beyond the FP16 range (FP16 store only).
+//
+// Bound by the FP32 issue of the two sums and by what hides their LDS reads: with all of t held
+// and the staged cells' coordinates kept unpacked over the rows the widest class used 224
+// registers (two wavefronts per SIMD); with the last JT values of t and one word per cell it
+// uses 109 (four).  Per launch, FP16 and FP32 (2048^2, 3M rows): side 31 107 -> 78 and
+// 166 -> 119 us, 21 58 -> 45 and 91 -> 69, 15 42 -> 39 and 82 -> 57, 11 49 -> 50 and 84 -> 72.
 template <int NK, int JT>
 struct EScratch {
   static constexpr int NN = NK * NK;
@@ -876,6 +882,13 @@ __device__ __forceinline__ int wave_max_u(int v) {
   return __builtin_amdgcn_readfirstlane(v);
 }
 
+// w, taken apart where this stands: its fields would otherwise be kept over the rows' loop, in
+// three registers for one.
+__device__ __forceinline__ uint32_t unpacked_here(uint32_t w) {
+  asm volatile("" : "+v"(w));
+  return w;
+}
+
 template <int STORE, int NK, int JT>
 __global__ __launch_bounds__(64) void k_expand(const int32_t* __restrict__ rows, int64_t nl,
                                                const uint32_t* __restrict__ meta,
@@ -895,6 +908,16 @@ __global__ __launch_bounds__(64) void k_expand(const int32_t* __restrict__ rows,
   const int lane = threadIdx.x;
   const int slot = lane / TM, au = lane - slot * TM;   // slot == SL: spare lanes
   bool ovf = false;
+  // The cells that this lane stages, lane + 64 q of the step's SL NN: kernel row m, column n,
+  // slot j (5 bits each) and byte offset in S.c, one word a cell.
+  static_assert(NK <= 31 && SL <= 31 && sizeof(S.c) < (1 << 17), "a cell's word");
+  uint32_t cw[CK];
+#pragma unroll
+  for (int q = 0; q < CK; ++q) {
+    const int i = lane + 64 * q, j = i / NN, e = i - j * NN, m = e / NK, n = e - m * NK;
+    cw[q] = (uint32_t)m | (uint32_t)n << 5 | (uint32_t)(j & 31) << 10 |
+            (uint32_t)((j * PS + m * PW + (JT - 1) + n) * 8) << 15;
+  }
   for (int64_t b0 = (int64_t)blockIdx.x * rpw; b0 < nl; b0 += (int64_t)gridDim.x * rpw) {
     const int nb = (int)(nl - b0 < rpw ? nl - b0 : rpw);
     // lane i: row b0 + i's patch side, kernel and value offsets, and taps
@@ -938,12 +961,8 @@ __global__ __launch_bounds__(64) void k_expand(const int32_t* __restrict__ rows,
       }
       return st;
     };
-    // cell i of the step: slot j, kernel row m, column n; its kernel index when inside
-    auto cell = [&](const Step& st, int i, int& j, int& m, int& n, int& np, uint32_t& ko) {
-      j = i / NN;
-      const int e = i - j * NN;
-      m = e / NK;
-      n = e - m * NK;
+    // the slot's n' and kernel offset for slot j
+    auto slot_of = [&](const Step& st, int j, int& np, uint32_t& ko) {
       np = st.np[0];
       ko = st.ko[0];
 #pragma unroll
@@ -957,11 +976,12 @@ __global__ __launch_bounds__(64) void k_expand(const int32_t* __restrict__ rows,
       const Step st = step_of(rb);
 #pragma unroll
       for (int q = 0; q < CK; ++q) {
-        const int i = lane + 64 * q;
-        int j, m, n, np;
+        const uint32_t w = unpacked_here(cw[q]);
+        const int m = (int)(w & 31u), n = (int)((w >> 5) & 31u);
+        int np;
         uint32_t ko;
-        cell(st, i, j, m, n, np, ko);
-        if (i < SL * NN && m < np && n < np)
+        slot_of(st, (int)((w >> 10) & 31u), np, ko);
+        if (lane + 64 * q < SL * NN && m < np && n < np)
           cb[q] = kraw_load<STORE>(khat, (int64_t)ko + m * np + n);
       }
     };
@@ -969,12 +989,13 @@ __global__ __launch_bounds__(64) void k_expand(const int32_t* __restrict__ rows,
       const Step st = step_of(rb);
 #pragma unroll
       for (int q = 0; q < CK; ++q) {
-        const int i = lane + 64 * q;
-        int j, m, n, np;
+        const uint32_t w = unpacked_here(cw[q]);
+        const int m = (int)(w & 31u), n = (int)((w >> 5) & 31u);
+        int np;
         uint32_t ko;
-        cell(st, i, j, m, n, np, ko);
-        if (i < SL * NN)
-          S.c[j * PS + m * PW + (JT - 1) + n] =
+        slot_of(st, (int)((w >> 10) & 31u), np, ko);
+        if (lane + 64 * q < SL * NN)
+          *reinterpret_cast<float2*>(reinterpret_cast<char*>(S.c) + (w >> 15)) =
               (m < np && n < np) ? kraw_widen<STORE>(cb[q]) : make_float2(0.f, 0.f);
       }
     };
@@ -1005,27 +1026,27 @@ __global__ __launch_bounds__(64) void k_expand(const int32_t* __restrict__ rows,
         kv[d] = __shfl(mykv[d], src, 64);
       }
       const int npmax = wave_max_u(np), Tmax = wave_max_u(T);
-      // t[m] = sum_d ku[d] c[m][a_u - d]: reads at a_u - d + JT - 1 in [0, PW) (a_u < TM)
+      // Patch row by patch row: t[m] = sum_d ku[d] c[m][a_u - d], which reads at
+      // a_u - d + JT - 1 in [0, PW) (a_u < TM), then G[a_v][a_u] = sum_d kv[d] t[a_v - d],
+      // so that the last JT values of t are all that is held.
       const float2* c = S.c + (slot < SL ? slot : 0) * PS + au;
+      const bool col = valid && au < T;
       float2 t[NK];
 #pragma unroll
-      for (int m = 0; m < NK; ++m) {
-        t[m] = make_float2(0.f, 0.f);
-        if (m < npmax) {
-          float re = 0.f, im = 0.f;
-#pragma unroll
-          for (int d = 0; d < JT; ++d) {
-            const float2 v = c[m * PW + (JT - 1 - d)];
-            re = fmaf(ku[d], v.x, re);
-            im = fmaf(ku[d], v.y, im);
-          }
-          t[m] = make_float2(re, im);
-        }
-      }
-      // G[a_v][a_u] = sum_d kv[d] t[a_v - d]
-      const bool col = valid && au < T;
-#pragma unroll
       for (int av = 0; av < TM; ++av) {
+        if (av < NK) {
+          t[av] = make_float2(0.f, 0.f);
+          if (av < npmax) {
+            float re = 0.f, im = 0.f;
+#pragma unroll
+            for (int d = 0; d < JT; ++d) {
+              const float2 v = c[av * PW + (JT - 1 - d)];
+              re = fmaf(ku[d], v.x, re);
+              im = fmaf(ku[d], v.y, im);
+            }
+            t[av] = make_float2(re, im);
+          }
+        }
         if (av < Tmax) {
           float re = 0.f, im = 0.f;
 #pragma unroll
