@@ -395,7 +395,7 @@ wf_status wf_set_bin_tiles(wf_op* op, int32_t chan, const int32_t* tiles, int32_
  * with x_dirty = Re{Phi^dag y}, here with the non-learned denoiser D(z) = max(z - gamma
  * lambda, 0), the prox of lambda ||x||_1 under positivity.  Images are real FP32
  * [nchan][ny][nx] device buffers; the library keeps two work images of that size (and a
- * complex one for the dirty image), allocated on first use. */
+ * complex one for a dirty image that overlaps its visibilities), allocated on first use. */
 
 /* x_dirty = Re{Phi^dag y}; d_vis complex FP32 [total rows].  Not for holographic
  * operators (WF_ENOTSUP). */
