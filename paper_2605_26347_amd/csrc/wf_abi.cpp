@@ -313,6 +313,7 @@ wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint
   ch.pc_0.assign(r0.size(), 0);
   ch.pc_n.assign(r0.size(), 0);
   std::vector<WorkItem> part;
+  std::vector<std::pair<int64_t, int32_t>> order;
   for (size_t k = 0; k < r0.size(); ++k) {
     if (rn[k] == 0) continue;
     int64_t rows = 0;
@@ -339,16 +340,16 @@ wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint
         part.push_back(p);
       }
     }
-    auto taps = [&](const WorkItem& w) {
-      const int64_t T = (meta[w.row0] >> 16) & 0xff;
-      return T * T * w.nrows;
-    };
-    std::stable_sort(part.begin(), part.end(), [&](const WorkItem& x, const WorkItem& y) {
-      return taps(x) > taps(y);
-    });
+    // largest first, by taps (read once: a comparison that looks them up is most of the time)
+    order.clear();
+    for (size_t i = 0; i < part.size(); ++i) {
+      const int64_t T = (meta[part[i].row0] >> 16) & 0xff;
+      order.emplace_back(-T * T * part[i].nrows, (int32_t)i);
+    }
+    std::sort(order.begin(), order.end());
     ch.pc_0[k] = (int32_t)all.size();
     ch.pc_n[k] = (int32_t)part.size();
-    all.insert(all.end(), part.begin(), part.end());
+    for (const auto& o : order) all.push_back(part[o.second]);
   }
   const size_t bytes = sizeof(WorkItem) * std::max<size_t>(all.size(), 1);
   if (ch.pieces.bytes < bytes) {
