@@ -304,6 +304,7 @@ void split_items(ChanOp& ch, const uint8_t* trow, const uint32_t* meta_base, int
 // Measured against whole items: 64^2 psf 81 -> 35 us (27 items), 512^2 iteration 296 -> 212 us,
 // 1024^2 forward 1682 -> 1419 us, 4096^2 psf with 30M rows unchanged (its items average 139
 // rows); 1536 pieces cost that one 2%, 384 leave the forward 6% slower.
+// The table is allocated anew: the one that the caller holds stays its own.
 constexpr int64_t PIECES = 768, PIECE_MIN = 64;
 wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint32_t* meta,
                         hipStream_t s) {
@@ -351,12 +352,8 @@ wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint
     ch.pc_n[k] = (int32_t)part.size();
     for (const auto& o : order) all.push_back(part[o.second]);
   }
-  const size_t bytes = sizeof(WorkItem) * std::max<size_t>(all.size(), 1);
-  if (ch.pieces.bytes < bytes) {
-    dfree(ch.pieces);
-    wf_status st = dalloc(ch.pieces, bytes);
-    if (st != WF_OK) return st;
-  }
+  wf_status st = dalloc(ch.pieces, sizeof(WorkItem) * std::max<size_t>(all.size(), 1));
+  if (st != WF_OK) return st;
   WF_HIP(hipMemcpyAsync(ch.pieces.p, all.data(), sizeof(WorkItem) * all.size(),
                         hipMemcpyHostToDevice, s));
   WF_HIP(hipStreamSynchronize(s));
@@ -1944,6 +1941,21 @@ wf_status retune_channel(wf_op* op, int c, int32_t maxrows, const int8_t* tsh = 
   std::vector<uint32_t> meta(M), voff(M);
   WF_HIP(hipMemcpy(meta.data(), ch.meta.p, sizeof(uint32_t) * M, hipMemcpyDeviceToHost));
   base_meta(ch, op->tile, op->halo, meta.data());
+  // The split in use stays whole, on the host and on the device, until all that the new one
+  // needs is allocated: where that fails the channel is left as it was.
+  struct Undo {
+    ChanOp& ch;
+    ItemTables old;
+    bool done = false;
+    ~Undo() {
+      ItemTables& now = ch;
+      if (!done) std::swap(now, old);
+      dfree(old.work);
+      dfree(old.pieces);
+    }
+  } undo{ch, ch};
+  ch.work = DevBuf{};
+  ch.pieces = DevBuf{};
   ch.bin_tsh = ntsh;
   std::vector<uint8_t> trow(M);
   for (int64_t r = 0; r < M; ++r) trow[r] = (uint8_t)((meta[r] >> 16) & 0xff);
@@ -1951,19 +1963,16 @@ wf_status retune_channel(wf_op* op, int c, int32_t maxrows, const int8_t* tsh = 
   std::vector<int32_t> row_wi(ch.otf ? M : 0);
   split_items(ch, trow.data(), meta.data(), maxrows, op->tile, op->halo, wis, voff.data(),
               meta.data(), ch.otf ? row_wi.data() : nullptr);
+  wf_status st = dalloc(ch.work, sizeof(WorkItem) * std::max<size_t>(wis.size(), 1));
+  if (st != WF_OK) return st;
+  if ((st = schedule_rows(ch, wis, meta.data(), nullptr)) != WF_OK) return st;
+  undo.done = true;
   if (ch.otf)   // the on-the-fly value pass finds each row's item through row_wi
     WF_HIP(hipMemcpy(ch.row_wi.p, row_wi.data(), sizeof(int32_t) * M, hipMemcpyHostToDevice));
-  if (ch.work.bytes < sizeof(WorkItem) * wis.size()) {
-    dfree(ch.work);
-    wf_status st = dalloc(ch.work, sizeof(WorkItem) * wis.size());
-    if (st != WF_OK) return st;
-  }
   WF_HIP(hipMemcpy(ch.meta.p, meta.data(), sizeof(uint32_t) * M, hipMemcpyHostToDevice));
   WF_HIP(hipMemcpy(ch.voff.p, voff.data(), sizeof(uint32_t) * M, hipMemcpyHostToDevice));
   WF_HIP(hipMemcpy(ch.work.p, wis.data(), sizeof(WorkItem) * wis.size(),
                    hipMemcpyHostToDevice));
-  wf_status st = schedule_rows(ch, wis, meta.data(), nullptr);
-  if (st != WF_OK) return st;
   ch.info.nwork = ch.nwork;
   ch.info.max_rows_per_item = ch.max_rows;
   op->generation++;

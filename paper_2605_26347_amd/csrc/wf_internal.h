@@ -215,7 +215,24 @@ struct DebugIndex {
   std::vector<WorkItem> items;
 };
 
-struct ChanOp {
+// A channel's split of its rows into work items and pieces: what a re-split replaces as one.
+struct ItemTables {
+  std::vector<int32_t> bin_wi0, bin_nwi;
+  std::vector<int32_t> cls_wi0, cls_nwi;   // [bin * NCLS + class]
+  std::vector<int32_t> ck_wi0, ck_nwi;     // [chunk * NCLS + class] work-item ranges
+  int32_t max_rows = 1024;                 // rows per work item of the current split
+  // per bin: work items cover aligned blocks of 2^s x 2^s base tiles (item tile side
+  // tile << s); the rows' patch words are relative to their item's window
+  std::vector<int8_t> bin_tsh;
+  int64_t nwork = 0;
+  DevBuf work;
+  // what the row kernels are launched on: the items of `work` cut into pieces (schedule_rows),
+  // largest first, per (bin, class), or per (chunk, class) on the fly: first piece, count
+  DevBuf pieces;
+  std::vector<int32_t> pc_0, pc_n;
+};
+
+struct ChanOp : ItemTables {
   double freq = 0, scale = 0;
   int64_t vis_off = 0;   // offset of this channel's rows in the caller's vis vector
   int64_t nrows = 0;     // rows built (flagged rows excluded)
@@ -225,14 +242,8 @@ struct ChanOp {
   int P = 0;
   std::vector<double> centroids;
   std::vector<int64_t> bin_row0, bin_nrows;
-  std::vector<int32_t> bin_wi0, bin_nwi;
-  std::vector<int32_t> cls_wi0, cls_nwi;   // [bin * NCLS + class]
   std::vector<int64_t> bin_taps;           // stored values per bin
   std::vector<RowGroup> groups;            // in sorted-row order
-  int32_t max_rows = 1024;                 // rows per work item of the current split
-  // per bin: work items cover aligned blocks of 2^s x 2^s base tiles (item tile side
-  // tile << s); the rows' patch words are relative to their item's window
-  std::vector<int8_t> bin_tsh;
   // per bin: the column table of its w-layer modulation ([P][nx] complex FP32, FP64
   // phases), used by the row FFT passes where cfast[p] (field and w_p small enough for
   // the series forms; otherwise the direct form)
@@ -240,7 +251,6 @@ struct ChanOp {
   std::vector<uint8_t> cfast;
   double measured_ms = 0;                  // last timed apply of this channel (0 = none)
   int64_t ntaps = 0;
-  int64_t nwork = 0;
   bool holo = false;                       // strategy (b): H only
   DevBuf htiles, hvals;                    // HTile [tiles of all bins], stencil values
   std::vector<int64_t> h_t0, h_nt;         // per bin: first tile, tile count
@@ -262,13 +272,8 @@ struct ChanOp {
   std::vector<int32_t> gchunk;             // chunk of each row group
   std::vector<int64_t> ck_s0, ck_s1, ck_vbase, ck_taps;  // sorted rows, first value, values
   std::vector<int32_t> ck_first, ck_count; // per bin: first chunk, chunk count
-  std::vector<int32_t> ck_wi0, ck_nwi;     // [chunk * NCLS + class] work-item ranges
   int64_t ck_max = 0;                      // values of the largest chunk
-  DevBuf meta, voff, perm, vals, work;
-  // what the row kernels are launched on: the items of `work` cut into pieces (schedule_rows),
-  // largest first, per (bin, class), or per (chunk, class) on the fly: first piece, count
-  DevBuf pieces;
-  std::vector<int32_t> pc_0, pc_n;
+  DevBuf meta, voff, perm, vals;
   DevBuf prune;                            // per bin: strip bits, tile bits, groups
   std::vector<size_t> pr_strip, pr_tile, pr_groups;  // byte offsets into prune per bin
   std::vector<int32_t> pr_ngroups;
