@@ -225,33 +225,83 @@ __device__ __forceinline__ void window_zero(double* acc, const Box& bx) {
   const int n = bx.w * bx.h;
   for (int c = threadIdx.x; c < 2 * n; c += GNT) acc[c] = 0.0;
 }
-// Add the box into Y, line by line of the grid's layout: 32 lanes on the 32 floats of one
-// 128-byte line (2^GRID_L columns x 2^(4 - GRID_L) rows of complex cells), floats outside the
-// box and untouched ones skipped.  An atomic costs by the 64-byte segments that it touches, so
-// a line is sent whole: real parts and imaginary parts in instructions of their own touched
-// every segment twice.
-__device__ __forceinline__ void window_flush(const double* acc, const Box& bx, int u0, int v0,
-                                             int Kx, int Ky, float2* __restrict__ Y) {
+// Goes over the cells of a box line by line of the grid's layout: 32 lanes on the 32 floats of
+// one 128-byte line (2^GRID_L columns x 2^(4 - GRID_L) rows of complex cells), lines first, first
+// + step, ..., calling on(a, b, part, at) for cell (row a, column b) of the box, part 0 the real
+// and 1 the imaginary float, at() its address.  An atomic costs by the 64-byte segments that it touches, so a
+// line is sent whole: real parts and imaginary parts in instructions of their own touched every
+// segment twice.
+template <typename ON>
+__device__ __forceinline__ void each_line(const Box& bx, int u0, int v0, int Kx, int Ky,
+                                          float2* __restrict__ Y, int first, int step, ON&& on) {
   constexpr int L = GRID_L, H = 4 - GRID_L;
-  const int n = bx.w * bx.h;
   const int ub = u0 + bx.u0, vb = v0 + bx.v0;          // grid origin of the box (unwrapped)
   const int fu = ub & ((1 << L) - 1), fv = vb & ((1 << H) - 1);
   const int nx = (fu + bx.w + (1 << L) - 1) >> L, ny = (fv + bx.h + (1 << H) - 1) >> H;
   const float inv = __builtin_amdgcn_rcpf((float)nx);
   const int part = threadIdx.x & 1, cell = (threadIdx.x >> 1) & 15;
   const int cu = (cell & ((1 << L) - 1)) - fu, cv = (cell >> L) - fv;
-  const double* __restrict__ plane = acc + part * n;
   float* __restrict__ Yp = reinterpret_cast<float*>(Y) + part;
-  for (int c = threadIdx.x >> 5; c < nx * ny; c += GNT / 32) {
+  for (int c = first + (threadIdx.x >> 5); c < nx * ny; c += step) {
     int ly, lx;
     tap_ab(c, nx, inv, ly, lx);
     const int a = (ly << H) + cv, b = (lx << L) + cu;
-    if ((unsigned)a < (unsigned)bx.h && (unsigned)b < (unsigned)bx.w) {
-      const float v = (float)plane[a * bx.w + b];
-      if (v != 0.f)
-        unsafeAtomicAdd(Yp + 2 * grid_index((vb + a) & (Ky - 1), (ub + b) & (Kx - 1), Ky), v);
-    }
+    if ((unsigned)a < (unsigned)bx.h && (unsigned)b < (unsigned)bx.w)
+      on(a, b, part,
+         [&] { return Yp + 2 * grid_index((vb + a) & (Ky - 1), (ub + b) & (Kx - 1), Ky); });
   }
+}
+
+// Add the box into Y (untouched cells skipped).
+__device__ __forceinline__ void window_flush(const double* acc, const Box& bx, int u0, int v0,
+                                             int Kx, int Ky, float2* __restrict__ Y) {
+  const double* __restrict__ plane = acc + (threadIdx.x & 1) * (bx.w * bx.h);
+  each_line(bx, u0, v0, Kx, Ky, Y, 0, GNT / 32, [&](int a, int b, int, auto&& at) {
+    const float v = (float)plane[a * bx.w + b];
+    if (v != 0.f) unsafeAtomicAdd(at(), v);
+  });
+}
+
+// Store the box where the pieces of its item meet.
+__device__ __forceinline__ void window_store(const double* acc, const Box& bx,
+                                             double2* __restrict__ sums) {
+  const int n = bx.w * bx.h;
+  for (int c = threadIdx.x; c < n; c += GNT) sums[c] = make_double2(acc[c], acc[n + c]);
+}
+
+// The cut items' sums into Y: a workgroup adds up the pieces of eight of an item's lines in
+// FP64, a cell's values of MERGE_P pieces requested at once (their latency is what the pass
+// costs), and adds each cell once.
+constexpr int MERGE_LINES = 8, MERGE_P = 8;
+__global__ __launch_bounds__(32 * MERGE_LINES) void k_merge(const CutItem* __restrict__ cuts,
+                                                            const CutPart* __restrict__ parts,
+                                                            const double2* __restrict__ sums,
+                                                            float2* __restrict__ Y, int Kx,
+                                                            int Ky) {
+  const CutItem it = cuts[blockIdx.x];
+  const Box bx = box_of(it.box);
+  each_line(bx, it.u0, it.v0, Kx, Ky, Y, blockIdx.y * MERGE_LINES, gridDim.y * MERGE_LINES,
+            [&](int a, int b, int part, auto&& at) {
+              const double* __restrict__ src = reinterpret_cast<const double*>(sums) + part;
+              double s = 0.0;
+              for (int j0 = 0; j0 < it.nparts; j0 += MERGE_P) {
+                double v[MERGE_P];
+#pragma unroll
+                for (int j = 0; j < MERGE_P; ++j) {
+                  const CutPart p = parts[it.part0 + min(j0 + j, it.nparts - 1)];
+                  const Box pb = box_of(p.box);
+                  const int pa = a + bx.v0 - pb.v0, pu = b + bx.u0 - pb.u0;
+                  v[j] = j0 + j < it.nparts && (unsigned)pa < (unsigned)pb.h &&
+                                 (unsigned)pu < (unsigned)pb.w
+                             ? src[2 * (int64_t)(p.slot + pa * pb.w + pu)]
+                             : 0.0;
+                }
+#pragma unroll
+                for (int j = 0; j < MERGE_P; ++j) s += v[j];
+              }
+              const float f = (float)s;
+              if (f != 0.f) unsafeAtomicAdd(at(), f);
+            });
 }
 
 // How a row kernel is held to the registers that let its workgroups (two wavefronts per SIMD
@@ -285,21 +335,45 @@ constexpr RowForm row_form(int store, int mk, int mode) {
   return {true, 1, f16 || mode == 2 ? 4 : 2};
 }
 
-// One work item on one workgroup.  MODE 0: fused G^dag G; 1: de-gridding; 2: gridding.
+// An item's words in scalar registers.  The item tables do not change during a launch, but beside
+// plain stores the compiler does not know that and loads them per lane, each time with a wait
+// (the fused kernels 10% slower): so they are read as constant memory.
+__device__ __forceinline__ WorkItem read_item(const WorkItem* wi) {
+  const auto* w = (const __attribute__((address_space(4))) int32_t*)(uintptr_t)wi;
+  WorkItem r;
+  r.voff = (int64_t)((uint64_t)(uint32_t)w[0] | (uint64_t)(uint32_t)w[1] << 32);
+  r.row0 = w[2];
+  r.nrows = w[3];
+  r.u0 = w[4];
+  r.v0 = w[5];
+  r.bin = w[6];
+  r.box = w[7];
+  return r;
+}
+
+// One work item on one workgroup.  Its box is added into Y; that of a piece of a cut item (sums
+// given, slot in wi.bin) is stored for k_merge.  MODE 0: fused G^dag G; 1: de-gridding; 2: gridding.
 // Every thread passes the same two barriers (scattering modes), whatever its rows.
 template <int STORE, int MK, int MODE>
-__device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __restrict__ meta,
+__device__ __forceinline__ void row_item(const WorkItem wi, const uint32_t* __restrict__ meta,
                                          const uint32_t* __restrict__ voff,
                                          const int32_t* __restrict__ perm,
                                          const void* __restrict__ vals,
                                          const float2* __restrict__ X, float2* __restrict__ Y,
                                          float2* __restrict__ vis, int Kx, int Ky,
-                                         double* acc) {
+                                         double* acc, double2* __restrict__ sums) {
   constexpr bool GATHER = MODE != 2;
   constexpr bool SCATTER = MODE != 1;
   constexpr int VB = value_bytes<STORE>();
   const Box bx = box_of(wi.box);
   const int plane = bx.w * bx.h * 8;
+  const int slot = sums ? wi.bin : -1;
+  auto finish = [&] {
+    if (slot >= 0)
+      window_store(acc, bx, sums + slot);
+    else
+      window_flush(acc, bx, wi.u0, wi.v0, Kx, Ky, Y);
+  };
   const int ksh = 31 - __builtin_clz(Ky);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -315,7 +389,7 @@ __device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __r
       window_zero(acc, bx);
       __syncthreads();
       __syncthreads();
-      window_flush(acc, bx, wi.u0, wi.v0, Kx, Ky, Y);
+      finish();
     }
     return;
   }
@@ -464,7 +538,7 @@ __device__ __forceinline__ void row_item(const WorkItem& wi, const uint32_t* __r
     if (!F.direct && cur != 0xffffffffu)
       scatter_patch<MK>(rg, sl, bx, lane, [&](int k) { return ac[k]; }, acc, plane);
     __syncthreads();
-    window_flush(acc, bx, wi.u0, wi.v0, Kx, Ky, Y);
+    finish();
   }
 }
 
@@ -494,8 +568,8 @@ __device__ __forceinline__ void row_block(int b, const RowPieces& pc,
   if constexpr (C1 > C0) {
     constexpr int C = C1 - 1;
     if (b < pc.n[C])
-      row_item<STORE, class_mk(C), MODE>(pc.items[pc.first[C] + b], meta, voff, perm, vals, X,
-                                         Y, vis, Kx, Ky, acc);
+      row_item<STORE, class_mk(C), MODE>(read_item(pc.items + pc.first[C] + b), meta, voff, perm,
+                                         vals, X, Y, vis, Kx, Ky, acc, pc.sums);
     else
       row_block<STORE, MODE, C0, C>(b - pc.n[C], pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky,
                                     acc);
@@ -536,10 +610,11 @@ __global__ __launch_bounds__(GNT) void k_rows_sweep(const WorkItem* __restrict__
     const int i = slot;
     __syncthreads();
     if (i >= nitems) break;
-    const WorkItem wi = wis[i];
+    const WorkItem wi = read_item(wis + i);
     const SweepLayer& L = layers[wi.bin];
     row_item<STORE, MK, MODE>(wi, L.meta, L.voff, L.perm, L.vals, L.X, L.Y,
-                              vis_base ? vis_base + L.vis_off : nullptr, Kx, Ky, acc);
+                              vis_base ? vis_base + L.vis_off : nullptr, Kx, Ky, acc,
+                              nullptr);
   }
   if (threadIdx.x == 0) {
     __threadfence();
@@ -604,17 +679,25 @@ static hipError_t launch_mode(const RowPieces& pc, const uint32_t* meta, const u
                               const int32_t* perm, const void* vals, wf_store store,
                               const float2* X, float2* Y, float2* vis, int Kx, int Ky, int tile,
                               hipStream_t s) {
+  hipError_t e;
   switch (store) {
     case WF_STORE_F32:
-      return launch_groups<WF_STORE_F32, MODE>(pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky,
-                                               tile, s);
+      e = launch_groups<WF_STORE_F32, MODE>(pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky, tile,
+                                            s);
+      break;
     case WF_STORE_F16:
-      return launch_groups<WF_STORE_F16, MODE>(pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky,
-                                               tile, s);
+      e = launch_groups<WF_STORE_F16, MODE>(pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky, tile,
+                                            s);
+      break;
     default:
-      return launch_groups<WF_STORE_BF16, MODE>(pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky,
-                                                tile, s);
+      e = launch_groups<WF_STORE_BF16, MODE>(pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky, tile,
+                                             s);
+      break;
   }
+  if (e != hipSuccess || MODE == 1 || pc.ncuts == 0) return e;
+  hipLaunchKernelGGL(k_merge, dim3(pc.ncuts, (pc.cut_lines + MERGE_LINES - 1) / MERGE_LINES),
+                     dim3(32 * MERGE_LINES), 0, s, pc.cuts, pc.parts, pc.sums, Y, Kx, Ky);
+  return hipGetLastError();
 }
 
 template <int STORE, int MK, int MODE>

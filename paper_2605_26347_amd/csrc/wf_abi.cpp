@@ -41,7 +41,7 @@ wf_status dalloc(DevBuf& b, size_t bytes) {
   }
   hipError_t e = hipMalloc(&b.p, bytes);
   if (e != hipSuccess) {
-    b.p = nullptr;
+    b = DevBuf{};
     (void)hipGetLastError();
     return fail(WF_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed: " +
                                hipGetErrorString(e));
@@ -97,6 +97,8 @@ void destroy_op(wf_op* op) {
     dfree(c.vals);
     dfree(c.work);
     dfree(c.pieces);
+    dfree(c.cuts);
+    dfree(c.parts);
     dfree(c.prune);
     dfree(c.htiles);
     dfree(c.hvals);
@@ -299,36 +301,66 @@ void split_items(ChanOp& ch, const uint8_t* trow, const uint32_t* meta_base, int
 // (chunk, class) range on the fly) is cut into pieces of consecutive rows and sent largest
 // first.  A launch ends with its longest workgroup, and an item of 1024 rows keeps one busy
 // for up to 100 us: where a class has few rows it would leave the chip idle behind it, so a
-// piece holds at most a 768th of the class's rows (three workgroups per compute unit), and
-// at least 64 (eight per wavefront): a piece clears and flushes an accumulator of its own.
-// Measured against whole items: 64^2 psf 81 -> 35 us (27 items), 512^2 iteration 296 -> 212 us,
-// 1024^2 forward 1682 -> 1419 us, 4096^2 psf with 30M rows unchanged (its items average 139
-// rows); 1536 pieces cost that one 2%, 384 leave the forward 6% slower.
-// The table is allocated anew: the one that the caller holds stays its own.
-constexpr int64_t PIECES = 768, PIECE_MIN = 64;
+// piece holds at most a share of the class's rows, and not less than keeps its wavefronts busy.
+// De-gridding takes a 768th (three workgroups per compute unit) and at least 64 rows (eight per
+// wavefront).  The kernels that scatter take a 384th and at least 128, for their pieces cost more:
+// each clears an accumulator of its own and stores it, and the sums of an item's pieces meet in
+// FP64 before they reach the FP32 grid (CutItem), as those of a whole item do in its one
+// accumulator.  (Each piece added into the grid by itself put a third on the adjoint's error
+// where a cell gathers many rows: 20,000 rows in 28^2 cells 2.3e-7 for 1.7e-7.)
+// Whole items / pieces of a 768th and 64 / of a 384th and 128: 64^2 psf 81 / 38 / 38 us (27
+// items), ten 512^2 iterations 1980 / 1465 / 1416 us, 1024^2 adjoint 900 / 923 / 884 us, 1024^2
+// forward 1471 / 1359 / 1404 us, 8192^2 forward 2536 / 2294 / 2406 us; 4096^2 psf with 30M rows
+// the same (its items average 139 rows).
+// The tables are allocated anew: those that the caller holds stay its own.
+struct PieceRule {
+  int64_t share, least;
+};
+constexpr PieceRule GATHER_PIECES{768, 64}, SCATTER_PIECES{384, 128};
 wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint32_t* meta,
                         hipStream_t s) {
   std::vector<WorkItem> all;
+  std::vector<CutItem> cuts;
+  std::vector<CutPart> parts;
   const std::vector<int32_t>& r0 = ch.ck_nwi.empty() ? ch.cls_wi0 : ch.ck_wi0;
   const std::vector<int32_t>& rn = ch.ck_nwi.empty() ? ch.cls_nwi : ch.ck_nwi;
-  ch.pc_0.assign(r0.size(), 0);
-  ch.pc_n.assign(r0.size(), 0);
+  const size_t nk = r0.size();
+  ch.pc_0.assign(2 * nk, 0);
+  ch.pc_n.assign(2 * nk, 0);
+  ch.cut_0.assign(nk / NCLS, 0);
+  ch.cut_n.assign(nk / NCLS, 0);
+  ch.cut_lines.assign(nk / NCLS, 0);
+  ch.sum_cells = 0;
   std::vector<WorkItem> part;
   std::vector<std::pair<int64_t, int32_t>> order;
-  for (size_t k = 0; k < r0.size(); ++k) {
+  int64_t slot = 0;   // of the bin's (chunk's) next piece
+  for (size_t k2 = 0; k2 < 2 * nk; ++k2) {
+    const bool scatter = k2 >= nk;
+    const PieceRule rule = scatter ? SCATTER_PIECES : GATHER_PIECES;
+    const size_t k = scatter ? k2 - nk : k2, bin = k / NCLS;
+    if (k % NCLS == 0) {
+      ch.cut_0[bin] = (int32_t)cuts.size();
+      slot = 0;
+    }
     if (rn[k] == 0) continue;
     int64_t rows = 0;
     for (int i = 0; i < rn[k]; ++i) rows += wis[r0[k] + i].nrows;
-    const int64_t most = std::max<int64_t>(PIECE_MIN, (rows / PIECES + 7) / 8 * 8);
+    const int64_t most = std::max(rule.least, (rows / rule.share + 7) / 8 * 8);
     part.clear();
     for (int i = 0; i < rn[k]; ++i) {
       const WorkItem& w = wis[r0[k] + i];
       const int n = (int)((w.nrows + most - 1) / most);
+      if (scatter && n > 1) {
+        cuts.push_back(CutItem{w.u0, w.v0, w.box, (int32_t)parts.size(), n});
+        ch.cut_n[bin]++;
+        ch.cut_lines[bin] = std::max(ch.cut_lines[bin], box_lines(w.box));
+      }
       for (int j = 0; j < n; ++j) {
         WorkItem p = w;
+        p.bin = -1;
         p.row0 = w.row0 + (int32_t)((int64_t)w.nrows * j / n);
         p.nrows = w.row0 + (int32_t)((int64_t)w.nrows * (j + 1) / n) - p.row0;
-        if (n > 1) {
+        if (scatter && n > 1) {
           int u0 = 255, v0 = 255, u1 = 0, v1 = 0;
           for (int r = p.row0; r < p.row0 + p.nrows; ++r) {
             const int lu = meta[r] & 0xff, lv = (meta[r] >> 8) & 0xff, T = (meta[r] >> 16) & 0xff;
@@ -337,10 +369,14 @@ wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint
           }
           p.box = (int32_t)((uint32_t)u0 | ((uint32_t)v0 << 8) | ((uint32_t)(u1 - u0) << 16) |
                             ((uint32_t)(v1 - v0) << 24));
+          p.bin = (int32_t)slot;
+          parts.push_back(CutPart{p.bin, p.box});
+          slot += (int64_t)(u1 - u0) * (v1 - v0);
         }
         part.push_back(p);
       }
     }
+    ch.sum_cells = std::max(ch.sum_cells, slot);
     // largest first, by taps (read once: a comparison that looks them up is most of the time)
     order.clear();
     for (size_t i = 0; i < part.size(); ++i) {
@@ -348,26 +384,22 @@ wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint
       order.emplace_back(-T * T * part[i].nrows, (int32_t)i);
     }
     std::sort(order.begin(), order.end());
-    ch.pc_0[k] = (int32_t)all.size();
-    ch.pc_n[k] = (int32_t)part.size();
+    ch.pc_0[k2] = (int32_t)all.size();
+    ch.pc_n[k2] = (int32_t)part.size();
     for (const auto& o : order) all.push_back(part[o.second]);
   }
-  wf_status st = dalloc(ch.pieces, sizeof(WorkItem) * std::max<size_t>(all.size(), 1));
-  if (st != WF_OK) return st;
-  WF_HIP(hipMemcpyAsync(ch.pieces.p, all.data(), sizeof(WorkItem) * all.size(),
-                        hipMemcpyHostToDevice, s));
+  wf_status st;
+  auto room = [](DevBuf& b, size_t bytes) { return dalloc(b, std::max<size_t>(bytes, 8)); };
+  const size_t nb = sizeof(WorkItem) * all.size(), nc = sizeof(CutItem) * cuts.size(),
+               np = sizeof(CutPart) * parts.size();
+  if ((st = room(ch.pieces, nb)) != WF_OK || (st = room(ch.cuts, nc)) != WF_OK ||
+      (st = room(ch.parts, np)) != WF_OK)
+    return st;
+  WF_HIP(hipMemcpyAsync(ch.pieces.p, all.data(), nb, hipMemcpyHostToDevice, s));
+  WF_HIP(hipMemcpyAsync(ch.cuts.p, cuts.data(), nc, hipMemcpyHostToDevice, s));
+  WF_HIP(hipMemcpyAsync(ch.parts.p, parts.data(), np, hipMemcpyHostToDevice, s));
   WF_HIP(hipStreamSynchronize(s));
   return WF_OK;
-}
-
-// The pieces of bin (on the fly: chunk) k.
-RowPieces pieces_of(const ChanOp& ch, int64_t k) {
-  RowPieces pc{(const WorkItem*)ch.pieces.p, {}, {}};
-  for (int c = 0; c < NCLS; ++c) {
-    pc.first[c] = ch.pc_0[(size_t)k * NCLS + c];
-    pc.n[c] = ch.pc_n[(size_t)k * NCLS + c];
-  }
-  return pc;
 }
 
 // Data weights and flags of one channel (Sect. 2): the rows that are built and the
@@ -1185,6 +1217,7 @@ struct Lane {
   float2* A;
   float* acc;
   void* gbuf;   // transient G values (on-the-fly channels)
+  int b;        // the branch: its sums may be replaced by a re-split, so they are not held here
   hipStream_t s;
   float* net_x;      // network inputs / outputs (on-the-fly channels with the network)
   float* net_pred;
@@ -1193,7 +1226,20 @@ struct Lane {
 Lane lane_of(wf_op* op, int b, hipStream_t caller) {
   Branch& B = op->br[b];
   return Lane{(float2*)B.X.p, (float2*)B.Y.p, (float2*)B.A.p, (float*)B.acc.p, B.gbuf.p,
-              b == 0 ? caller : B.s, (float*)B.net_x.p, (float*)B.net_pred.p};
+              b, b == 0 ? caller : B.s, (float*)B.net_x.p, (float*)B.net_pred.p};
+}
+
+// What the row kernels go over for bin (on the fly: chunk) k on lane L.
+RowPieces pieces_of(const wf_op* op, const ChanOp& ch, int64_t k, const Lane& L, bool scatter) {
+  RowPieces pc{(const WorkItem*)ch.pieces.p, {}, {}, (const CutItem*)ch.cuts.p + ch.cut_0[k],
+               (const CutPart*)ch.parts.p, scatter ? ch.cut_n[k] : 0, ch.cut_lines[k],
+               (double2*)op->br[L.b].sums.p};
+  const size_t at = (scatter ? ch.pc_n.size() / 2 : 0) + (size_t)k * NCLS;
+  for (int c = 0; c < NCLS; ++c) {
+    pc.first[c] = ch.pc_0[at + c];
+    pc.n[c] = ch.pc_n[at + c];
+  }
+  return pc;
 }
 
 Profiler* prof_of(wf_op* op, int k) { return op->capturing ? nullptr : &op->prof[k]; }
@@ -1335,7 +1381,7 @@ wf_status otf_bin_apply(wf_op* op, int kind, const Lane& L, const ChanOp& ch, in
     }
     // item value offsets are absolute: shift the base so that they land in the buffer
     const void* vals = (const char*)L.gbuf - (size_t)ch.ck_vbase[k] * b_v;
-    const RowPieces pc = pieces_of(ch, k);
+    const RowPieces pc = pieces_of(op, ch, k, L, kind != WF_APPLY_FORWARD);
     if (kind == WF_APPLY_FORWARD) {
       WF_HIP(launch_degrid(pc, (const uint32_t*)ch.meta.p, (const uint32_t*)ch.voff.p,
                            (const int32_t*)ch.perm.p, vals, store, L.X, (float2*)out, op->Kx,
@@ -1366,14 +1412,14 @@ wf_status bin_apply(wf_op* op, int kind, const Lane& L, const ChanOp& ch, int p,
   const float2* ct = ctab_of(op, ch, p);
   if (kind == WF_APPLY_FORWARD) {
     if ((st = layer_forward(op, L, in, wp, &pr, ct)) != WF_OK) return st;
-    WF_HIP(launch_degrid(pieces_of(ch, p), (const uint32_t*)ch.meta.p,
+    WF_HIP(launch_degrid(pieces_of(op, ch, p, L, false), (const uint32_t*)ch.meta.p,
                          (const uint32_t*)ch.voff.p, (const int32_t*)ch.perm.p, ch.vals.p,
                          op->opt.store, L.X, (float2*)out, op->Kx, op->Ky, L.s));
     return WF_OK;
   }
   const int mode = (real_out(kind) ? 2 : 0) + (first ? 0 : 1);
   if (from_vis(kind)) {
-    WF_HIP(launch_grid(pieces_of(ch, p), (const uint32_t*)ch.meta.p,
+    WF_HIP(launch_grid(pieces_of(op, ch, p, L, true), (const uint32_t*)ch.meta.p,
                        (const uint32_t*)ch.voff.p, (const int32_t*)ch.perm.p, ch.vals.p,
                        op->opt.store, (const float2*)in, L.Y, op->Kx, op->Ky,
                        bin_tile(op, ch, p), L.s));
@@ -1389,7 +1435,7 @@ wf_status bin_apply(wf_op* op, int kind, const Lane& L, const ChanOp& ch, int p,
                          op->Ky, L.s));
   } else {
     ProfScope ps(prof_of(op, 0), L.s);
-    WF_HIP(launch_gtg(pieces_of(ch, p), (const uint32_t*)ch.meta.p, (const uint32_t*)ch.voff.p,
+    WF_HIP(launch_gtg(pieces_of(op, ch, p, L, true), (const uint32_t*)ch.meta.p, (const uint32_t*)ch.voff.p,
                       ch.vals.p, op->opt.store, L.X, L.Y, op->Kx, op->Ky, bin_tile(op, ch, p),
                       L.s));
   }
@@ -1849,12 +1895,39 @@ void release_branch(Branch& B, bool own_stream) {
   dfree(B.A);
   dfree(B.acc);
   dfree(B.gbuf);
+  dfree(B.sums);
   dfree(B.net_x);
   dfree(B.net_pred);
   if (own_stream && B.s) (void)hipStreamDestroy(B.s);
   if (B.done) (void)hipEventDestroy(B.done);
   B.s = nullptr;
   B.done = nullptr;
+}
+
+// Bytes that a branch needs for the partial sums of a bin's cut items.
+size_t sum_bytes(const wf_op* op) {
+  int64_t n = 0;
+  for (const ChanOp& ch : op->chans) n = std::max(n, ch.sum_cells);
+  return sizeof(double2) * (size_t)n;
+}
+
+// Branches' buffers of partial sums brought to the size that the channels' pieces need: all of
+// them, or, where the memory for one is missing, none.
+wf_status grow_sums(wf_op* op) {
+  const size_t need = sum_bytes(op);
+  struct Fresh {
+    std::vector<DevBuf> b;
+    ~Fresh() {
+      for (DevBuf& x : b) dfree(x);
+    }
+  } fresh;
+  fresh.b.resize(op->br.size());
+  wf_status st;
+  for (size_t i = 0; i < op->br.size(); ++i)
+    if (need > op->br[i].sums.bytes && (st = dalloc(fresh.b[i], need)) != WF_OK) return st;
+  for (size_t i = 0; i < op->br.size(); ++i)
+    if (fresh.b[i].p) std::swap(fresh.b[i], op->br[i].sums);
+  return WF_OK;
 }
 
 // Allocate the grids (and streams) of branches [0, op->nbranch) and the accumulators the
@@ -1884,6 +1957,10 @@ wf_status ensure_branches(wf_op* op) {
     if (op->otf_bytes > B.gbuf.bytes) {
       dfree(B.gbuf);
       if ((st = dalloc(B.gbuf, op->otf_bytes)) != WF_OK) return st;
+    }
+    if (sum_bytes(op) > B.sums.bytes) {
+      dfree(B.sums);
+      if ((st = dalloc(B.sums, sum_bytes(op))) != WF_OK) return st;
     }
     if (op->net_otf && !B.net_x.p) {
       if ((st = dalloc(B.net_x, sizeof(float) * MLP_IN * NET_CHUNK)) != WF_OK) return st;
@@ -1950,12 +2027,10 @@ wf_status retune_channel(wf_op* op, int c, int32_t maxrows, const int8_t* tsh = 
     ~Undo() {
       ItemTables& now = ch;
       if (!done) std::swap(now, old);
-      dfree(old.work);
-      dfree(old.pieces);
+      for (DevBuf* b : {&old.work, &old.pieces, &old.cuts, &old.parts}) dfree(*b);
     }
   } undo{ch, ch};
-  ch.work = DevBuf{};
-  ch.pieces = DevBuf{};
+  ch.work = ch.pieces = ch.cuts = ch.parts = DevBuf{};
   ch.bin_tsh = ntsh;
   std::vector<uint8_t> trow(M);
   for (int64_t r = 0; r < M; ++r) trow[r] = (uint8_t)((meta[r] >> 16) & 0xff);
@@ -1966,6 +2041,7 @@ wf_status retune_channel(wf_op* op, int c, int32_t maxrows, const int8_t* tsh = 
   wf_status st = dalloc(ch.work, sizeof(WorkItem) * std::max<size_t>(wis.size(), 1));
   if (st != WF_OK) return st;
   if ((st = schedule_rows(ch, wis, meta.data(), nullptr)) != WF_OK) return st;
+  if ((st = grow_sums(op)) != WF_OK) return st;
   undo.done = true;
   if (ch.otf)   // the on-the-fly value pass finds each row's item through row_wi
     WF_HIP(hipMemcpy(ch.row_wi.p, row_wi.data(), sizeof(int32_t) * M, hipMemcpyHostToDevice));
@@ -1982,7 +2058,7 @@ wf_status retune_channel(wf_op* op, int c, int32_t maxrows, const int8_t* tsh = 
 // The fused G^dag G launches of bin p alone on lane L (autotuning: X is read as it is,
 // Y is added into).
 wf_status bin_gtg(wf_op* op, const ChanOp& ch, int p, const Lane& L) {
-  WF_HIP(launch_gtg(pieces_of(ch, p), (const uint32_t*)ch.meta.p, (const uint32_t*)ch.voff.p,
+  WF_HIP(launch_gtg(pieces_of(op, ch, p, L, true), (const uint32_t*)ch.meta.p, (const uint32_t*)ch.voff.p,
                     ch.vals.p, op->opt.store, L.X, L.Y, op->Kx, op->Ky, bin_tile(op, ch, p),
                     L.s));
   return WF_OK;

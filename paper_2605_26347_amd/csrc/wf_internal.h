@@ -47,11 +47,19 @@ struct WorkItem {
   int32_t row0;   // first sorted row
   int32_t nrows;  // rows in this item
   int32_t u0, v0; // window origin
-  int32_t bin;
+  int32_t bin;    // (of a piece: where its sums meet those of its item's others, see CutItem)
   int32_t box;    // window-local bounding box of the rows' patches: u0 | v0 << 8 |
                   // width << 16 | height << 24
 };
 static_assert(sizeof(WorkItem) == 32, "WorkItem layout");
+
+// Grid lines (128 bytes: 2^GRID_L columns x 2^(4 - GRID_L) rows of complex cells) that a box can
+// touch, wherever its origin lies.
+__host__ __device__ inline int32_t box_lines(int32_t box) {
+  const int w = (int)(((uint32_t)box >> 16) & 0xff), h = (int)((uint32_t)box >> 24);
+  constexpr int H = 4 - GRID_L;
+  return (((w + 2 * (1 << GRID_L) - 2) >> GRID_L)) * ((h + 2 * (1 << H) - 2) >> H);
+}
 
 // Patch-size classes of the row kernels: class c covers T*T <= 64 * cls_taps(c) taps,
 // i.e. patch sides up to 11, 15, 21, 27, 31, 37.
@@ -97,10 +105,25 @@ __host__ __device__ inline uint32_t pack_meta(int lu0, int lv0, int T) {
 __host__ __device__ constexpr int class_mk(int c) {
   return c == 0 ? 2 : c == 1 ? 4 : c == 2 ? 7 : c == 3 ? 12 : c == 4 ? 16 : 22;
 }
-// What a launch of the row kernels goes over: of each class the first piece and their count.
+// A work item that was cut into pieces: its window origin and box, and where its pieces' boxes
+// lie in the branch's buffer of partial sums (a slot is a cell of the buffer: real and imaginary
+// part in FP64).  A piece of a whole item has slot -1 and adds into Y by itself.
+struct CutItem {
+  int32_t u0, v0, box;
+  int32_t part0, nparts;
+};
+struct CutPart {
+  int32_t slot, box;
+};
+// What a launch of the row kernels goes over: of each class the first piece and their count,
+// the cut items among them, and the buffer where the pieces of those meet.
 struct RowPieces {
   const WorkItem* items;
   int32_t first[NCLS], n[NCLS];
+  const CutItem* cuts;
+  const CutPart* parts;
+  int32_t ncuts, cut_lines;   // cut items; grid lines under the largest of their boxes
+  double2* sums;
 };
 // One (channel, bin) layer of a sweep: its work grids, pruning masks, row data of G,
 // w-layer centroid, channel, and the offset of its channel's visibilities.  A sweep
@@ -227,9 +250,15 @@ struct ItemTables {
   int64_t nwork = 0;
   DevBuf work;
   // what the row kernels are launched on: the items of `work` cut into pieces (schedule_rows),
-  // largest first, per (bin, class), or per (chunk, class) on the fly: first piece, count
+  // largest first, per (bin, class), or per (chunk, class) on the fly: first piece, count; all
+  // of those for de-gridding, then all of those for the kernels that scatter
   DevBuf pieces;
   std::vector<int32_t> pc_0, pc_n;
+  // the items that were cut, per bin (chunk): first, count, grid lines of the largest box; their
+  // pieces' slots and boxes; and the cells that the largest bin's pieces need in a branch
+  DevBuf cuts, parts;
+  std::vector<int32_t> cut_0, cut_n, cut_lines;
+  int64_t sum_cells = 0;
 };
 
 struct ChanOp : ItemTables {
@@ -300,6 +329,7 @@ struct Branch {
   hipEvent_t done = nullptr;
   DevBuf X, Y, A, acc;
   DevBuf gbuf;   // transient G values of on-the-fly channels
+  DevBuf sums;   // partial sums of a bin's cut items (CutItem)
   DevBuf net_x, net_pred;   // network inputs and outputs (on-the-fly with the network)
 };
 

@@ -115,15 +115,83 @@ static void covered(const ChanOp& ch) {
   for (int64_t i = 0; i < ch.nwork; ++i)
     for (int r = 0; r < wk[i].nrows; ++r) ++hit[wk[i].row0 + r];
   for (int h : hit) CHECK(h == 1);
-  std::fill(hit.begin(), hit.end(), 0);
   const WorkItem* pc = (const WorkItem*)ch.pieces.p;
-  for (size_t k = 0; k < ch.pc_n.size(); ++k) {
-    if (ch.pc_n[k] == 0) continue;
-    CHECK(held(ch.pieces, sizeof(WorkItem) * (ch.pc_0[k] + ch.pc_n[k])));
-    for (int i = ch.pc_0[k]; i < ch.pc_0[k] + ch.pc_n[k]; ++i)
-      for (int r = 0; r < pc[i].nrows; ++r) ++hit[pc[i].row0 + r];
+  const size_t nk = ch.pc_n.size() / 2;   // de-gridding's, then the scattering kernels'
+  for (size_t use = 0; use < 2; ++use) {
+    std::fill(hit.begin(), hit.end(), 0);
+    for (size_t k = use * nk; k < (use + 1) * nk; ++k) {
+      if (ch.pc_n[k] == 0) continue;
+      CHECK(held(ch.pieces, sizeof(WorkItem) * (ch.pc_0[k] + ch.pc_n[k])));
+      for (int i = ch.pc_0[k]; i < ch.pc_0[k] + ch.pc_n[k]; ++i)
+        for (int r = 0; r < pc[i].nrows; ++r) ++hit[pc[i].row0 + r];
+    }
+    for (int h : hit) CHECK(h == 1);
   }
-  for (int h : hit) CHECK(h == 1);
+}
+
+// Each cut item is covered by its pieces: their boxes inside its box, their slots apart and inside
+// the buffer, and nothing but pieces of whole items adds into the grid by itself.
+static void cut_items_meet(const ChanOp& ch) {
+  const WorkItem* wk = (const WorkItem*)ch.work.p;
+  const WorkItem* pc = (const WorkItem*)ch.pieces.p;
+  const CutItem* cuts = (const CutItem*)ch.cuts.p;
+  const CutPart* parts = (const CutPart*)ch.parts.p;
+  struct B {
+    int u0, v0, w, h;
+  };
+  auto box = [](int32_t b) {
+    const uint32_t x = (uint32_t)b;
+    return B{(int)(x & 255), (int)((x >> 8) & 255), (int)((x >> 16) & 255), (int)(x >> 24)};
+  };
+  const size_t nk = ch.pc_n.size() / 2;
+  int64_t largest = 0;
+  for (size_t bin = 0; bin < ch.cut_n.size(); ++bin) {
+    // pieces of the bin by slot; the items that they come from
+    std::vector<std::pair<int, const WorkItem*>> by_slot;
+    size_t whole = 0;
+    for (int c = 0; c < NCLS; ++c)
+      for (int i = 0; i < ch.pc_n[nk + bin * NCLS + c]; ++i) {
+        const WorkItem& p = pc[ch.pc_0[nk + bin * NCLS + c] + i];
+        if (p.bin >= 0) by_slot.push_back({p.bin, &p});
+        else ++whole;
+      }
+    std::sort(by_slot.begin(), by_slot.end());
+    size_t at = 0;
+    int64_t cells = 0, items = 0;
+    CHECK(held(ch.cuts, sizeof(CutItem) * (ch.cut_0[bin] + ch.cut_n[bin])));
+    for (int i = 0; i < ch.cut_n[bin]; ++i) {
+      const CutItem& it = cuts[ch.cut_0[bin] + i];
+      const B ib = box(it.box);
+      CHECK(it.nparts > 1 && held(ch.parts, sizeof(CutPart) * (it.part0 + it.nparts)));
+      CHECK(box_lines(it.box) <= ch.cut_lines[bin]);
+      int rows = 0;
+      const WorkItem* from = nullptr;
+      for (int j = 0; j < it.nparts; ++j, ++at) {
+        const CutPart& q = parts[it.part0 + j];
+        CHECK(at < by_slot.size() && by_slot[at].first == q.slot && q.slot == cells);
+        const WorkItem& p = *by_slot[at].second;
+        CHECK(p.box == q.box && p.u0 == it.u0 && p.v0 == it.v0);
+        const B b = box(q.box);
+        CHECK(b.u0 >= ib.u0 && b.v0 >= ib.v0 && b.u0 + b.w <= ib.u0 + ib.w &&
+              b.v0 + b.h <= ib.v0 + ib.h);
+        for (int64_t k = 0; k < ch.nwork; ++k)
+          if (p.row0 >= wk[k].row0 && p.row0 < wk[k].row0 + wk[k].nrows) {
+            CHECK(!from || from == &wk[k]);
+            from = &wk[k];
+          }
+        rows += p.nrows;
+        cells += (int64_t)b.w * b.h;
+      }
+      CHECK(from && rows == from->nrows && it.box == from->box);
+      ++items;
+    }
+    CHECK(at == by_slot.size());
+    int64_t in_bin = 0;
+    for (int64_t k = 0; k < ch.nwork; ++k) in_bin += wk[k].bin == (int)bin;
+    CHECK(items + (int64_t)whole == in_bin);
+    largest = std::max(largest, cells);
+  }
+  CHECK(largest == ch.sum_cells);
 }
 
 // A re-split that runs out of memory, at each of its allocations, leaves the split in use.
@@ -132,7 +200,12 @@ static void failed_resplit() {
   fill(op, {3000, 70, 1, 500});
   ChanOp& ch = op.chans[0];
   covered(ch);
+  cut_items_meet(ch);
+  CHECK(ch.cut_n[0] > 0);
+  op.br.resize(2);
+  CHECK(grow_sums(&op) == WF_OK);
   const ItemTables was = ch;
+  const void* sums = op.br[1].sums.p;
   const std::vector<uint32_t> meta((uint32_t*)ch.meta.p, (uint32_t*)ch.meta.p + ch.nrows);
   const std::vector<int8_t> wide(ch.P, 1);
   const size_t blocks = g_live.size();
@@ -152,18 +225,53 @@ static void failed_resplit() {
     CHECK(ch.work.p == was.work.p && ch.pieces.p == was.pieces.p);
     CHECK(ch.pc_0 == was.pc_0 && ch.pc_n == was.pc_n && ch.nwork == was.nwork);
     CHECK(ch.cls_wi0 == was.cls_wi0 && ch.cls_nwi == was.cls_nwi);
+    CHECK(op.br[0].sums.bytes == op.br[1].sums.bytes && op.br[1].sums.p == sums);
+    CHECK(sizeof(double2) * ch.sum_cells <= op.br[1].sums.bytes);
     CHECK(ch.bin_tsh == was.bin_tsh && ch.max_rows == was.max_rows);
     CHECK(std::equal(meta.begin(), meta.end(), (uint32_t*)ch.meta.p));
     covered(ch);
   }
-  CHECK(fails >= 2);
+  CHECK(fails >= 4);
   CHECK(ch.max_rows == 256 && ch.bin_tsh == wide);
   CHECK(g_live.size() == blocks);
   covered(ch);
+  cut_items_meet(ch);
+  CHECK(held(op.br[0].sums, sizeof(double2) * ch.sum_cells));
+  CHECK(held(op.br[1].sums, sizeof(double2) * ch.sum_cells));
+}
+
+// A lane taken before a re-split launches on the buffers that the re-split left.
+static void lane_after_resplit() {
+  wf_op op;
+  fill(op, {200, 70, 1, 100});
+  ChanOp& ch = op.chans[0];
+  op.br.resize(1);
+  CHECK(grow_sums(&op) == WF_OK);
+  const Lane L = lane_of(&op, 0, nullptr);
+  const size_t was = op.br[0].sums.bytes;
+  const std::vector<int8_t> wide(ch.P, 1);
+  CHECK(retune_channel(&op, 0, 1024, wide.data()) == WF_OK);
+  CHECK(op.br[0].sums.bytes > was);
+  const RowPieces pc = pieces_of(&op, ch, 0, L, true);
+  CHECK(pc.sums == op.br[0].sums.p && g_live.count(pc.sums));
+  CHECK(g_live.count((void*)pc.items) && pc.cuts == (const CutItem*)ch.cuts.p);
+}
+
+// Few rows, rows in one item, items at the pieces' smallest size, and many items.
+static void pieces_of_items() {
+  for (const std::vector<int>& rows : {std::vector<int>{1}, {64}, {65}, {1025}, {0, 63, 64, 129},
+                                       {5000, 1, 1, 700, 64, 65, 2000, 333}}) {
+    wf_op op;
+    fill(op, rows);
+    covered(op.chans[0]);
+    cut_items_meet(op.chans[0]);
+  }
 }
 
 int main() {
+  pieces_of_items();
   failed_resplit();
+  lane_after_resplit();
   std::printf("host split ok\n");
   return 0;
 }
