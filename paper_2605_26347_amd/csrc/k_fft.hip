@@ -301,7 +301,7 @@ __global__ __launch_bounds__(RowPlan<N>::WG) __attribute__((amdgpu_waves_per_eu(
     // branch per pixel would keep the loads of different pixels from overlapping)
     constexpr int B = E / R1;
     float2 zr[B][R1 / 2];
-    if (ctab) {
+    if (N >= SERIES_N && ctab) {
       const ChirpRow cr = chirp_row(jr, NX, ny, cell, wp, syj);
 #pragma unroll
       for (int b = 0; b < B; ++b)
@@ -399,7 +399,7 @@ __global__ __launch_bounds__(RowPlan<N>::WG) __attribute__((amdgpu_waves_per_eu(
   for (int b = 0; b < E / R3; ++b) {
     // one group's modulations at a time (registers), one uniform branch per group
     float2 zr[R3 / 2];
-    if (ctab) {
+    if (N >= SERIES_N && ctab) {
 #pragma unroll
       for (int r = 0; r < R3; ++r)
         if (kept<R3>(r)) {

@@ -402,6 +402,20 @@ wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint
   return WF_OK;
 }
 
+// Whether a w-layer's modulation (eq. 6) is formed from its column table by the FP32 series of the
+// row FFT passes instead of pixel by pixel in FP64.  The series hold where r2 = l^2 + m^2 <= 1/100
+// over the image and the phase beyond the quadratic term, 2 pi |w_p| |n - 1 + r2/2|, stays within
+// 1/4 radian.  Only rows of SERIES_N points and more take them, which are bound by instruction
+// issue: their modulation is off by 7.0e-8 (rms, against 64 bits), the FP64 form's by 4.9e-8, and
+// short rows have no time to gain by it (ten 512^2 iterations 1477 and 1486 us).
+bool series_modulation(const wf_image_shape& im, int Kx, double wp) {
+  if (Kx < SERIES_N) return false;
+  const double hl = 0.5 * im.nx * im.cell_rad, hm = 0.5 * im.ny * im.cell_rad;
+  const double r2 = hl * hl + hm * hm;
+  const double dl = std::fabs(-r2 / (1.0 + std::sqrt(1.0 - r2)) + 0.5 * r2);
+  return r2 <= 0.01 && 2.0 * M_PI * std::fabs(wp) * dl <= 0.25;
+}
+
 // Data weights and flags of one channel (Sect. 2): the rows that are built and the
 // weight of each.
 struct RowSel {
@@ -1158,17 +1172,12 @@ wf_status build_channel(wf_op* op, int c, const double* uvw, int64_t M, double f
   in.mem_h_bytes = holo ? (double)b_v * ch.h_values + (double)ch.htiles.bytes : 0.0;
   in.nflagged = ch.nflag;
   {
-    // column tables of the w-layer modulations (eq. 6): the series forms of the row FFT
-    // passes hold where r2 = l^2 + m^2 <= 1/100 over the image and the phase beyond the
-    // quadratic term, 2 pi |w_p| |n - 1 + r2/2|, stays within 1/4 radian
+    // column tables of the w-layer modulations (eq. 6)
     const int nx = op->shape.nx;
-    const double hl = 0.5 * nx * op->shape.cell_rad, hm = 0.5 * op->shape.ny * op->shape.cell_rad;
-    const double r2 = hl * hl + hm * hm;
-    const double dl = std::fabs(-r2 / (1.0 + std::sqrt(1.0 - r2)) + 0.5 * r2);
     ch.cfast.assign(ch.P, 0);
     bool any = false;
     for (int p = 0; p < ch.P; ++p) {
-      ch.cfast[p] = r2 <= 0.01 && 2.0 * M_PI * std::fabs(ch.centroids[p]) * dl <= 0.25;
+      ch.cfast[p] = series_modulation(op->shape, op->Kx, ch.centroids[p]);
       any = any || ch.cfast[p];
     }
     if (any) {

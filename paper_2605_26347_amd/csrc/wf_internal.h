@@ -161,6 +161,9 @@ struct ColPrune {
 // Columns per workgroup of the column passes for a column length of Ky.
 inline int col_width_for(int Ky) { return Ky <= 32 ? 16 : Ky <= 1024 ? 4 : 16384 / Ky; }
 
+// Shortest row that may take the modulation's column table and FP32 series (series_modulation).
+constexpr int SERIES_N = 2048;
+
 // Radices of the first two passes of a transform of N >= 64 points (the third is N / (R1 R2)).
 __host__ __device__ constexpr int fft_r1(int N) {
   return N >= 8192 ? 32 : N >= 1024 ? 16 : N >= 128 ? 8 : 4;

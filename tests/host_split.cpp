@@ -1,5 +1,5 @@
-// CPU driver of the work-item tables (built and run by tests/test_host_split.py): the C ABI's
-// source with the device memory calls replaced by host memory, whose allocations can be made
+// CPU driver of host decisions and of the work-item tables (built and run by
+// tests/test_host_split.py): the C ABI's source with the device memory calls replaced by host memory, whose allocations can be made
 // to fail.  No kernel is launched.
 #include "../paper_2605_26347_amd/csrc/wf_abi.cpp"
 
@@ -268,7 +268,19 @@ static void pieces_of_items() {
   }
 }
 
+// The FP32 series of the modulation serve the long rows only, and there within their bounds.
+static void modulation_form() {
+  for (int nx = 8; nx <= 8192; nx *= 2)
+    for (int ny : {8, 512, 8192}) {
+      const wf_image_shape small{nx, ny, 1e-5};
+      CHECK(series_modulation(small, 2 * nx, 100.0) == (nx >= 1024));
+      CHECK(!series_modulation(small, 2 * nx, 1e11));
+    }
+  CHECK(!series_modulation(wf_image_shape{1024, 1024, 2e-4}, 2048, 0.0));
+}
+
 int main() {
+  modulation_form();
   pieces_of_items();
   failed_resplit();
   lane_after_resplit();
