@@ -120,36 +120,40 @@ __device__ __forceinline__ void hval4(const void* __restrict__ v, int64_t i, flo
   }
 }
 
-// Y += H X over the active tiles of one bin.  Workgroup (tile, part) streams the stencil
-// rows [part D / parts, (part + 1) D / parts) of its tile, the X cells they reach (tile +
-// rows - 1 rows of tile + 2R cells, wrapped on the periodic grid) staged in LDS as two
-// planes.  Thread t owns the four consecutive cells 4t .. 4t + 3 of the tile (one vector load
-// of stencil values per offset); tile * tile == 4 * 256.  The stream from HBM is what bounds
-// it: HU vector loads are in flight per thread, and along a stencil row the four cells' X
-// values slide by one cell per offset, so an offset reads two floats of LDS.
-// A bin of a small field has a few hundred tiles, fewer than the chip holds workgroups: its
-// tiles are cut into parts (launch_happly) that add their sums atomically; a single part
-// adds plainly.  512^2 field, 8M rows, 2 bins of 455 tiles: 415 us per bin in one part with
-// one load in flight, 214 us (3.9 TB/s of stencil values, what a plain sum over them reads at) now.
+// Y += H X over the active tiles of one bin.  A workgroup owns a tile, or one of gridDim.y = 4
+// bands of its rows (bits: log2 of gridDim.y), and cuts the stencil's rows into equal shares, one
+// to every 256 (64) threads.  The X cells that it reaches (its rows + D - 1 rows of tile + 2R
+// cells, wrapped on the periodic grid) are staged in LDS as two planes.  Thread t of a share owns
+// the four consecutive cells 4t .. 4t + 3 of the band (one vector load of stencil values per
+// offset); tile * tile == 4 * 256.  The stream from HBM is what bounds it: HU vector loads are in
+// flight per thread, and along a stencil row the four cells' X values slide by one cell per
+// offset, so an offset reads two floats of LDS.
+// A bin of a small field has a few hundred tiles, fewer than fill the chip with 256 threads each
+// (launch_happly).  The sums of a workgroup's shares meet in LDS in their order and every cell of
+// Y has one owner, so that an apply gives the same bits every time.  Applies, two bins each, with
+// one share and one load in flight / workgroups of 256 threads that add to Y atomically / now:
+// 512^2 and 8M rows (455 tiles a bin) 975 / 535 / 454 us, 256^2 397 / 202 / 146, 64^2 257 / 75 /
+// 68 us.
 constexpr int HU = 4;
 
 template <int STORE>
-__global__ __launch_bounds__(256) void k_happly(const HTile* __restrict__ ht,
+__global__ __launch_bounds__(1024) void k_happly(const HTile* __restrict__ ht,
                                                 const void* __restrict__ hv,
                                                 const float2* __restrict__ X,
                                                 float2* __restrict__ Y, int tiles_x, int tsh,
-                                                int Kx, int Ky) {
+                                                int bits, int Kx, int Ky) {
   extern __shared__ float xw[];
   const HTile t = ht[blockIdx.x];
-  const int parts = gridDim.y;
-  const int dv0 = t.D * (int)blockIdx.y / parts, dv1 = t.D * ((int)blockIdx.y + 1) / parts;
-  if (dv0 == dv1) return;
+  const int S = 256 >> bits, G = blockDim.x >> (8 - bits);   // threads of a share, shares
+  const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> (8 - bits));
+  const int tid = threadIdx.x & (S - 1);
+  const int dv0 = t.D * grp / G, dv1 = t.D * (grp + 1) / G;   // the share's stencil rows
   const int tile = 1 << tsh, ncell = tile * tile;
   const int tu = t.tile % tiles_x, tv = t.tile / tiles_x;
-  const int R = (t.D - 1) / 2, W = tile + 2 * R, H = tile + (dv1 - dv0) - 1;
+  const int R = (t.D - 1) / 2, W = tile + 2 * R, H = (tile >> bits) + t.D - 1;
   float* xr = xw;
   float* xi = xw + W * H;
-  const int u0 = tu * tile - R, v0 = tv * tile - R + dv0;
+  const int u0 = tu * tile - R, v0 = tv * tile - R + (int)blockIdx.y * (tile >> bits);
   for (int i = threadIdx.x; i < W * H; i += blockDim.x) {
     const int wv = i / W, wu = i - wv * W;
     const float2 x = X[grid_index((v0 + wv) & (Ky - 1), (u0 + wu) & (Kx - 1), Ky)];
@@ -157,12 +161,13 @@ __global__ __launch_bounds__(256) void k_happly(const HTile* __restrict__ ht,
     xi[i] = x.y;
   }
   __syncthreads();
-  const int c0 = 4 * threadIdx.x;
+  const int c0 = 4 * (tid + (int)blockIdx.y * S);
   const int cv = c0 >> tsh, cu = c0 & (tile - 1);
+  const int bv = cv - (int)blockIdx.y * (tile >> bits);   // the row in the band
   float ar[4] = {0.f, 0.f, 0.f, 0.f}, ai[4] = {0.f, 0.f, 0.f, 0.f};
   for (int dv = dv0; dv < dv1; ++dv) {
-    const float* rr = xr + (cv + dv - dv0) * W + cu;
-    const float* ri = xi + (cv + dv - dv0) * W + cu;
+    const float* rr = xr + (bv + dv) * W + cu;
+    const float* ri = xi + (bv + dv) * W + cu;
     const int64_t rowbase = t.voff + (int64_t)dv * t.D * ncell + c0;
     float wr[3 + HU], wi[3 + HU];
 #pragma unroll
@@ -199,16 +204,27 @@ __global__ __launch_bounds__(256) void k_happly(const HTile* __restrict__ ht,
     for (; du + HU <= t.D; du += HU) offsets(du, std::integral_constant<int, HU>{});
     for (; du < t.D; ++du) offsets(du, std::integral_constant<int, 1>{});
   }
+  if (G > 1) {
+    // shares 1 .. G - 1 through LDS (over the X cells, which all have been read)
+    __syncthreads();
+    float4* sh = reinterpret_cast<float4*>(xw);
+    if (grp > 0) {
+      sh[(grp - 1) * 2 * S + tid] = make_float4(ar[0], ar[1], ar[2], ar[3]);
+      sh[(grp - 1) * 2 * S + S + tid] = make_float4(ai[0], ai[1], ai[2], ai[3]);
+    }
+    __syncthreads();
+    if (grp > 0) return;
+    for (int g = 0; g < G - 1; ++g) {
+      const float4 r = sh[g * 2 * S + tid], i = sh[g * 2 * S + S + tid];
+      ar[0] += r.x, ar[1] += r.y, ar[2] += r.z, ar[3] += r.w;
+      ai[0] += i.x, ai[1] += i.y, ai[2] += i.z, ai[3] += i.w;
+    }
+  }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     float2* p = Y + grid_index(tv * tile + cv, tu * tile + cu + j, Ky);
-    if (parts > 1) {
-      unsafeAtomicAdd(&p->x, ar[j]);
-      unsafeAtomicAdd(&p->y, ai[j]);
-    } else {
-      const float2 y = *p;
-      *p = make_float2(y.x + ar[j], y.y + ai[j]);
-    }
+    const float2 y = *p;
+    *p = make_float2(y.x + ar[j], y.y + ai[j]);
   }
 }
 
@@ -251,17 +267,21 @@ hipError_t launch_happly(const HTile* ht, int ntiles, int Dmax, const void* hv, 
                          const float2* X, float2* Y, int tiles_x, int tsh, int Kx, int Ky,
                          hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-  // parts: enough workgroups for eight per compute unit (2048), none below four stencil
-  // rows on the widest tile (each part stages the tile's own X rows again)
-  const int parts = std::max(1, std::min((2048 + ntiles - 1) / ntiles, Dmax / 4));
-  const int W = (1 << tsh) + (Dmax - 1);
-  const int H = (1 << tsh) + (Dmax + parts - 1) / parts - 1;
-  const size_t lds = 2 * sizeof(float) * (size_t)W * H;
+  // Enough threads for 2048 times 256 (eight such shares per compute unit): up to four shares of
+  // 256 in a workgroup, none below four stencil rows on the widest tile; with far fewer tiles than
+  // that fills, four bands of 64-thread shares (455 tiles: 480 us an apply in bands, 454 without).
+  const int want = (2048 + ntiles - 1) / ntiles;
+  const bool bands = want > 6;
+  const int G = bands ? (want > 8 && Dmax >= 32 ? 16 : Dmax >= 16 ? 8 : 4)
+                      : std::max(1, std::min(want >= 3 ? 4 : want, Dmax / 4));
+  const int bits = bands ? 2 : 0, S = 256 >> bits;
+  const int W = (1 << tsh) + (Dmax - 1), H = ((1 << tsh) >> bits) + (Dmax - 1);
+  const size_t lds = std::max(2 * sizeof(float) * (size_t)W * H, (size_t)(G - 1) * S * 32);
   hipError_t e;
 #define WF_H(ST)                                                                             \
   if ((e = lds_limit(k_happly<ST>, lds)) != hipSuccess) return e;                            \
-  hipLaunchKernelGGL(k_happly<ST>, dim3(ntiles, parts), dim3(256), lds, s, ht, hv, X, Y,     \
-                     tiles_x, tsh, Kx, Ky);
+  hipLaunchKernelGGL(k_happly<ST>, dim3(ntiles, 1 << bits), dim3(S * G), lds, s, ht, hv, X,  \
+                     Y, tiles_x, tsh, bits, Kx, Ky);
   switch (store) {
     case WF_STORE_F32: WF_H(WF_STORE_F32) break;
     case WF_STORE_F16: WF_H(WF_STORE_F16) break;
