@@ -221,9 +221,9 @@ __device__ __forceinline__ void scatter_patch(const Run& r, const Slots<MK>& sl,
   }
 }
 
-__device__ __forceinline__ void window_zero(double* acc, const Box& bx) {
+__device__ __forceinline__ void window_zero(double* acc, const Box& bx, int tid) {
   const int n = bx.w * bx.h;
-  for (int c = threadIdx.x; c < 2 * n; c += GNT) acc[c] = 0.0;
+  for (int c = tid; c < 2 * n; c += GNT) acc[c] = 0.0;
 }
 // Goes over the cells of a box line by line of the grid's layout: 32 lanes on the 32 floats of
 // one 128-byte line (2^GRID_L columns x 2^(4 - GRID_L) rows of complex cells), lines first, first
@@ -233,16 +233,17 @@ __device__ __forceinline__ void window_zero(double* acc, const Box& bx) {
 // segment twice.
 template <typename ON>
 __device__ __forceinline__ void each_line(const Box& bx, int u0, int v0, int Kx, int Ky,
-                                          float2* __restrict__ Y, int first, int step, ON&& on) {
+                                          float2* __restrict__ Y, int tid, int first, int step,
+                                          ON&& on) {
   constexpr int L = GRID_L, H = 4 - GRID_L;
   const int ub = u0 + bx.u0, vb = v0 + bx.v0;          // grid origin of the box (unwrapped)
   const int fu = ub & ((1 << L) - 1), fv = vb & ((1 << H) - 1);
   const int nx = (fu + bx.w + (1 << L) - 1) >> L, ny = (fv + bx.h + (1 << H) - 1) >> H;
   const float inv = __builtin_amdgcn_rcpf((float)nx);
-  const int part = threadIdx.x & 1, cell = (threadIdx.x >> 1) & 15;
+  const int part = tid & 1, cell = (tid >> 1) & 15;
   const int cu = (cell & ((1 << L) - 1)) - fu, cv = (cell >> L) - fv;
   float* __restrict__ Yp = reinterpret_cast<float*>(Y) + part;
-  for (int c = first + (threadIdx.x >> 5); c < nx * ny; c += step) {
+  for (int c = first + (tid >> 5); c < nx * ny; c += step) {
     int ly, lx;
     tap_ab(c, nx, inv, ly, lx);
     const int a = (ly << H) + cv, b = (lx << L) + cu;
@@ -254,9 +255,9 @@ __device__ __forceinline__ void each_line(const Box& bx, int u0, int v0, int Kx,
 
 // Add the box into Y (untouched cells skipped).
 __device__ __forceinline__ void window_flush(const double* acc, const Box& bx, int u0, int v0,
-                                             int Kx, int Ky, float2* __restrict__ Y) {
-  const double* __restrict__ plane = acc + (threadIdx.x & 1) * (bx.w * bx.h);
-  each_line(bx, u0, v0, Kx, Ky, Y, 0, GNT / 32, [&](int a, int b, int, auto&& at) {
+                                             int Kx, int Ky, float2* __restrict__ Y, int tid) {
+  const double* __restrict__ plane = acc + (tid & 1) * (bx.w * bx.h);
+  each_line(bx, u0, v0, Kx, Ky, Y, tid, 0, GNT / 32, [&](int a, int b, int, auto&& at) {
     const float v = (float)plane[a * bx.w + b];
     if (v != 0.f) unsafeAtomicAdd(at(), v);
   });
@@ -264,9 +265,9 @@ __device__ __forceinline__ void window_flush(const double* acc, const Box& bx, i
 
 // Store the box where the pieces of its item meet.
 __device__ __forceinline__ void window_store(const double* acc, const Box& bx,
-                                             double2* __restrict__ sums) {
+                                             double2* __restrict__ sums, int tid) {
   const int n = bx.w * bx.h;
-  for (int c = threadIdx.x; c < n; c += GNT) sums[c] = make_double2(acc[c], acc[n + c]);
+  for (int c = tid; c < n; c += GNT) sums[c] = make_double2(acc[c], acc[n + c]);
 }
 
 // The cut items' sums into Y: a workgroup adds up the pieces of eight of an item's lines in
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(32 * MERGE_LINES) void k_merge(const CutItem* __res
                                                             int Ky) {
   const CutItem it = cuts[blockIdx.x];
   const Box bx = box_of(it.box);
-  each_line(bx, it.u0, it.v0, Kx, Ky, Y, blockIdx.y * MERGE_LINES, gridDim.y * MERGE_LINES,
+  each_line(bx, it.u0, it.v0, Kx, Ky, Y, threadIdx.x, blockIdx.y * MERGE_LINES, gridDim.y * MERGE_LINES,
             [&](int a, int b, int part, auto&& at) {
               const double* __restrict__ src = reinterpret_cast<const double*>(sums) + part;
               double s = 0.0;
@@ -312,6 +313,7 @@ __global__ __launch_bounds__(32 * MERGE_LINES) void k_merge(const CutItem* __res
 //           they have, which saves a copy of it (MK to 2 MK).
 //   depth:  rows of values in flight.
 //   waves:  wavefronts per SIMD that the compiler has to allow.
+//   ahead:  the next run's grid values are gathered while the current run is reduced.
 // Each form is the one with the most workgroups that needs no scratch memory (one that does
 // runs two to three times slower), and among those the faster.  Fused, FP16, us per launch
 // (2048^2 with four channels of 1 to 3M rows; 4096^2 with 30M rows), before with one workgroup
@@ -320,14 +322,22 @@ __global__ __launch_bounds__(32 * MERGE_LINES) void k_merge(const CutItem* __res
 // 120 -> 96.  MK 12 keeps its run accumulator in FP16, where it fits: without it 83 for 76.
 // Fused MK 22 of FP32 and BF16 needs 164 registers.  De-gridding MK 22 in FP32 fits 128 by its
 // late loads, which cost more than the second workgroup gives (37 us for 33).
+// The persistent kernels of a sweep need a few registers more for their queue, so three of FP16
+// fused take one workgroup less than above (MK 4, 7) or no run accumulator (MK 12).  A sweep of
+// four channels (2048^2, 8M rows; fused / de-gridding / gridding), with these forms but no
+// bound on the registers and now: FP16 24.4 / 14.2 / 15.5 -> 20.8 / 13.6 / 15.5 ms, FP32 24.9 /
+// 16.5 / 17.7 -> 23.3 / 15.9 / 17.1, BF16 23.3 / 14.5 / 15.7 -> 22.4 / 14.6 / 15.6.
 struct RowForm {
   bool direct;
   int depth, waves;
+  bool ahead = false;
 };
-constexpr RowForm row_form(int store, int mk, int mode) {
+constexpr RowForm row_form(int store, int mk, int mode, bool sweep = false) {
   const bool f16 = store == WF_STORE_F16, f32 = store == WF_STORE_F32;
   const bool thin = f16 || (!f32 && mode != 0);   // the classes below fit one workgroup more
-  if (mk <= 4) return {false, 4, f32 && mode == 0 ? 4 : !f32 && thin && mode != 2 ? 8 : 6};
+  if (sweep && f16 && mode == 0 && mk > 2 && mk <= 12)
+    return {mk == 12, mk == 4 ? 4 : 2, mk == 4 ? 6 : 4, mk != 12};
+  if (mk <= 4) return {false, 4, f32 && mode == 0 ? 4 : !f32 && thin && mode != 2 ? 8 : 6, true};
   if (mk == 7) return {false, 2, thin ? 6 : 4};
   if (mk == 12) return {!f16, 2, 4};
   if (mk == 16) return {true, 1, 4};
@@ -335,33 +345,33 @@ constexpr RowForm row_form(int store, int mk, int mode) {
   return {true, 1, f16 || mode == 2 ? 4 : 2};
 }
 
-// An item's words in scalar registers.  The item tables do not change during a launch, but beside
-// plain stores the compiler does not know that and loads them per lane, each time with a wait
-// (the fused kernels 10% slower): so they are read as constant memory.
-__device__ __forceinline__ WorkItem read_item(const WorkItem* wi) {
-  const auto* w = (const __attribute__((address_space(4))) int32_t*)(uintptr_t)wi;
-  WorkItem r;
-  r.voff = (int64_t)((uint64_t)(uint32_t)w[0] | (uint64_t)(uint32_t)w[1] << 32);
-  r.row0 = w[2];
-  r.nrows = w[3];
-  r.u0 = w[4];
-  r.v0 = w[5];
-  r.bin = w[6];
-  r.box = w[7];
-  return r;
+// A table entry (an item, a sweep's layer) in scalar registers.  The tables do not change during
+// a launch, but beside plain stores or a loop's atomics the compiler does not know that and loads
+// them per lane, each time with a wait (the fused kernels 10% slower): so they are read as
+// constant memory.
+template <typename T>
+__device__ __forceinline__ T read_entry(const T* p) {
+  static_assert(sizeof(T) % 4 == 0 && alignof(T) >= 4, "whole words");
+  const auto* w = (const __attribute__((address_space(4))) uint32_t*)(uintptr_t)p;
+  uint32_t r[sizeof(T) / 4];
+#pragma unroll
+  for (size_t i = 0; i < sizeof(T) / 4; ++i) r[i] = w[i];
+  T t;
+  __builtin_memcpy(&t, r, sizeof(T));
+  return t;
 }
 
 // One work item on one workgroup.  Its box is added into Y; that of a piece of a cut item (sums
 // given, slot in wi.bin) is stored for k_merge.  MODE 0: fused G^dag G; 1: de-gridding; 2: gridding.
 // Every thread passes the same two barriers (scattering modes), whatever its rows.
-template <int STORE, int MK, int MODE>
+template <int STORE, int MK, int MODE, bool SWEEP>
 __device__ __forceinline__ void row_item(const WorkItem wi, const uint32_t* __restrict__ meta,
                                          const uint32_t* __restrict__ voff,
                                          const int32_t* __restrict__ perm,
                                          const void* __restrict__ vals,
                                          const float2* __restrict__ X, float2* __restrict__ Y,
                                          float2* __restrict__ vis, int Kx, int Ky,
-                                         double* acc, double2* __restrict__ sums) {
+                                         double* acc, double2* __restrict__ sums, int tid) {
   constexpr bool GATHER = MODE != 2;
   constexpr bool SCATTER = MODE != 1;
   constexpr int VB = value_bytes<STORE>();
@@ -370,13 +380,13 @@ __device__ __forceinline__ void row_item(const WorkItem wi, const uint32_t* __re
   const int slot = sums ? wi.bin : -1;
   auto finish = [&] {
     if (slot >= 0)
-      window_store(acc, bx, sums + slot);
+      window_store(acc, bx, sums + slot, tid);
     else
-      window_flush(acc, bx, wi.u0, wi.v0, Kx, Ky, Y);
+      window_flush(acc, bx, wi.u0, wi.v0, Kx, Ky, Y, tid);
   };
   const int ksh = 31 - __builtin_clz(Ky);
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int seg = (wi.nrows + GWAVES - 1) / GWAVES;
   const int r0 = wave * seg;
   const int r1 = min(wi.nrows, r0 + seg);
@@ -386,7 +396,7 @@ __device__ __forceinline__ void row_item(const WorkItem wi, const uint32_t* __re
   using Raw = typename RawT<STORE>::type;
   if (r0 >= r1) {
     if constexpr (SCATTER) {
-      window_zero(acc, bx);
+      window_zero(acc, bx, tid);
       __syncthreads();
       __syncthreads();
       finish();
@@ -399,11 +409,9 @@ __device__ __forceinline__ void row_item(const WorkItem wi, const uint32_t* __re
   // the LDS/scalar counter that the window atomics use.  Value offsets are the running
   // sum of T^2 inside the item; the values of row r + D are requested (after a new run's
   // grid values) before row r is reduced.
-  constexpr RowForm F = row_form(STORE, MK, MODE);
+  constexpr RowForm F = row_form(STORE, MK, MODE, SWEEP);
   constexpr int D = F.depth;
-  // the next run's grid values are gathered while the current run is reduced (one run
-  // ahead), where that costs no workgroup its registers
-  constexpr bool PREFETCH = GATHER && MK <= 4;
+  constexpr bool PREFETCH = GATHER && F.ahead;
   const int nseg = r1 - r0;
   const uint32_t* __restrict__ mrow = meta + wi.row0 + r0;
   const uint32_t mv0 = mrow[min(lane, nseg - 1)];
@@ -443,7 +451,7 @@ __device__ __forceinline__ void row_item(const WorkItem wi, const uint32_t* __re
   }
   // the accumulator is cleared while the first rows' values are on their way
   if constexpr (SCATTER) {
-    window_zero(acc, bx);
+    window_zero(acc, bx, tid);
     __syncthreads();
   }
   Slots<MK> sl;
@@ -568,8 +576,9 @@ __device__ __forceinline__ void row_block(int b, const RowPieces& pc,
   if constexpr (C1 > C0) {
     constexpr int C = C1 - 1;
     if (b < pc.n[C])
-      row_item<STORE, class_mk(C), MODE>(read_item(pc.items + pc.first[C] + b), meta, voff, perm,
-                                         vals, X, Y, vis, Kx, Ky, acc, pc.sums);
+      row_item<STORE, class_mk(C), MODE, false>(read_entry(pc.items + pc.first[C] + b), meta, voff, perm,
+                                         vals, X, Y, vis, Kx, Ky, acc, pc.sums,
+                                         (int)threadIdx.x);
     else
       row_block<STORE, MODE, C0, C>(b - pc.n[C], pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky,
                                     acc);
@@ -597,26 +606,41 @@ __attribute__((amdgpu_waves_per_eu(row_form(STORE, class_mk(C0), MODE).waves))) 
 // (queue[1]), so that the next launch, or the next replay of a captured graph, starts
 // from zero without a separate clearing step.
 template <int STORE, int MK, int MODE>
-__global__ __launch_bounds__(GNT) void k_rows_sweep(const WorkItem* __restrict__ wis,
-                                                    int nitems,
-                                                    const SweepLayer* __restrict__ layers,
-                                                    float2* __restrict__ vis_base,
-                                                    int* __restrict__ queue, int Kx, int Ky) {
+__global__ __launch_bounds__(GNT)
+__attribute__((amdgpu_waves_per_eu(row_form(STORE, MK, MODE, true).waves))) void k_rows_sweep(
+    const WorkItem* __restrict__ wis, int nitems, const SweepLayer* __restrict__ layers,
+    float2* __restrict__ vis_base, int* __restrict__ queue, int Kx, int Ky) {
   extern __shared__ double acc[];
   __shared__ int slot;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // An item's words in scalar registers, except for 16-bit gridding of the two widest classes: there
+  // the compiler's code is slower for it (FP16 MK 22 2.45 ms a sweep for 2.09).
+  constexpr bool SCALAR = MODE != 2 || MK < 16 || STORE == WF_STORE_F32;
+  // the thread's index, formed afresh for every item (the empty asm hides that it is unchanged):
+  // it and what follows from it would otherwise be held in registers over the loop
+  auto thread = [&] {
+    if constexpr (!SCALAR) return (int)threadIdx.x;
+    uint32_t none = 0;
+    asm volatile("" : "+v"(none));
+    const int t =
+        64 * wave + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none));
+    __builtin_assume(t >= 0 && t < GNT);
+    return t;
+  };
   for (;;) {
-    if (threadIdx.x == 0) slot = atomicAdd(queue, 1);
+    if (thread() == 0) slot = atomicAdd(queue, 1);
     __syncthreads();
-    const int i = slot;
+    int i = slot;
+    if constexpr (SCALAR) i = __builtin_amdgcn_readfirstlane(i);
     __syncthreads();
     if (i >= nitems) break;
-    const WorkItem wi = read_item(wis + i);
-    const SweepLayer& L = layers[wi.bin];
-    row_item<STORE, MK, MODE>(wi, L.meta, L.voff, L.perm, L.vals, L.X, L.Y,
+    const WorkItem wi = SCALAR ? read_entry(wis + i) : wis[i];
+    const SweepLayer L = SCALAR ? read_entry(layers + wi.bin) : layers[wi.bin];
+    row_item<STORE, MK, MODE, true>(wi, L.meta, L.voff, L.perm, L.vals, L.X, L.Y,
                               vis_base ? vis_base + L.vis_off : nullptr, Kx, Ky, acc,
-                              nullptr);
+                              nullptr, thread());
   }
-  if (threadIdx.x == 0) {
+  if (thread() == 0) {
     __threadfence();
     if (atomicAdd(queue + 1, 1) == (int)gridDim.x - 1) {
       atomicExch(queue, 0);
