@@ -550,8 +550,9 @@ __device__ __forceinline__ void row_item(const WorkItem wi, const uint32_t* __re
   }
 }
 
-// The classes that share a launch, from c0 on: those held to the same registers, except where
-// four workgroups share a compute unit (4096^2 psf 16.21 -> 16.37 ms with those two merged).
+// The classes that share a launch, from c0 on: those whose forms ask for the same number of
+// wavefronts, except where four workgroups share a compute unit (4096^2 psf 16.21 -> 16.37 ms with
+// those two merged).
 constexpr int group_end(int store, int mode, int c0) {
   const int w = row_form(store, class_mk(c0), mode).waves;
   int c = c0 + 1;
@@ -559,11 +560,26 @@ constexpr int group_end(int store, int mode, int c0) {
   return c;
 }
 
+// Rows from which class 0 is launched apart from the group that it is part of (-1: never).  The
+// group's kernel has the registers of its largest class, and class 0 compiled alone holds more
+// workgroups (FP32 fused: 45 registers and four for 122 and two).  The lines lie where the
+// launch costs less than that gives: 512^2, 4M rows of class 0, us an apply in the group and
+// apart: FP32 fused 741 / 569 (300,000 rows 129 / 126, 100,000 75 / 80), de-gridding 800 / 727 (94
+// / 89, 52 / 54), BF16 fused 519 / 450 (1.5M rows 243 / 237, 700,000 158 / 163), FP16 and BF16
+// gridding 431 / 380 (1.5M rows 186 / 188).  FP32 gridding gains at no size, nor do the other
+// classes that would hold more workgroups alone (1 and 4, and 3 of BF16, in gridding).
+constexpr int64_t alone_rows(int store, int mode) {
+  const bool f16 = store == WF_STORE_F16, f32 = store == WF_STORE_F32;
+  if (mode == 0) return f32 ? 300'000 : f16 ? -1 : 1'200'000;
+  if (mode == 1) return f32 ? 300'000 : -1;
+  return f32 ? -1 : 2'000'000;
+}
+
 // One launch over the pieces of the classes [C0, C1), the widest patches first: the workgroups
-// of one class run beside the last ones of another instead of behind them.  Classes of fewer
-// registers stay apart, where they would lose workgroups (all of them at 128: 4096^2 psf
-// 16.1 -> 17.5 ms).  Measured against a launch per class: 512^2 iteration (FP32, 460 pieces in
-// all) 172 -> 142 us, 1024^2 adjoint 940 -> 881 us, 2048^2 wideband 16.82 -> 16.66 ms.
+// of one class run beside the last ones of another instead of behind them.  (All classes at 128
+// registers in one launch, those that need fewer losing workgroups: 4096^2 psf 16.1 -> 17.5 ms.)
+// Measured against a launch per class: 512^2 iteration (FP32, 460 pieces in all) 172 -> 142 us,
+// 1024^2 adjoint 940 -> 881 us, 2048^2 wideband 16.82 -> 16.66 ms.
 template <int STORE, int MODE, int C0, int C1>
 __device__ __forceinline__ void row_block(int b, const RowPieces& pc,
                                           const uint32_t* __restrict__ meta,
@@ -672,26 +688,45 @@ constexpr size_t box_bytes(int mk, int mode, int tile) {
   return mode == 1 ? 0 : side * side * 2 * sizeof(double);
 }
 
+// One launch over the classes [C0, C1).
+template <int STORE, int MODE, int C0, int C1>
+static hipError_t launch_classes(const RowPieces& pc, const uint32_t* meta, const uint32_t* voff,
+                                 const int32_t* perm, const void* vals, const float2* X,
+                                 float2* Y, float2* vis, int Kx, int Ky, int tile,
+                                 hipStream_t s) {
+  int blocks = 0;
+  size_t lds = 0;
+  for (int c = C0; c < C1; ++c) {
+    blocks += pc.n[c];
+    if (pc.n[c] > 0) lds = box_bytes(class_mk(c), MODE, tile);
+  }
+  if (blocks == 0) return hipSuccess;
+  hipError_t e = set_lds(k_rows<STORE, MODE, C0, C1>, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_rows<STORE, MODE, C0, C1>), dim3(blocks), dim3(GNT), lds, s, pc, meta,
+                     voff, perm, vals, X, Y, vis, Kx, Ky);
+  return hipGetLastError();
+}
+
 template <int STORE, int MODE, int C0 = 0>
-static hipError_t launch_groups(const RowPieces& pc, const uint32_t* meta, const uint32_t* voff,
+static hipError_t launch_groups(RowPieces pc, const uint32_t* meta, const uint32_t* voff,
                                 const int32_t* perm, const void* vals, const float2* X,
                                 float2* Y, float2* vis, int Kx, int Ky, int tile,
                                 hipStream_t s) {
   if constexpr (C0 < NCLS) {
     constexpr int C1 = group_end(STORE, MODE, C0);
-    int blocks = 0;
-    size_t lds = 0;
-    for (int c = C0; c < C1; ++c) {
-      blocks += pc.n[c];
-      if (pc.n[c] > 0) lds = box_bytes(class_mk(c), MODE, tile);
+    hipError_t e;
+    if constexpr (C0 == 0 && alone_rows(STORE, MODE) >= 0) {
+      if (pc.rows0 >= alone_rows(STORE, MODE)) {
+        e = launch_classes<STORE, MODE, 0, 1>(pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky, tile,
+                                              s);
+        if (e != hipSuccess) return e;
+        pc.n[0] = 0;
+      }
     }
-    if (blocks > 0) {
-      hipError_t e = set_lds(k_rows<STORE, MODE, C0, C1>, lds);
-      if (e != hipSuccess) return e;
-      hipLaunchKernelGGL((k_rows<STORE, MODE, C0, C1>), dim3(blocks), dim3(GNT), lds, s, pc,
-                         meta, voff, perm, vals, X, Y, vis, Kx, Ky);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+    e = launch_classes<STORE, MODE, C0, C1>(pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky, tile,
+                                            s);
+    if (e != hipSuccess) return e;
     return launch_groups<STORE, MODE, C1>(pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky, tile,
                                           s);
   }

@@ -327,6 +327,7 @@ wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint
   const size_t nk = r0.size();
   ch.pc_0.assign(2 * nk, 0);
   ch.pc_n.assign(2 * nk, 0);
+  ch.rows0.assign(nk / NCLS, 0);
   ch.cut_0.assign(nk / NCLS, 0);
   ch.cut_n.assign(nk / NCLS, 0);
   ch.cut_lines.assign(nk / NCLS, 0);
@@ -345,6 +346,7 @@ wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint
     if (rn[k] == 0) continue;
     int64_t rows = 0;
     for (int i = 0; i < rn[k]; ++i) rows += wis[r0[k] + i].nrows;
+    if (k % NCLS == 0) ch.rows0[bin] = rows;
     const int64_t most = std::max(rule.least, (rows / rule.share + 7) / 8 * 8);
     part.clear();
     for (int i = 0; i < rn[k]; ++i) {
@@ -1241,8 +1243,8 @@ Lane lane_of(wf_op* op, int b, hipStream_t caller) {
 // What the row kernels go over for bin (on the fly: chunk) k on lane L.
 RowPieces pieces_of(const wf_op* op, const ChanOp& ch, int64_t k, const Lane& L, bool scatter) {
   RowPieces pc{(const WorkItem*)ch.pieces.p, {}, {}, (const CutItem*)ch.cuts.p + ch.cut_0[k],
-               (const CutPart*)ch.parts.p, scatter ? ch.cut_n[k] : 0, ch.cut_lines[k],
-               (double2*)op->br[L.b].sums.p};
+               (const CutPart*)ch.parts.p, ch.rows0[k], scatter ? ch.cut_n[k] : 0,
+               ch.cut_lines[k], (double2*)op->br[L.b].sums.p};
   const size_t at = (scatter ? ch.pc_n.size() / 2 : 0) + (size_t)k * NCLS;
   for (int c = 0; c < NCLS; ++c) {
     pc.first[c] = ch.pc_0[at + c];

@@ -122,6 +122,7 @@ struct RowPieces {
   int32_t first[NCLS], n[NCLS];
   const CutItem* cuts;
   const CutPart* parts;
+  int64_t rows0;              // rows of class 0 (the narrowest patches)
   int32_t ncuts, cut_lines;   // cut items; grid lines under the largest of their boxes
   double2* sums;
 };
@@ -257,6 +258,7 @@ struct ItemTables {
   // of those for de-gridding, then all of those for the kernels that scatter
   DevBuf pieces;
   std::vector<int32_t> pc_0, pc_n;
+  std::vector<int64_t> rows0;              // rows of class 0, per bin or chunk
   // the items that were cut, per bin (chunk): first, count, grid lines of the largest box; their
   // pieces' slots and boxes; and the cells that the largest bin's pieces need in a branch
   DevBuf cuts, parts;
