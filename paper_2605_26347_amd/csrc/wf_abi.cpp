@@ -307,18 +307,28 @@ void split_items(ChanOp& ch, const uint8_t* trow, const uint32_t* meta_base, int
 // each clears an accumulator of its own and stores it, and the sums of an item's pieces meet in
 // FP64 before they reach the FP32 grid (CutItem), as those of a whole item do in its one
 // accumulator.  (Each piece added into the grid by itself put a third on the adjoint's error
-// where a cell gathers many rows: 20,000 rows in 28^2 cells 2.3e-7 for 1.7e-7.)
+// where a cell gathers many rows: 20,000 rows in 28^2 cells 2.3e-7 for 1.7e-7.)  A class that has
+// a launch to itself takes a 768th there too: the narrow ones of FP16 (k_grid.hip, group_end) and
+// one that holds nearly all of the bin's rows; and the least is 64 rows in FP16, whose classes are
+// spread over four launches.
 // Whole items / pieces of a 768th and 64 / of a 384th and 128: 64^2 psf 81 / 38 / 38 us (27
 // items), ten 512^2 iterations 1980 / 1465 / 1416 us, 1024^2 adjoint 900 / 923 / 884 us, 1024^2
 // forward 1471 / 1359 / 1404 us, 8192^2 forward 2536 / 2294 / 2406 us; 4096^2 psf with 30M rows
-// the same (its items average 139 rows).
+// the same (its items average 139 rows).  Classes to themselves, of a 384th and a 768th: 512^2 psf
+// with 300,000 narrow rows 128 / 114 us (FP32) and 124 / 103 (FP16), 1024^2 psf with 1M rows in
+// FP16 536 / 489, with the least of 64 rows 465.
 // The tables are allocated anew: those that the caller holds stay its own.
 struct PieceRule {
   int64_t share, least;
 };
-constexpr PieceRule GATHER_PIECES{768, 64}, SCATTER_PIECES{384, 128};
+constexpr PieceRule FINE_PIECES{768, 64}, COARSE_PIECES{384, 128}, COARSE_F16{384, 64};
+PieceRule piece_rule(bool scatter, wf_store store, int cls, int64_t rows, int64_t bin_rows) {
+  const bool f16 = store == WF_STORE_F16;
+  const bool to_itself = (f16 && cls <= 1) || 8 * rows >= 7 * bin_rows;
+  return !scatter || to_itself ? FINE_PIECES : f16 ? COARSE_F16 : COARSE_PIECES;
+}
 wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint32_t* meta,
-                        hipStream_t s) {
+                        wf_store store, hipStream_t s) {
   std::vector<WorkItem> all;
   std::vector<CutItem> cuts;
   std::vector<CutPart> parts;
@@ -334,18 +344,23 @@ wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint
   ch.sum_cells = 0;
   std::vector<WorkItem> part;
   std::vector<std::pair<int64_t, int32_t>> order;
-  int64_t slot = 0;   // of the bin's (chunk's) next piece
+  auto rows_of = [&](size_t k) {
+    int64_t n = 0;
+    for (int i = 0; i < rn[k]; ++i) n += wis[r0[k] + i].nrows;
+    return n;
+  };
+  int64_t slot = 0, bin_rows = 0;   // slot of the bin's (chunk's) next piece; its rows
   for (size_t k2 = 0; k2 < 2 * nk; ++k2) {
     const bool scatter = k2 >= nk;
-    const PieceRule rule = scatter ? SCATTER_PIECES : GATHER_PIECES;
     const size_t k = scatter ? k2 - nk : k2, bin = k / NCLS;
     if (k % NCLS == 0) {
       ch.cut_0[bin] = (int32_t)cuts.size();
-      slot = 0;
+      slot = bin_rows = 0;
+      for (int c = 0; c < NCLS; ++c) bin_rows += rows_of(k + c);
     }
     if (rn[k] == 0) continue;
-    int64_t rows = 0;
-    for (int i = 0; i < rn[k]; ++i) rows += wis[r0[k] + i].nrows;
+    const int64_t rows = rows_of(k);
+    const PieceRule rule = piece_rule(scatter, store, (int)(k % NCLS), rows, bin_rows);
     if (k % NCLS == 0) ch.rows0[bin] = rows;
     const int64_t most = std::max(rule.least, (rows / rule.share + 7) / 8 * 8);
     part.clear();
@@ -905,7 +920,7 @@ wf_status build_channel(wf_op* op, int c, const double* uvw, int64_t M, double f
   WF_HIP(hipMemcpyAsync(drowwi.p, row_wi.data(), sizeof(int32_t) * M, hipMemcpyHostToDevice, s));
   WF_HIP(hipMemcpyAsync(ch.work.p, wis.data(), sizeof(WorkItem) * wis.size(),
                         hipMemcpyHostToDevice, s));
-  if (!holo && (st = schedule_rows(ch, wis, meta.data(), s)) != WF_OK) return st;
+  if (!holo && (st = schedule_rows(ch, wis, meta.data(), opt.store, s)) != WF_OK) return st;
   if (holo) {
     // holographic matrix (Sect. 3.3): stencil tiles of every bin, accumulated from that
     // bin's rows of G built one bin at a time in FP32; G itself is not kept
@@ -2051,7 +2066,7 @@ wf_status retune_channel(wf_op* op, int c, int32_t maxrows, const int8_t* tsh = 
               meta.data(), ch.otf ? row_wi.data() : nullptr);
   wf_status st = dalloc(ch.work, sizeof(WorkItem) * std::max<size_t>(wis.size(), 1));
   if (st != WF_OK) return st;
-  if ((st = schedule_rows(ch, wis, meta.data(), nullptr)) != WF_OK) return st;
+  if ((st = schedule_rows(ch, wis, meta.data(), op->opt.store, nullptr)) != WF_OK) return st;
   if ((st = grow_sums(op)) != WF_OK) return st;
   undo.done = true;
   if (ch.otf)   // the on-the-fly value pass finds each row's item through row_wi

@@ -51,7 +51,8 @@ const char* hipGetErrorString(hipError_t) { return "out of memory"; }
   }
 
 // One channel: rows of every patch class in a few tiles of 32 cells, in two bins.
-static void fill(wf_op& op, std::vector<int> rows_of) {
+static void fill(wf_op& op, std::vector<int> rows_of, wf_store store = WF_STORE_F32) {
+  op.opt.store = store;
   op.tile = 32;
   op.halo = 18;
   op.max_tsh = 1;
@@ -100,7 +101,7 @@ static void fill(wf_op& op, std::vector<int> rows_of) {
   up(ch.meta, meta.data(), 4 * meta.size());
   up(ch.voff, voff.data(), 4 * voff.size());
   up(ch.work, wis.data(), sizeof(WorkItem) * wis.size());
-  CHECK(schedule_rows(ch, wis, meta.data(), nullptr) == WF_OK);
+  CHECK(schedule_rows(ch, wis, meta.data(), op.opt.store, nullptr) == WF_OK);
 }
 
 static bool held(const DevBuf& b, size_t bytes) {
@@ -261,10 +262,12 @@ static void lane_after_resplit() {
 static void pieces_of_items() {
   for (const std::vector<int>& rows : {std::vector<int>{1}, {64}, {65}, {1025}, {0, 63, 64, 129},
                                        {5000, 1, 1, 700, 64, 65, 2000, 333}}) {
-    wf_op op;
-    fill(op, rows);
-    covered(op.chans[0]);
-    cut_items_meet(op.chans[0]);
+    for (wf_store store : {WF_STORE_F32, WF_STORE_F16}) {
+      wf_op op;
+      fill(op, rows, store);
+      covered(op.chans[0]);
+      cut_items_meet(op.chans[0]);
+    }
   }
 }
 
