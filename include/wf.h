@@ -228,7 +228,7 @@ typedef struct {
   int64_t ntaps;            /* stored values of G (K of eq. 9)                          */
   int64_t nwork;            /* work items of the fused kernel                           */
   double k_estimate;        /* planner's K(P) estimate at the chosen P                  */
-  double mem_g_bytes;       /* device bytes of G (values + row metadata)                */
+  double mem_g_bytes;       /* device bytes of G (values, row metadata, work-item tables) */
   double mem_model_bytes;   /* eq. 9 (GPU form) at the chosen P                         */
   double cost_model;        /* eq. 10 at the chosen P                                   */
   double capped_fraction;   /* rows whose kernel side was capped at smax               */

@@ -419,6 +419,11 @@ wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint
   return WF_OK;
 }
 
+// Device bytes of a split's tables.
+double item_bytes(const ItemTables& t) {
+  return (double)(t.work.bytes + t.pieces.bytes + t.cuts.bytes + t.parts.bytes);
+}
+
 // Whether a w-layer's modulation (eq. 6) is formed from its column table by the FP32 series of the
 // row FFT passes instead of pixel by pixel in FP64.  The series hold where r2 = l^2 + m^2 <= 1/100
 // over the image and the phase beyond the quadratic term, 2 pi |w_p| |n - 1 + r2/2|, stays within
@@ -1172,8 +1177,8 @@ wf_status build_channel(wf_op* op, int c, const double* uvw, int64_t M, double f
   in.mem_g_bytes = otf ? (double)(ch.uvw.bytes + ch.wts.bytes + ch.uperm.bytes +
                                    ch.row_wi.bytes + ch.crow.bytes + ch.khat.bytes +
                                    ch.kof.bytes + ch.ktap.bytes + ch.xrow.bytes) + 12.0 * M +
-                             sizeof(WorkItem) * wis.size()
-                      : (double)b_v * taps_total + 12.0 * M + sizeof(WorkItem) * wis.size();
+                             item_bytes(ch)
+                      : (double)b_v * taps_total + 12.0 * M + item_bytes(ch);
   in.mem_transient_bytes = otf ? (double)b_v * ch.ck_max : 0.0;
   in.value_pass_flops = vp_flops;
   in.mem_khat_bytes = (double)(ch.khat.bytes + ch.kof.bytes + ch.ktap.bytes);
@@ -2075,6 +2080,7 @@ wf_status retune_channel(wf_op* op, int c, int32_t maxrows, const int8_t* tsh = 
   WF_HIP(hipMemcpy(ch.voff.p, voff.data(), sizeof(uint32_t) * M, hipMemcpyHostToDevice));
   WF_HIP(hipMemcpy(ch.work.p, wis.data(), sizeof(WorkItem) * wis.size(),
                    hipMemcpyHostToDevice));
+  ch.info.mem_g_bytes += item_bytes(ch) - item_bytes(undo.old);
   ch.info.nwork = ch.nwork;
   ch.info.max_rows_per_item = ch.max_rows;
   op->generation++;

@@ -205,6 +205,8 @@ static void failed_resplit() {
   CHECK(ch.cut_n[0] > 0);
   op.br.resize(2);
   CHECK(grow_sums(&op) == WF_OK);
+  const double rows = 1e6;   // the channel's other bytes
+  ch.info.mem_g_bytes = rows + item_bytes(ch);
   const ItemTables was = ch;
   const void* sums = op.br[1].sums.p;
   const std::vector<uint32_t> meta((uint32_t*)ch.meta.p, (uint32_t*)ch.meta.p + ch.nrows);
@@ -223,6 +225,7 @@ static void failed_resplit() {
     ++fails;
     CHECK(st == WF_ENOMEM);
     CHECK(g_live.size() == blocks);
+    CHECK(ch.info.mem_g_bytes == rows + item_bytes(was));
     CHECK(ch.work.p == was.work.p && ch.pieces.p == was.pieces.p);
     CHECK(ch.pc_0 == was.pc_0 && ch.pc_n == was.pc_n && ch.nwork == was.nwork);
     CHECK(ch.cls_wi0 == was.cls_wi0 && ch.cls_nwi == was.cls_nwi);
@@ -234,6 +237,8 @@ static void failed_resplit() {
   }
   CHECK(fails >= 4);
   CHECK(ch.max_rows == 256 && ch.bin_tsh == wide);
+  CHECK(item_bytes(ch) != item_bytes(was) && ch.info.mem_g_bytes == rows + item_bytes(ch));
+  CHECK(item_bytes(ch) >= sizeof(WorkItem) * 3.0 * ch.nwork);   // items and two lists of pieces
   CHECK(g_live.size() == blocks);
   covered(ch);
   cut_items_meet(ch);
