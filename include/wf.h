@@ -372,8 +372,9 @@ typedef struct {
  * into the caller's scratch d_out (same shape), choose per channel the rows per work
  * item (256, 512 or 1024) and per bin the work items' tile side (the base tile, or 2 x 2
  * base tiles where the LDS accumulator of such an item fits), from the fused kernel's
- * time on every bin under each combination; only the work-item split of the stored rows
- * and their patch words change, never their values.  Then, unless the operator runs as
+ * time on every bin under each combination; a channel that has such a split already keeps it
+ * unless the choice makes a whole apply of the channel faster by more than 1%.  Only the
+ * work-item split of the stored rows and their patch words change, never their values.  Then, unless the operator runs as
  * a layer-batched sweep (wf_set_sweep, whose item lists are rebuilt instead), the branch
  * count (1, 2, 4, and 8 when nchan >= 8).  reps timed runs per candidate (>= 1).
  * Synchronous; invalidates graphs captured earlier. */

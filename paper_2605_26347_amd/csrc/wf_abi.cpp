@@ -2096,6 +2096,11 @@ wf_status bin_gtg(wf_op* op, const ChanOp& ch, int p, const Lane& L) {
   return WF_OK;
 }
 
+// The autotuner changes a channel's split for a whole apply below this share of its time: what two
+// timings of one split differ by.  (Taken by the sum of single-bin timings alone, the choice left
+// 4096^2 with 50M rows 1% slower in FP32, 29.86 to 30.22 ms.)
+constexpr double TUNE_GAIN = 0.99;
+
 // Mean duration in ms of `reps` runs of fn on stream s, after one untimed run.
 template <class F>
 wf_status time_runs(hipStream_t s, int reps, F&& fn, double* ms) {
@@ -2829,43 +2834,63 @@ wf_status wf_autotune(wf_op* op, const float* d_img, float* d_out, void* hip_str
     for (int c = 0; c < (int)op->chans.size(); ++c) {
       ChanOp& ch = op->chans[c];
       if (ch.nrows == 0) continue;
+      // the split that a channel has stays, if it is one of those tried, unless a whole apply of
+      // the channel gains by another
       const int32_t orig = ch.max_rows;
-      if (ch.otf || ch.holo) {
+      const bool tried = std::find(cand_rows, cand_rows + 3, orig) != cand_rows + 3;
+      const std::vector<int8_t> orig_tsh =
+          ch.bin_tsh.empty() ? std::vector<int8_t>(ch.P, 0) : ch.bin_tsh;
+      const std::vector<int32_t> orig_nwi = ch.ck_nwi.empty() ? ch.cls_nwi : ch.ck_nwi;
+      auto whole = [&](double* ms) {
+        return time_runs(s, reps, [&]() { return run_channel(op, kind, c, L, d_img, d_out); },
+                         ms);
+      };
+      double orig_ms = 0;
+      if ((st = whole(&orig_ms)) != WF_OK) return st;
+      ch.measured_ms = orig_ms;
+      if (ch.holo) continue;   // no work items are left to split
+      if (ch.otf) {
         // no stored G to time alone: whole-channel applies choose the rows per item
         int32_t best = orig;
-        double best_ms = 1e300;
+        double best_ms = tried ? TUNE_GAIN * orig_ms : 1e300;
         for (int32_t mr : cand_rows) {
+          if (mr == orig) continue;
           if ((st = retune_channel(op, c, mr)) != WF_OK) return st;
-          double tc = 0;
-          st = time_runs(s, reps, [&]() { return run_channel(op, kind, c, L, d_img, d_out); },
-                         &tc);
-          if (st != WF_OK) return st;
+          double tc = orig_ms;
+          if (ch.ck_nwi != orig_nwi && (st = whole(&tc)) != WF_OK) return st;
           if (tc < best_ms) {
-            best_ms = tc;
+            best_ms = ch.measured_ms = tc;
             best = mr;
           }
         }
         if ((st = retune_channel(op, c, best)) != WF_OK) return st;
-        ch.measured_ms = best_ms;
         if (best != orig) ++retuned;
         continue;
       }
-      const std::vector<int8_t> orig_tsh = ch.bin_tsh;
       const int nsh = op->max_tsh + 1;
-      // fused-kernel time of every bin under each (rows per item, item tile)
+      // fused-kernel time of every bin under each (rows per item, item tile); a split with the
+      // items of one already timed has its times
       std::vector<double> t((size_t)3 * nsh * ch.P, 0.0);
-      for (int i = 0; i < 3; ++i)
-        for (int sh = 0; sh < nsh; ++sh) {
+      for (int sh = 0; sh < nsh; ++sh) {
+        std::vector<std::vector<int32_t>> seen;
+        for (int i = 0; i < 3; ++i) {
+          double* ti = t.data() + ((size_t)i * nsh + sh) * ch.P;
           const std::vector<int8_t> all(ch.P, (int8_t)sh);
           if ((st = retune_channel(op, c, cand_rows[i], all.data())) != WF_OK) return st;
-          for (int p = 0; p < ch.P; ++p) {
-            if (ch.bin_nrows[p] == 0) continue;
-            double ms = 0;
-            st = time_runs(s, reps, [&]() { return bin_gtg(op, ch, p, L); }, &ms);
-            if (st != WF_OK) return st;
-            t[((size_t)i * nsh + sh) * ch.P + p] = ms;
+          const auto same = std::find(seen.begin(), seen.end(), ch.cls_nwi);
+          if (same != seen.end()) {
+            const size_t j = same - seen.begin();
+            std::copy_n(t.data() + (j * nsh + sh) * ch.P, ch.P, ti);
+          } else {
+            for (int p = 0; p < ch.P; ++p) {
+              if (ch.bin_nrows[p] == 0) continue;
+              st = time_runs(s, reps, [&]() { return bin_gtg(op, ch, p, L); }, &ti[p]);
+              if (st != WF_OK) return st;
+            }
           }
+          seen.push_back(ch.cls_nwi);
         }
+      }
       int best = 0;
       double best_ms = 1e300;
       std::vector<int8_t> best_tsh(ch.P, 0);
@@ -2890,12 +2915,16 @@ wf_status wf_autotune(wf_op* op, const float* d_img, float* d_out, void* hip_str
         }
       }
       if ((st = retune_channel(op, c, cand_rows[best], best_tsh.data())) != WF_OK) return st;
-      for (int p = 0; p < ch.P; ++p) big_bins += best_tsh[p] > 0;
-      double tc = 0;
-      st = time_runs(s, reps, [&]() { return run_channel(op, kind, c, L, d_img, d_out); }, &tc);
-      if (st != WF_OK) return st;
-      ch.measured_ms = tc;
-      if (cand_rows[best] != orig || ch.bin_tsh != orig_tsh) ++retuned;
+      const bool same = ch.cls_nwi == orig_nwi && best_tsh == orig_tsh;
+      double tc = orig_ms;
+      if (!same && (st = whole(&tc)) != WF_OK) return st;
+      const bool keep = !tried || tc < TUNE_GAIN * orig_ms;
+      if (keep) ch.measured_ms = tc;
+      if (keep)
+        ++retuned;
+      else if ((st = retune_channel(op, c, orig, orig_tsh.data())) != WF_OK)
+        return st;
+      for (int p = 0; p < ch.P; ++p) big_bins += !ch.bin_tsh.empty() && ch.bin_tsh[p] > 0;
     }
     WF_HIP(launch_fill_zero(L.Y, grid_floats, s));
     const int nchan = (int)op->chans.size();
