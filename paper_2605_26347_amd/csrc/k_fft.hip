@@ -141,19 +141,8 @@ struct Masks {
   int tsh;                // log2(tile)
 };
 
-template <int N>
-constexpr int row_threads() {
-  return N / 16 < 64 ? 64 : (N / 16 > 1024 ? 1024 : N / 16);
-}
-template <int N>
-constexpr int col_width() {
-  return (16384 / N) > 16 ? 16 : (16384 / N);
-}
-template <int N>
-constexpr int col_threads() {
-  return (col_width<N>() * N) / 16 < 64 ? 64
-         : ((col_width<N>() * N) / 16 > 1024 ? 1024 : (col_width<N>() * N) / 16);
-}
+// Threads of a workgroup of the LDS-resident passes (lines of 16 and 32 points).
+constexpr int SHORT_THREADS = 64;
 
 template <int N, int NT>
 __global__ __launch_bounds__(NT) void k_fwd_rows(const float* __restrict__ img,
@@ -532,7 +521,7 @@ __global__ __launch_bounds__(RowPlan<N>::NT) void k_inv_rows_sweep(
 // compile-time rule as rows.
 template <int N>
 struct ColPlan {
-  static constexpr int CW = N <= 1024 ? 4 : 16384 / N;
+  static constexpr int CW = col_width_for(N);
   static constexpr int NTC = RowPlan<N>::NT;   // threads per column
   static constexpr int NT = CW * NTC;
   // The CW columns of one grid row sit on neighbouring lanes.  An LDS access of 64 lanes
@@ -869,7 +858,7 @@ hipError_t launch_fwd_rows(const float* img, float2* A, const float2* tw, const 
 #undef C
 #define C(N)                                                                              \
   case N: {                                                                               \
-    constexpr int NT = row_threads<N>();                                                  \
+    constexpr int NT = SHORT_THREADS;                                                     \
     hipLaunchKernelGGL((k_fwd_rows<N, NT>), dim3(ny), dim3(NT), N * sizeof(float2), s,    \
                        img, A, tw, sx, sy, nx, ny, cell, wp, smask);                      \
     return hipGetLastError();                                                             \
@@ -900,7 +889,7 @@ hipError_t launch_inv_rows(const float2* A, void* out, const float2* tw, const f
 #undef C
 #define C(N)                                                                              \
   case N: {                                                                               \
-    constexpr int NT = row_threads<N>();                                                  \
+    constexpr int NT = SHORT_THREADS;                                                     \
     hipLaunchKernelGGL((k_inv_rows<N, NT>), dim3(ny), dim3(NT), N * sizeof(float2), s, A, \
                        out, tw, sx, sy, nx, ny, cell, wp, mode, smask);                   \
     return hipGetLastError();                                                             \
@@ -960,8 +949,7 @@ hipError_t launch_fwd_cols(const float2* A, float2* X, const float2* tw, int ny,
 #undef C
 #define C(N)                                                                              \
   case N: {                                                                               \
-    constexpr int CW = col_width<N>();                                                    \
-    constexpr int NT = col_threads<N>();                                                  \
+    constexpr int CW = col_width_for(N), NT = SHORT_THREADS;                              \
     if (Kx % CW != 0) return hipErrorInvalidValue;                                        \
     int ng;                                                                               \
     const Masks mk = col_masks<CW>(pr, Kx, &ng);                                          \
@@ -987,8 +975,7 @@ hipError_t launch_inv_cols(float2* Y, float2* A, const float2* tw, int ny, int K
 #undef C
 #define C(N)                                                                              \
   case N: {                                                                               \
-    constexpr int CW = col_width<N>();                                                    \
-    constexpr int NT = col_threads<N>();                                                  \
+    constexpr int CW = col_width_for(N), NT = SHORT_THREADS;                              \
     if (Kx % CW != 0) return hipErrorInvalidValue;                                        \
     int ng;                                                                               \
     const Masks mk = col_masks<CW>(pr, Kx, &ng);                                          \

@@ -149,7 +149,7 @@ struct SweepLayer {
 
 // Active uv support of one bin for the column passes: tiles that hold rows, dilated by
 // one tile (the LDS windows reach into neighbours), the column strips under them, and the
-// column groups (col_width columns each) that cover those strips.
+// column groups (col_width_for columns each) that cover those strips.
 struct ColPrune {
   const uint32_t* strip;   // [Kx/MSTRIP] bits
   const uint32_t* tile;    // [Ky/tile][Kx/tile] bits
@@ -159,8 +159,9 @@ struct ColPrune {
   int tsh;                 // log2(tile)
 };
 
-// Columns per workgroup of the column passes for a column length of Ky.
-inline int col_width_for(int Ky) { return Ky <= 32 ? 16 : Ky <= 1024 ? 4 : 16384 / Ky; }
+// Columns per workgroup of the column passes for a column length of Ky: the host's lists of column
+// groups and the kernels both take it from here.
+constexpr int col_width_for(int Ky) { return Ky <= 32 ? 16 : Ky <= 1024 ? 4 : 16384 / Ky; }
 
 // Shortest row that may take the modulation's column table and FP32 series (series_modulation).
 constexpr int SERIES_N = 2048;
