@@ -205,8 +205,8 @@ __global__ __launch_bounds__(NT) void k_inv_rows(const float2* __restrict__ A,
 }
 
 // Row passes of lines of 64 points and more: three register-resident passes (fft_reg.h).
-// They are bound by instruction issue and L1 accesses rather than by HBM (205 and 272 MB per
-// pass at 8192 points, half of the columns needed: 45 and 60 us at the copy rate), so that
+// They are bound by instruction issue and L1 accesses rather than by HBM (217 and 281 MB per
+// pass at 8192 points, half of the columns needed: 45 and 59 us at the copy rate), so that
 // what counts is instructions and lines per element: constant parts of addresses in scalar
 // registers and immediate offsets, twiddles in reading order, padding terms dropped by the
 // compiler, masks settled by scalar branches.  Forward / inverse pass at 8192 points 109 / 121
