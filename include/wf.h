@@ -304,7 +304,8 @@ wf_status wf_profile_read(wf_op* op, int32_t kernel_id, int64_t* launches, doubl
 
 /* Set the number of branches (1..16).  Allocates the extra branches' grids; with one
  * channel and n > 1 the channel's bins are split over the branches and the partial sums
- * are added in the caller's stream.  Invalidates graphs captured earlier. */
+ * are added in the caller's stream.  Where the memory for them is missing (WF_ENOMEM) the
+ * operator is left on one branch.  Invalidates graphs captured earlier. */
 wf_status wf_set_branches(wf_op* op, int32_t branches);
 
 /* Layer-batched sweep (enable >= 1): every later apply (and every graph captured

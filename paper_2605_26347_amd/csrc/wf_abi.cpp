@@ -2008,12 +2008,22 @@ wf_status ensure_branches(wf_op* op) {
   return WF_OK;
 }
 
+// Where the memory for the branches is missing the operator is left on its first one, which
+// has all that it needs.
 wf_status set_branches(wf_op* op, int n) {
   WF_HIP(hipDeviceSynchronize());
   op->opt.branches = n;
   assign_segments(op);
   op->generation++;
-  return ensure_branches(op);
+  const wf_status st = ensure_branches(op);
+  if (st != WF_OK) {
+    const std::string why = g_err;
+    op->opt.branches = 1;
+    assign_segments(op);
+    (void)ensure_branches(op);
+    return fail(st, why);
+  }
+  return WF_OK;
 }
 
 // Patch words relative to each row's base-tile window, from words relative to the

@@ -41,6 +41,20 @@ hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipSt
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipMemset(void* d, int v, size_t n) {
+  std::memset(d, v, n);
+  return hipSuccess;
+}
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+  *s = (hipStream_t)1;
+  return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
+  *e = (hipEvent_t)1;
+  return hipSuccess;
+}
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "out of memory"; }
 }
 
@@ -263,6 +277,40 @@ static void lane_after_resplit() {
   CHECK(g_live.count((void*)pc.items) && pc.cuts == (const CutItem*)ch.cuts.p);
 }
 
+// Branches that run out of memory, at each of their allocations, leave a complete first one.
+static void failed_branches() {
+  wf_op op;
+  fill(op, {3000, 70, 1, 500});
+  op.shape = wf_image_shape{128, 128, 1e-5};
+  ChanOp& ch = op.chans[0];
+  ch.bin_nrows.assign(ch.P, 1);
+  ch.bin_taps.assign(ch.P, 1);
+  ch.active_tile_frac.assign(ch.P, 1.0);
+  CHECK(set_branches(&op, 1) == WF_OK);
+  const Branch one = op.br[0];
+  const size_t blocks = g_live.size(), grid = sizeof(float2) * 256 * 256;
+  auto whole = [&](const Branch& b) {
+    return held(b.X, grid) && held(b.Y, grid) && held(b.A, grid / 2) &&
+           held(b.sums, sizeof(double2) * ch.sum_cells);
+  };
+  CHECK(whole(one) && ch.sum_cells > 0);
+  for (int k = 0;; ++k) {
+    g_fail_at = k;
+    g_failed = false;
+    const wf_status st = set_branches(&op, 2);
+    g_fail_at = -1;
+    if (!g_failed) {
+      CHECK(st == WF_OK && k == 5);   // grids, half image, partial sums, image sum
+      break;
+    }
+    CHECK(st == WF_ENOMEM && g_live.size() == blocks);
+    CHECK(op.nbranch == 1 && op.br.size() == 1 && op.br[0].X.p == one.X.p && whole(op.br[0]));
+    CHECK(op.segs.size() == 1 && op.segs[0].branch == 0 && op.segs[0].direct);
+    CHECK(op.segs[0].bins.size() == 2);
+  }
+  CHECK(op.nbranch == 2 && whole(op.br[0]) && whole(op.br[1]));
+}
+
 // Few rows, rows in one item, items at the pieces' smallest size, and many items.
 static void pieces_of_items() {
   for (const std::vector<int>& rows : {std::vector<int>{1}, {64}, {65}, {1025}, {0, 63, 64, 129},
@@ -292,6 +340,7 @@ int main() {
   pieces_of_items();
   failed_resplit();
   lane_after_resplit();
+  failed_branches();
   std::printf("host split ok\n");
   return 0;
 }

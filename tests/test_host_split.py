@@ -1,7 +1,7 @@
 """Work items and pieces of the row kernels (CPU only): tests/host_split.cpp, built against the
 C ABI's source with host memory in the place of device memory, checks that every row is covered
 once, that the pieces of a cut item meet in slots of their own, and that a re-split which runs
-out of memory leaves the one in use.  Also which rows take the modulation's FP32 series."""
+out of memory leaves the one in use; that branches which run out of memory leave one.  Also which rows take the modulation's FP32 series."""
 import os
 import shutil
 import subprocess
