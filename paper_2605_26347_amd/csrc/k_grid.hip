@@ -225,12 +225,13 @@ __device__ __forceinline__ void window_zero(double* acc, const Box& bx, int tid)
   const int n = bx.w * bx.h;
   for (int c = tid; c < 2 * n; c += GNT) acc[c] = 0.0;
 }
+
 // Goes over the cells of a box line by line of the grid's layout: 32 lanes on the 32 floats of
 // one 128-byte line (2^GRID_L columns x 2^(4 - GRID_L) rows of complex cells), lines first, first
 // + step, ..., calling on(a, b, part, at) for cell (row a, column b) of the box, part 0 the real
-// and 1 the imaginary float, at() its address.  An atomic costs by the 64-byte segments that it touches, so a
-// line is sent whole: real parts and imaginary parts in instructions of their own touched every
-// segment twice.
+// and 1 the imaginary float, at() its address.  An atomic costs by the 64-byte segments that it
+// touches, so a line is sent whole: real parts and imaginary parts in instructions of their own
+// touched every segment twice.
 template <typename ON>
 __device__ __forceinline__ void each_line(const Box& bx, int u0, int v0, int Kx, int Ky,
                                           float2* __restrict__ Y, int tid, int first, int step,
@@ -281,8 +282,8 @@ __global__ __launch_bounds__(32 * MERGE_LINES) void k_merge(const CutItem* __res
                                                             int Ky) {
   const CutItem it = cuts[blockIdx.x];
   const Box bx = box_of(it.box);
-  each_line(bx, it.u0, it.v0, Kx, Ky, Y, threadIdx.x, blockIdx.y * MERGE_LINES, gridDim.y * MERGE_LINES,
-            [&](int a, int b, int part, auto&& at) {
+  each_line(bx, it.u0, it.v0, Kx, Ky, Y, threadIdx.x, blockIdx.y * MERGE_LINES,
+            gridDim.y * MERGE_LINES, [&](int a, int b, int part, auto&& at) {
               const double* __restrict__ src = reinterpret_cast<const double*>(sums) + part;
               double s = 0.0;
               for (int j0 = 0; j0 < it.nparts; j0 += MERGE_P) {
@@ -362,7 +363,8 @@ __device__ __forceinline__ T read_entry(const T* p) {
 }
 
 // One work item on one workgroup.  Its box is added into Y; that of a piece of a cut item (sums
-// given, slot in wi.bin) is stored for k_merge.  MODE 0: fused G^dag G; 1: de-gridding; 2: gridding.
+// given, slot in wi.bin) is stored for k_merge.  MODE 0: fused G^dag G; 1: de-gridding; 2:
+// gridding.
 // Every thread passes the same two barriers (scattering modes), whatever its rows.
 template <int STORE, int MK, int MODE, bool SWEEP>
 __device__ __forceinline__ void row_item(const WorkItem wi, const uint32_t* __restrict__ meta,
@@ -592,9 +594,9 @@ __device__ __forceinline__ void row_block(int b, const RowPieces& pc,
   if constexpr (C1 > C0) {
     constexpr int C = C1 - 1;
     if (b < pc.n[C])
-      row_item<STORE, class_mk(C), MODE, false>(read_entry(pc.items + pc.first[C] + b), meta, voff, perm,
-                                         vals, X, Y, vis, Kx, Ky, acc, pc.sums,
-                                         (int)threadIdx.x);
+      row_item<STORE, class_mk(C), MODE, false>(read_entry(pc.items + pc.first[C] + b), meta,
+                                                voff, perm, vals, X, Y, vis, Kx, Ky, acc,
+                                                pc.sums, (int)threadIdx.x);
     else
       row_block<STORE, MODE, C0, C>(b - pc.n[C], pc, meta, voff, perm, vals, X, Y, vis, Kx, Ky,
                                     acc);
@@ -629,8 +631,8 @@ __attribute__((amdgpu_waves_per_eu(row_form(STORE, MK, MODE, true).waves))) void
   extern __shared__ double acc[];
   __shared__ int slot;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // An item's words in scalar registers, except for 16-bit gridding of the two widest classes: there
-  // the compiler's code is slower for it (FP16 MK 22 2.45 ms a sweep for 2.09).
+  // An item's words in scalar registers, except for 16-bit gridding of the two widest classes:
+  // there the compiler's code is slower for it (FP16 MK 22 2.45 ms a sweep for 2.09).
   constexpr bool SCALAR = MODE != 2 || MK < 16 || STORE == WF_STORE_F32;
   // the thread's index, formed afresh for every item (the empty asm hides that it is unchanged):
   // it and what follows from it would otherwise be held in registers over the loop
