@@ -97,8 +97,6 @@ void destroy_op(wf_op* op) {
     dfree(c.vals);
     dfree(c.work);
     dfree(c.pieces);
-    dfree(c.cuts);
-    dfree(c.parts);
     dfree(c.prune);
     dfree(c.htiles);
     dfree(c.hvals);
@@ -343,18 +341,20 @@ wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint
   ch.cut_lines.assign(nk / NCLS, 0);
   ch.sum_cells = 0;
   std::vector<WorkItem> part;
-  std::vector<std::pair<int64_t, int32_t>> order;
+  std::vector<std::pair<int32_t, int32_t>> whole, cut, order;   // (minus rows, piece)
   auto rows_of = [&](size_t k) {
     int64_t n = 0;
     for (int i = 0; i < rn[k]; ++i) n += wis[r0[k] + i].nrows;
     return n;
   };
+  all.reserve(wis.size() + wis.size() / 4);
   int64_t slot = 0, bin_rows = 0;   // slot of the bin's (chunk's) next piece; its rows
-  for (size_t k2 = 0; k2 < 2 * nk; ++k2) {
-    const bool scatter = k2 >= nk;
-    const size_t k = scatter ? k2 - nk : k2, bin = k / NCLS;
+  std::vector<int64_t> largest(nk, 0);   // rows of a scattering piece
+  for (size_t j2 = 0; j2 < 2 * nk; ++j2) {
+    const bool scatter = j2 < nk;   // first, so that de-gridding can take the same pieces
+    const size_t k = scatter ? j2 : j2 - nk, k2 = scatter ? nk + k : k, bin = k / NCLS;
     if (k % NCLS == 0) {
-      ch.cut_0[bin] = (int32_t)cuts.size();
+      if (scatter) ch.cut_0[bin] = (int32_t)cuts.size();
       slot = bin_rows = 0;
       for (int c = 0; c < NCLS; ++c) bin_rows += rows_of(k + c);
     }
@@ -363,7 +363,16 @@ wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint
     const PieceRule rule = piece_rule(scatter, store, (int)(k % NCLS), rows, bin_rows);
     if (k % NCLS == 0) ch.rows0[bin] = rows;
     const int64_t most = std::max(rule.least, (rows / rule.share + 7) / 8 * 8);
+    if (scatter) {
+      largest[k] = most;
+    } else if (most == largest[k]) {
+      ch.pc_0[k] = ch.pc_0[nk + k];
+      ch.pc_n[k] = ch.pc_n[nk + k];
+      continue;
+    }
     part.clear();
+    whole.clear();
+    cut.clear();
     for (int i = 0; i < rn[k]; ++i) {
       const WorkItem& w = wis[r0[k] + i];
       const int n = (int)((w.nrows + most - 1) / most);
@@ -390,38 +399,44 @@ wf_status schedule_rows(ChanOp& ch, const std::vector<WorkItem>& wis, const uint
           parts.push_back(CutPart{p.bin, p.box});
           slot += (int64_t)(u1 - u0) * (v1 - v0);
         }
+        // by rows (one class: patches of much the same size); whole items come largest first
+        int32_t key = -p.nrows;
+        if (n == 1 && !whole.empty()) key = std::max(key, whole.back().first);
+        (n > 1 ? cut : whole).emplace_back(key, (int32_t)part.size());
         part.push_back(p);
       }
     }
     ch.sum_cells = std::max(ch.sum_cells, slot);
-    // largest first, by taps (read once: a comparison that looks them up is most of the time)
-    order.clear();
-    for (size_t i = 0; i < part.size(); ++i) {
-      const int64_t T = (meta[part[i].row0] >> 16) & 0xff;
-      order.emplace_back(-T * T * part[i].nrows, (int32_t)i);
+    if (cut.empty()) {
+      ch.pc_0[k2] = (int32_t)all.size();
+      ch.pc_n[k2] = (int32_t)part.size();
+      all.insert(all.end(), part.begin(), part.end());
+      continue;
     }
-    std::sort(order.begin(), order.end());
+    std::sort(cut.begin(), cut.end());
+    order.resize(part.size());
+    std::merge(whole.begin(), whole.end(), cut.begin(), cut.end(), order.begin());
     ch.pc_0[k2] = (int32_t)all.size();
     ch.pc_n[k2] = (int32_t)part.size();
     for (const auto& o : order) all.push_back(part[o.second]);
   }
-  wf_status st;
-  auto room = [](DevBuf& b, size_t bytes) { return dalloc(b, std::max<size_t>(bytes, 8)); };
   const size_t nb = sizeof(WorkItem) * all.size(), nc = sizeof(CutItem) * cuts.size(),
                np = sizeof(CutPart) * parts.size();
-  if ((st = room(ch.pieces, nb)) != WF_OK || (st = room(ch.cuts, nc)) != WF_OK ||
-      (st = room(ch.parts, np)) != WF_OK)
-    return st;
-  WF_HIP(hipMemcpyAsync(ch.pieces.p, all.data(), nb, hipMemcpyHostToDevice, s));
-  WF_HIP(hipMemcpyAsync(ch.cuts.p, cuts.data(), nc, hipMemcpyHostToDevice, s));
-  WF_HIP(hipMemcpyAsync(ch.parts.p, parts.data(), np, hipMemcpyHostToDevice, s));
+  ch.cuts_at = nb;
+  ch.parts_at = (nb + nc + 7) / 8 * 8;
+  wf_status st = dalloc(ch.pieces, std::max<size_t>(ch.parts_at + np, 8));
+  if (st != WF_OK) return st;
+  char* d = (char*)ch.pieces.p;
+  if (nb) WF_HIP(hipMemcpyAsync(d, all.data(), nb, hipMemcpyHostToDevice, s));
+  if (nc) WF_HIP(hipMemcpyAsync(d + ch.cuts_at, cuts.data(), nc, hipMemcpyHostToDevice, s));
+  if (np) WF_HIP(hipMemcpyAsync(d + ch.parts_at, parts.data(), np, hipMemcpyHostToDevice, s));
   WF_HIP(hipStreamSynchronize(s));
   return WF_OK;
 }
 
 // Device bytes of a split's tables.
 double item_bytes(const ItemTables& t) {
-  return (double)(t.work.bytes + t.pieces.bytes + t.cuts.bytes + t.parts.bytes);
+  return (double)(t.work.bytes + t.pieces.bytes);
 }
 
 // Whether a w-layer's modulation (eq. 6) is formed from its column table by the FP32 series of the
@@ -1262,8 +1277,10 @@ Lane lane_of(wf_op* op, int b, hipStream_t caller) {
 
 // What the row kernels go over for bin (on the fly: chunk) k on lane L.
 RowPieces pieces_of(const wf_op* op, const ChanOp& ch, int64_t k, const Lane& L, bool scatter) {
-  RowPieces pc{(const WorkItem*)ch.pieces.p, {}, {}, (const CutItem*)ch.cuts.p + ch.cut_0[k],
-               (const CutPart*)ch.parts.p, ch.rows0[k], scatter ? ch.cut_n[k] : 0,
+  const char* tables = (const char*)ch.pieces.p;
+  RowPieces pc{(const WorkItem*)tables, {}, {},
+               (const CutItem*)(tables + ch.cuts_at) + ch.cut_0[k],
+               (const CutPart*)(tables + ch.parts_at), ch.rows0[k], scatter ? ch.cut_n[k] : 0,
                ch.cut_lines[k], (double2*)op->br[L.b].sums.p};
   const size_t at = (scatter ? ch.pc_n.size() / 2 : 0) + (size_t)k * NCLS;
   for (int c = 0; c < NCLS; ++c) {
@@ -2068,10 +2085,11 @@ wf_status retune_channel(wf_op* op, int c, int32_t maxrows, const int8_t* tsh = 
     ~Undo() {
       ItemTables& now = ch;
       if (!done) std::swap(now, old);
-      for (DevBuf* b : {&old.work, &old.pieces, &old.cuts, &old.parts}) dfree(*b);
+      dfree(old.work);
+      dfree(old.pieces);
     }
   } undo{ch, ch};
-  ch.work = ch.pieces = ch.cuts = ch.parts = DevBuf{};
+  ch.work = ch.pieces = DevBuf{};
   ch.bin_tsh = ntsh;
   std::vector<uint8_t> trow(M);
   for (int64_t r = 0; r < M; ++r) trow[r] = (uint8_t)((meta[r] >> 16) & 0xff);

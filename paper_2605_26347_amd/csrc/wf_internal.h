@@ -256,13 +256,15 @@ struct ItemTables {
   DevBuf work;
   // what the row kernels are launched on: the items of `work` cut into pieces (schedule_rows),
   // largest first, per (bin, class), or per (chunk, class) on the fly: first piece, count; all
-  // of those for de-gridding, then all of those for the kernels that scatter
+  // of those for de-gridding, then all of those for the kernels that scatter (one list where
+  // both cut to the same size)
   DevBuf pieces;
   std::vector<int32_t> pc_0, pc_n;
   std::vector<int64_t> rows0;              // rows of class 0, per bin or chunk
   // the items that were cut, per bin (chunk): first, count, grid lines of the largest box; their
-  // pieces' slots and boxes; and the cells that the largest bin's pieces need in a branch
-  DevBuf cuts, parts;
+  // tables lie behind the pieces in the same allocation (byte offsets); and the cells that the
+  // largest bin's pieces need in a branch
+  size_t cuts_at = 0, parts_at = 0;
   std::vector<int32_t> cut_0, cut_n, cut_lines;
   int64_t sum_cells = 0;
 };

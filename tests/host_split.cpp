@@ -1,6 +1,6 @@
 // CPU driver of host decisions and of the work-item tables (built and run by
-// tests/test_host_split.py): the C ABI's source with the device memory calls replaced by host memory, whose allocations can be made
-// to fail.  No kernel is launched.
+// tests/test_host_split.py): the C ABI's source with the device memory calls replaced by host
+// memory, whose allocations can be made to fail.  No kernel is launched.
 #include "../paper_2605_26347_amd/csrc/wf_abi.cpp"
 
 #include <cstdio>
@@ -122,6 +122,13 @@ static bool held(const DevBuf& b, size_t bytes) {
   return b.p && g_live.count(b.p) && b.bytes >= bytes;
 }
 
+static const CutItem* cuts_of(const ChanOp& ch) {
+  return (const CutItem*)((const char*)ch.pieces.p + ch.cuts_at);
+}
+static const CutPart* parts_of(const ChanOp& ch) {
+  return (const CutPart*)((const char*)ch.pieces.p + ch.parts_at);
+}
+
 // Items and pieces cover each row of the channel once, within their tables.
 static void covered(const ChanOp& ch) {
   CHECK(held(ch.work, sizeof(WorkItem) * ch.nwork));
@@ -149,8 +156,8 @@ static void covered(const ChanOp& ch) {
 static void cut_items_meet(const ChanOp& ch) {
   const WorkItem* wk = (const WorkItem*)ch.work.p;
   const WorkItem* pc = (const WorkItem*)ch.pieces.p;
-  const CutItem* cuts = (const CutItem*)ch.cuts.p;
-  const CutPart* parts = (const CutPart*)ch.parts.p;
+  const CutItem* cuts = cuts_of(ch);
+  const CutPart* parts = parts_of(ch);
   struct B {
     int u0, v0, w, h;
   };
@@ -173,11 +180,12 @@ static void cut_items_meet(const ChanOp& ch) {
     std::sort(by_slot.begin(), by_slot.end());
     size_t at = 0;
     int64_t cells = 0, items = 0;
-    CHECK(held(ch.cuts, sizeof(CutItem) * (ch.cut_0[bin] + ch.cut_n[bin])));
+    CHECK(held(ch.pieces, ch.cuts_at + sizeof(CutItem) * (ch.cut_0[bin] + ch.cut_n[bin])));
     for (int i = 0; i < ch.cut_n[bin]; ++i) {
       const CutItem& it = cuts[ch.cut_0[bin] + i];
       const B ib = box(it.box);
-      CHECK(it.nparts > 1 && held(ch.parts, sizeof(CutPart) * (it.part0 + it.nparts)));
+      CHECK(it.nparts > 1);
+      CHECK(held(ch.pieces, ch.parts_at + sizeof(CutPart) * (it.part0 + it.nparts)));
       CHECK(box_lines(it.box) <= ch.cut_lines[bin]);
       int rows = 0;
       const WorkItem* from = nullptr;
@@ -249,10 +257,10 @@ static void failed_resplit() {
     CHECK(std::equal(meta.begin(), meta.end(), (uint32_t*)ch.meta.p));
     covered(ch);
   }
-  CHECK(fails >= 4);
+  CHECK(fails >= 2);
   CHECK(ch.max_rows == 256 && ch.bin_tsh == wide);
   CHECK(item_bytes(ch) != item_bytes(was) && ch.info.mem_g_bytes == rows + item_bytes(ch));
-  CHECK(item_bytes(ch) >= sizeof(WorkItem) * 3.0 * ch.nwork);   // items and two lists of pieces
+  CHECK(item_bytes(ch) >= sizeof(WorkItem) * 2.0 * ch.nwork);   // items and their pieces
   CHECK(g_live.size() == blocks);
   covered(ch);
   cut_items_meet(ch);
@@ -274,7 +282,7 @@ static void lane_after_resplit() {
   CHECK(op.br[0].sums.bytes > was);
   const RowPieces pc = pieces_of(&op, ch, 0, L, true);
   CHECK(pc.sums == op.br[0].sums.p && g_live.count(pc.sums));
-  CHECK(g_live.count((void*)pc.items) && pc.cuts == (const CutItem*)ch.cuts.p);
+  CHECK(g_live.count((void*)pc.items) && pc.cuts == cuts_of(ch));
 }
 
 // Branches that run out of memory, at each of their allocations, leave a complete first one.
